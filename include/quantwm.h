@@ -181,14 +181,14 @@ quantwm_status quantwm_calib_pack(const quantwm_config* cfg, const void* mu_k, c
 /* QSAC/PSAC statistics and centroids for every (b, h):
  *  - Eq. 6: M = (1/n_hist) sum q q^T over q_hist [B,n_hist,H,d] (fp64 on the device);
  *  - Eq. 8: w_c = M_cc / (tr(M)/d);
- *  - Eq. 15: U_r = top-r eigenvectors of M (host fp64 Jacobi; sorted by
+ *  - Eq. 15: U_r = top-r eigenvectors of M (fp64 on the device; sorted by
  *    eigenvalue, each vector's largest-magnitude entry positive);
  *  - Eq. 3: centroids by deterministic Lloyd K-means (kmeans_iters rounds) on
  *    k_calib / v_calib [B,n_calib,H,d], starting from tokens floor(j*n/Kc).
  * n_hist == 0 is the cold start: w = 1 and U_r = 0, so PSAC stores zero rows.
  * Needs n_calib >= 1 and a device workspace of
- * quantwm_calibrate_workspace_bytes(). The call synchronises `stream` (it reads
- * M back to the host). */
+ * quantwm_calibrate_workspace_bytes(). The call synchronises `stream`: its
+ * results are complete when it returns. */
 quantwm_status quantwm_calibrate(const quantwm_config* cfg, const void* q_hist, int64_t n_hist,
                                  const void* k_calib, const void* v_calib, int64_t n_calib,
                                  int32_t kmeans_iters, void* calib, void* workspace,
@@ -211,7 +211,8 @@ quantwm_status quantwm_stats_update(const quantwm_config* cfg, const void* q, in
  * M = sums / count (Eq. 6), w (Eq. 8), U_r (Eq. 15), and the centroids by
  * K-means on k_calib / v_calib (Eq. 3), e.g. the chunk that opens the epoch.
  * Workspace: quantwm_calibrate_workspace_bytes(cfg, 0, n_calib). Synchronises
- * `stream` (it reads the sums back to the host). */
+ * `stream` (it reads the count back to the host, and its results are complete
+ * when it returns). */
 quantwm_status quantwm_calibrate_epoch(const quantwm_config* cfg, const void* stats, const void* k_calib,
                                        const void* v_calib, int64_t n_calib, int32_t kmeans_iters, void* calib,
                                        void* workspace, size_t workspace_bytes, void* stream);

@@ -2,8 +2,7 @@
 
 Translation units compile in parallel: append.hip (fp32) and append_bf16.hip
 once per (head_dim, group size), attend.hip once per (element type, head_dim, PSAC rank padding),
-attend_host.hip, calib.hip, coef.hip, api.hip and the host eigensolver; the
-objects link into ``paper_2609_26425_amd/libquantwm.so``.
+attend_host.hip, calib.hip, basis.hip, coef.hip and api.hip; the objects link into ``paper_2609_26425_amd/libquantwm.so``.
 """
 from __future__ import annotations
 
@@ -47,9 +46,8 @@ def _units():
                               ["-fno-honor-nans", f"-DQWM_ATTEND_T={t}", f"-DQWM_ATTEND_D={d}",
                                f"-DQWM_ATTEND_RP={rp}"]))
     units.append(("attend_host.o", "attend_host.hip", ["-fno-honor-nans"]))
-    for name in ("calib", "coef", "api"):
+    for name in ("calib", "basis", "coef", "api"):
         units.append((f"{name}.o", f"{name}.hip", []))
-    units.append(("eigh.o", "eigh.cpp", ["-x", "hip"]))
     return units
 
 
@@ -101,8 +99,8 @@ SAN_OUT = os.path.join(BUILD, "san", "libquantwm_san.so")
 
 
 def build_sanitized() -> str:
-    """libquantwm with its host-side code (the C ABI's validation and launches,
-    the host eigensolver) built with AddressSanitizer and UndefinedBehaviorSanitizer,
+    """libquantwm with its host-side code (the C ABI's validation and launches)
+    built with AddressSanitizer and UndefinedBehaviorSanitizer,
     linked with the kernel objects of the normal build (built first if missing).
     A process that loads it must preload clang's ASan runtime."""
     units = _units()
@@ -114,7 +112,7 @@ def build_sanitized() -> str:
              "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
     objs = []
     for obj, src, extra in units:
-        if src in ("api.hip", "eigh.cpp"):
+        if src == "api.hip":
             out = os.path.join(san, obj)
             cmd = [_hipcc(), *HIPFLAGS, *extra, *flags, "-c", os.path.join(CSRC, src), "-o", out]
             p = subprocess.run(cmd, capture_output=True, text=True)

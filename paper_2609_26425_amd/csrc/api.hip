@@ -249,79 +249,23 @@ quantwm_status quantwm_calib_pack(const quantwm_config* cfg, const void* mu_k, c
   return ok();
 }
 
-// Eq. 8 and Eq. 15 on the host in fp64 from the second moment M ([B*H][d][d],
-// already divided by the token count), then Eq. 3 centroids on the device.
-// cold: no historical Query yet (w = 1, U_r = 0).
-static quantwm_status finish_calibration(const quantwm_config& c, const std::vector<double>& M, bool cold,
+// Eq. 8 and Eq. 15 from the second moment m ([B*H][d][d] on the device, divided
+// by div unless that is 0), then Eq. 3 centroids, all on the device. cold: no
+// historical Query yet (w = 1, U_r = 0). workspace: [B*H][d][d] doubles (may be
+// m), then the K-means assignments.
+static quantwm_status finish_calibration(const quantwm_config& c, const double* m, int64_t div, bool cold,
                                          const void* k_calib, const void* v_calib, int64_t n_calib,
-                                         int32_t kmeans_iters, uint8_t* cal, int32_t* assign, hipStream_t s) {
-  const quantwm_calib_layout C = qwm::calib_layout(c);
-  const int bh = c.batch * c.heads, d = c.head_dim, r = c.rank, e = qwm::elem_bytes(c);
+                                         int32_t kmeans_iters, uint8_t* cal, void* workspace, hipStream_t s) {
+  double* scratch = static_cast<double*>(workspace);
+  const int64_t mb = int64_t(c.batch) * c.heads * c.head_dim * c.head_dim * int64_t(sizeof(double));
+  uint8_t* assign = static_cast<uint8_t*>(workspace) + qwm::align256(mb);
   hipError_t he;
-  std::vector<float> w(size_t(bh) * d), lam(size_t(bh) * (r > 0 ? r : 1));
-  std::vector<uint8_t> ut(size_t(bh) * (r > 0 ? r : 1) * d * e, 0);
-  std::vector<double> ev(d), vt(size_t(d) * d);
-  const bool full = c.metric == QWM_METRIC_FULL;
-  std::vector<float> mn(full ? size_t(bh) * d * d : 0);
-  for (int i = 0; i < bh; ++i) {
-    const double* Mi = M.data() + size_t(i) * d * d;
-    double tr = 0.0;
-    for (int k = 0; k < d; ++k) tr += Mi[size_t(k) * d + k];
-    float* wi = w.data() + size_t(i) * d;
-    float* mi = full ? mn.data() + size_t(i) * d * d : nullptr;
-    if (cold || tr == 0.0) {  // cold start: uniform sensitivity, PSAC inactive
-      for (int k = 0; k < d; ++k) wi[k] = 1.0f;
-      for (int k = 0; k < r; ++k) lam[size_t(i) * r + k] = 0.0f;
-      if (mi)
-        for (int k = 0; k < d * d; ++k) mi[k] = (k / d == k % d) ? 1.0f : 0.0f;
-      continue;
-    }
-    for (int k = 0; k < d; ++k) wi[k] = (float)(Mi[size_t(k) * d + k] / (tr / (double)d));
-    // the full metric: M over the mean of its diagonal (its diagonal is w)
-    if (mi)
-      for (int k = 0; k < d * d; ++k) mi[k] = (float)(Mi[k] / (tr / (double)d));
-    qwm::host_eigh(Mi, d, ev.data(), vt.data());
-    for (int k = 0; k < r; ++k) {
-      lam[size_t(i) * r + k] = (float)ev[k];
-      for (int cc = 0; cc < d; ++cc) {
-        const double x = vt[size_t(k) * d + cc];
-        uint8_t* dst = ut.data() + ((size_t(i) * r + k) * d + cc) * e;
-        if (e == 4) {
-          const float f = (float)x;
-          std::memcpy(dst, &f, 4);
-        } else {  // bf16, one rounding from fp64 (nearest, ties to even)
-          uint64_t u;
-          std::memcpy(&u, &x, 8);
-          u += ((uint64_t(1) << 44) - 1) + ((u >> 45) & 1);
-          u &= ~((uint64_t(1) << 45) - 1);
-          double y;
-          std::memcpy(&y, &u, 8);
-          const float f = (float)y;
-          uint32_t fb;
-          std::memcpy(&fb, &f, 4);
-          const uint16_t hb = uint16_t(fb >> 16);
-          std::memcpy(dst, &hb, 2);
-        }
-      }
-    }
-  }
-  auto put = [&](int64_t off, const void* src, size_t row) -> hipError_t {
-    if (row == 0) return hipSuccess;
-    return hipMemcpy2DAsync(cal + off, size_t(C.slab_bytes), src, row, row, size_t(bh), hipMemcpyHostToDevice, s);
-  };
-  if ((he = put(C.w, w.data(), size_t(d) * 4)) != hipSuccess) return hip_fail(he, "w upload");
-  if (full && (he = put(C.m, mn.data(), size_t(d) * d * 4)) != hipSuccess) return hip_fail(he, "m upload");
-  if (r > 0) {
-    if ((he = put(C.u_t, ut.data(), size_t(r) * d * e)) != hipSuccess) return hip_fail(he, "u_t upload");
-    if ((he = put(C.lam, lam.data(), size_t(r) * 4)) != hipSuccess) return hip_fail(he, "lam upload");
-  }
+  if ((he = qwm::launch_basis(c, m, div, cold, scratch, cal, s)) != hipSuccess) return hip_fail(he, "basis");
   // Eq. 3: Key and Value centroids by Lloyd K-means on the calibration tokens.
-  if ((he = qwm::launch_kmeans(c, k_calib, n_calib, kmeans_iters, cal, C.mu_k, assign, s)) != hipSuccess)
-    return hip_fail(he, "kmeans (K)");
-  if ((he = qwm::launch_kmeans(c, v_calib, n_calib, kmeans_iters, cal, C.mu_v, assign, s)) != hipSuccess)
-    return hip_fail(he, "kmeans (V)");
+  if ((he = qwm::launch_kmeans(c, k_calib, v_calib, n_calib, kmeans_iters, cal, assign, s)) != hipSuccess)
+    return hip_fail(he, "kmeans");
   if ((he = qwm::launch_derive_constants(c, cal, s)) != hipSuccess) return hip_fail(he, "derive");
-  // the host staging buffers die with this call
+  // the call returns with its results complete
   if ((he = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(he, "calibrate sync");
   return ok();
 }
@@ -342,21 +286,14 @@ quantwm_status quantwm_calibrate(const quantwm_config* cfg, const void* q_hist, 
                 quantwm_calibrate_workspace_bytes(cfg, n_hist, n_calib));
   const quantwm_config& c = *cfg;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int bh = c.batch * c.heads, d = c.head_dim;
-  double* m_dev = static_cast<double*>(workspace);
-  int32_t* assign = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(workspace) +
-                                               qwm::align256(int64_t(size_t(bh) * d * d * sizeof(double))));
-  hipError_t he;
+  double* m = static_cast<double*>(workspace);
   // Eq. 6 on the device
-  std::vector<double> M(size_t(bh) * d * d, 0.0);
   if (n_hist > 0) {
-    if ((he = qwm::launch_second_moment(c, q_hist, n_hist, m_dev, s)) != hipSuccess) return hip_fail(he, "moment");
-    if ((he = hipMemcpyAsync(M.data(), m_dev, M.size() * sizeof(double), hipMemcpyDeviceToHost, s)) != hipSuccess)
-      return hip_fail(he, "moment readback");
-    if ((he = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(he, "moment sync");
+    const hipError_t he = qwm::launch_moment(c, q_hist, n_hist, m, nullptr, s);
+    if (he != hipSuccess) return hip_fail(he, "moment");
   }
-  return finish_calibration(c, M, n_hist == 0, k_calib, v_calib, n_calib, kmeans_iters, static_cast<uint8_t*>(calib),
-                            assign, s);
+  return finish_calibration(c, m, 0, n_hist == 0, k_calib, v_calib, n_calib, kmeans_iters, static_cast<uint8_t*>(calib),
+                            workspace, s);
 }
 
 size_t quantwm_stats_bytes(const quantwm_config* cfg) {
@@ -372,7 +309,7 @@ quantwm_status quantwm_stats_update(const quantwm_config* cfg, const void* q, in
   QWM_TRY(check_dev(stats, "stats"));
   int64_t* count = static_cast<int64_t*>(stats);
   double* sums = reinterpret_cast<double*>(static_cast<uint8_t*>(stats) + 256);
-  const hipError_t he = qwm::launch_moment_accumulate(*cfg, q, n, sums, count, static_cast<hipStream_t>(stream));
+  const hipError_t he = qwm::launch_moment(*cfg, q, n, sums, count, static_cast<hipStream_t>(stream));
   if (he != hipSuccess) return hip_fail(he, "stats update");
   return ok();
 }
@@ -392,21 +329,16 @@ quantwm_status quantwm_calibrate_epoch(const quantwm_config* cfg, const void* st
                 quantwm_calibrate_workspace_bytes(cfg, 0, n_calib));
   const quantwm_config& c = *cfg;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t nm = size_t(c.batch) * c.heads * c.head_dim * c.head_dim;
-  std::vector<double> M(nm);
   int64_t count = 0;
   hipError_t he;
   if ((he = hipMemcpyAsync(&count, stats, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (he = hipMemcpyAsync(M.data(), static_cast<const uint8_t*>(stats) + 256, nm * sizeof(double),
-                           hipMemcpyDeviceToHost, s)) != hipSuccess)
+      (he = hipStreamSynchronize(s)) != hipSuccess)
     return hip_fail(he, "stats readback");
-  if ((he = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(he, "stats sync");
   if (count < 0) return fail(QWM_ERR_INVALID_ARG, "stats count is negative (buffer not initialised?)");
   // Eq. 6: M = sum / count, the same fp64 division as the one-pass moment
-  if (count > 0)
-    for (double& x : M) x = x / (double)count;
-  return finish_calibration(c, M, count == 0, k_calib, v_calib, n_calib, kmeans_iters, static_cast<uint8_t*>(calib),
-                            static_cast<int32_t*>(workspace), s);
+  const double* sums = reinterpret_cast<const double*>(static_cast<const uint8_t*>(stats) + 256);
+  return finish_calibration(c, sums, count, count == 0, k_calib, v_calib, n_calib, kmeans_iters,
+                            static_cast<uint8_t*>(calib), workspace, s);
 }
 
 quantwm_status quantwm_append(const quantwm_config* cfg, const void* calib, void* cache, int64_t n_cached,

@@ -27,10 +27,16 @@ __device__ inline void store_rn(bf16* p, double x) { *p = to_bf16_rn(x); }
 // With the full metric the Key constants expand (k - mu_j)^T Mn (k - mu_j)
 // instead: p_j = Mn mu_j (fp32, columns in order), a_jc = -2 p_jc and
 // b_j = sum_c p_jc mu_jc; the k^T Mn k term is the same for every centroid.
+//
+// A block takes kDeriveRows centroids of one head (the first block of a head
+// also its small fields). Latency bounds it (a serial b_j sum per centroid):
+// one block per head took 96 us at 10 heads, 128 centroids and d = 128, these take 32 us.
+constexpr int kDeriveRows = 16;
 template <typename T>
 __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_calib_layout C, int d, int G,
                                                      int Kc, int r, int full) {
   uint8_t* slab = calib + int64_t(blockIdx.x) * C.slab_bytes;
+  const int j0 = blockIdx.y * kDeriveRows, j1 = min(j0 + kDeriveRows, Kc);
   const float* w = reinterpret_cast<const float*>(slab + C.w);
   float* wg = reinterpret_cast<float*>(slab + C.wg);
   const T* mk = reinterpret_cast<const T*>(slab + C.mu_k);
@@ -39,13 +45,8 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
   float* bk = reinterpret_cast<float*>(slab + C.b_k);
   float* av = reinterpret_cast<float*>(slab + C.a_v);
   float* bv = reinterpret_cast<float*>(slab + C.b_v);
-  for (int g = threadIdx.x; g < d / G; g += 256) {
-    float s = 0.0f;
-    for (int c = g * G; c < (g + 1) * G; ++c) s = s + w[c];
-    wg[g] = s;
-  }
   const float* mm = reinterpret_cast<const float*>(slab + C.m);
-  for (int i = threadIdx.x; i < Kc * d; i += 256) {
+  for (int i = j0 * d + threadIdx.x; i < j1 * d; i += 256) {
     const int c = i % d;
     const float mkv = ldf(mk + i), mvv = ldf(mv + i);
     if (full) {
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
     // remainder a - p0, and p2 = a - p0 - p1, which has at most 8 significant
     // bits left and so is a BF16 value (for |a| above 2^-110 or so)
     uint16_t* pl = reinterpret_cast<uint16_t*>(slab + C.a_k3);
-    for (int i = threadIdx.x; i < Kc * d; i += 256) {
+    for (int i = j0 * d + threadIdx.x; i < j1 * d; i += 256) {
       const float av0 = ak[i];
       const uint32_t u0 = __float_as_uint(av0) & 0xffff0000u;
       const float r1 = av0 - __uint_as_float(u0);
@@ -76,37 +77,57 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
       pl[2 * Kc * d + i] = __builtin_bit_cast(uint16_t, bf16(r2));
     }
   }
-  const T* ut = reinterpret_cast<const T*>(slab + C.u_t);
-  float* udr = reinterpret_cast<float*>(slab + C.u_dr);
-  const int rs = r == 0 ? 0 : (r <= 16 ? 16 : 32);
-  for (int i = threadIdx.x; i < rs * d; i += 256) {
-    const int c = i / rs, k = i % rs;
-    udr[i] = k < r ? ldf(ut + k * d + c) : 0.0f;
-  }
-  for (int j = threadIdx.x; j < Kc; j += 256) {
-    float sk = 0.0f, sv = 0.0f;
-    for (int c = 0; c < d; ++c) {
-      const float mkv = ldf(mk + j * d + c), mvv = ldf(mv + j * d + c);
-      // full metric: -0.5 a_jc is p_jc exactly
-      sk = __builtin_fmaf(full ? -0.5f * ak[j * d + c] : w[c] * mkv, mkv, sk);
-      sv = __builtin_fmaf(mvv, mvv, sv);
+  if (threadIdx.x < 2 * kDeriveRows) {
+    // even threads the Keys' b_j, odd ones the Values'
+    const int j = j0 + threadIdx.x / 2;
+    const bool val = threadIdx.x & 1;
+    if (j < j1) {
+      float acc = 0.0f;
+#pragma unroll 16
+      for (int c = 0; c < d; ++c) {
+        const float mu = ldf((val ? mv : mk) + j * d + c);
+        // full metric: -0.5 a_jc is p_jc exactly
+        const float p = val ? mu : (full ? -0.5f * ak[j * d + c] : w[c] * mu);
+        acc = __builtin_fmaf(p, mu, acc);
+      }
+      (val ? bv : bk)[j] = acc;
     }
-    bk[j] = sk;
-    bv[j] = sv;
+  }
+  if (blockIdx.y == 0) {
+    for (int g = threadIdx.x; g < d / G; g += 256) {
+      float s = 0.0f;
+      for (int c = g * G; c < (g + 1) * G; ++c) s = s + w[c];
+      wg[g] = s;
+    }
+    const T* ut = reinterpret_cast<const T*>(slab + C.u_t);
+    float* udr = reinterpret_cast<float*>(slab + C.u_dr);
+    const int rs = r == 0 ? 0 : (r <= 16 ? 16 : 32);
+    for (int i = threadIdx.x; i < rs * d; i += 256) {
+      const int c = i / rs, k = i % rs;
+      udr[i] = k < r ? ldf(ut + k * d + c) : 0.0f;
+    }
   }
   if constexpr (sizeof(T) == 2) {
     // binary16 copies of the BF16 tables for the attention producers, scaled by a
     // power of two: the table's largest magnitude lands in [2^14, 2^15), so each
     // component of at least 2^-31 of it is exact in binary16 (BF16 keeps 8
-    // significant bits) and none overflows
+    // significant bits) and none overflows. Every block scans the whole tables.
     __shared__ float s_max[2][256];
-    float mxk = 0.0f, mxv = 0.0f;
-    for (int i = threadIdx.x; i < Kc * d; i += 256) {
-      mxk = fmaxf(mxk, fabsf(ldf(mk + i)));
-      mxv = fmaxf(mxv, fabsf(ldf(mv + i)));
+    float mx[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      const uint4* p = reinterpret_cast<const uint4*>(side ? mv : mk);
+#pragma unroll 4
+      for (int i = threadIdx.x; i < Kc * d / 8; i += 256) {
+        const uint4 u = p[i];
+        const uint32_t q[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          mx[side] = fmaxf(mx[side], fmaxf(fabsf(__uint_as_float(q[k] << 16)), fabsf(__uint_as_float(q[k] & 0xffff0000u))));
+      }
     }
-    s_max[0][threadIdx.x] = mxk;
-    s_max[1][threadIdx.x] = mxv;
+    s_max[0][threadIdx.x] = mx[0];
+    s_max[1][threadIdx.x] = mx[1];
     __syncthreads();
     for (int st = 128; st > 0; st /= 2) {
       if (threadIdx.x < st) {
@@ -120,11 +141,11 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
     if (s_max[1][0] > 0.0f) { int x; frexpf(s_max[1][0], &x); ev = x - 15; }
     _Float16* hk = reinterpret_cast<_Float16*>(slab + C.mu_k16);
     _Float16* hv = reinterpret_cast<_Float16*>(slab + C.mu_v16);
-    for (int i = threadIdx.x; i < Kc * d; i += 256) {
+    for (int i = j0 * d + threadIdx.x; i < j1 * d; i += 256) {
       hk[i] = (_Float16)ldexpf(ldf(mk + i), -ek);
       hv[i] = (_Float16)ldexpf(ldf(mv + i), -ev);
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && blockIdx.y == 0) {
       int32_t* e16 = reinterpret_cast<int32_t*>(slab + C.e16);
       e16[0] = ek;
       e16[1] = ev;
@@ -159,75 +180,189 @@ __global__ __launch_bounds__(256) void pack_kernel(uint8_t* calib, quantwm_calib
   }
 }
 
-// Eq. 6 without the 1/N: thread (i, j) sums q_i q_j over the tokens in order,
-// in fp64 (each fp32 x fp32 product is exact in fp64), then divides by n.
-template <typename T>
-__global__ __launch_bounds__(256) void moment_kernel(const T* q, int64_t n, int heads, int d, double* m) {
+// Eight consecutive channels as doubles
+__device__ inline void load8(const float* p, double (&x)[8]) {
+  const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+  x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+  x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+}
+__device__ inline void load8(const bf16* p, double (&x)[8]) {
+  const uint4 u = *reinterpret_cast<const uint4*>(p);
+  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    x[2 * k] = (double)__uint_as_float(w[k] << 16);
+    x[2 * k + 1] = (double)__uint_as_float(w[k] & 0xffff0000u);
+  }
+}
+
+// Eq. 6: sums of q_i q_j over the tokens in order, in fp64 (each fp32 x fp32
+// product is exact in fp64). ACC continues the stored sums of a statistics
+// buffer, so a sequence of updates equals one pass over all the tokens, and
+// adds n to *count; otherwise the sums start at 0 and are divided by n, and the
+// tiles below the diagonal mirror those above (the product commutes).
+//
+// A block takes a 32 x 32 tile of one head's matrix, 2 x 2 elements per thread,
+// and stages 64 tokens at a time in LDS as doubles, the next 64 loading while
+// these multiply. The token order is a serial chain of n fmas per element, so
+// the tile is kept small to spread a head over many CUs, and 2 x 2 halves the
+// LDS reads per fma. 4,680 tokens of 10 heads at d = 128 (ACC): 1,230 us with a
+// thread per element and no staging, 260 us so.
+constexpr int kMomTile = 32, kMomTok = 64;
+template <typename T, bool ACC>
+__global__ __launch_bounds__(256) void moment_kernel(const T* q, int64_t n, int heads, int d, double* m,
+                                                     int64_t* count) {
+  __shared__ __attribute__((aligned(16))) double s_q[2][kMomTok][kMomTile];
   const int64_t bh = blockIdx.y;
-  const int b = int(bh / heads), h = int(bh % heads);
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= d * d) return;
-  const int i = p / d, j = p % d;
-  const T* base = q + (int64_t(b) * n * heads + h) * d;
-  double acc = 0.0;
-  for (int64_t t = 0; t < n; ++t) {
-    const T* row = base + t * heads * d;
-    acc = __builtin_fma((double)ldf(row + i), (double)ldf(row + j), acc);
+  const int b = int(bh / heads), h = int(bh % heads), tid = threadIdx.x;
+  const int nt = d / kMomTile;
+  int ti = 0, tj = blockIdx.x;  // tile row and column: all of them, or those with ti <= tj
+  if constexpr (ACC) {
+    ti = blockIdx.x / nt;
+    tj = blockIdx.x % nt;
+  } else {
+    while (tj >= nt - ti) { tj -= nt - ti; ++ti; }
+    tj += ti;
   }
-  m[bh * d * d + p] = acc / (double)n;
+  const T* base = q + (int64_t(b) * n * heads + h) * d;
+  const int64_t stride = int64_t(heads) * d;
+  // staging: thread -> (token, eight channels) of each side
+  const int st = tid / 4, sc = (tid % 4) * 8;
+  double xi[8], xj[8];
+  auto fetch = [&](int64_t t0) {
+    const int64_t t = t0 + st < n ? t0 + st : n - 1;
+    load8(base + t * stride + ti * kMomTile + sc, xi);
+    load8(base + t * stride + tj * kMomTile + sc, xj);
+  };
+  const int i2 = (tid / 16) * 2, j2 = (tid % 16) * 2;
+  double* mh = m + bh * d * d;
+  const int gi = ti * kMomTile + i2, gj = tj * kMomTile + j2;
+  double a00 = 0.0, a01 = 0.0, a10 = 0.0, a11 = 0.0;
+  if constexpr (ACC) {
+    a00 = mh[gi * d + gj];
+    a01 = mh[gi * d + gj + 1];
+    a10 = mh[(gi + 1) * d + gj];
+    a11 = mh[(gi + 1) * d + gj + 1];
+  }
+  fetch(0);
+  for (int64_t t0 = 0; t0 < n; t0 += kMomTok) {
+    __syncthreads();  // the previous tokens are used up
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) {
+      *reinterpret_cast<double2*>(&s_q[0][st][sc + k]) = make_double2(xi[k], xi[k + 1]);
+      *reinterpret_cast<double2*>(&s_q[1][st][sc + k]) = make_double2(xj[k], xj[k + 1]);
+    }
+    __syncthreads();
+    if (t0 + kMomTok < n) fetch(t0 + kMomTok);
+    const int nn = n - t0 < kMomTok ? int(n - t0) : kMomTok;
+    auto step = [&](int t) __attribute__((always_inline)) {
+      const double2 x = *reinterpret_cast<const double2*>(&s_q[0][t][i2]);
+      const double2 y = *reinterpret_cast<const double2*>(&s_q[1][t][j2]);
+      a00 = __builtin_fma(x.x, y.x, a00);
+      a01 = __builtin_fma(x.x, y.y, a01);
+      a10 = __builtin_fma(x.y, y.x, a10);
+      a11 = __builtin_fma(x.y, y.y, a11);
+    };
+    if (nn == kMomTok) {
+#pragma unroll 16
+      for (int t = 0; t < kMomTok; ++t) step(t);
+    } else {
+      for (int t = 0; t < nn; ++t) step(t);
+    }
+  }
+  if constexpr (!ACC) {
+    a00 /= (double)n;
+    a01 /= (double)n;
+    a10 /= (double)n;
+    a11 /= (double)n;
+  }
+  mh[gi * d + gj] = a00;
+  mh[gi * d + gj + 1] = a01;
+  mh[(gi + 1) * d + gj] = a10;
+  mh[(gi + 1) * d + gj + 1] = a11;
+  if (!ACC && ti != tj) {
+    mh[gj * d + gi] = a00;
+    mh[(gj + 1) * d + gi] = a01;
+    mh[gj * d + gi + 1] = a10;
+    mh[(gj + 1) * d + gi + 1] = a11;
+  }
+  if (ACC && bh == 0 && blockIdx.x == 0 && tid == 0) *count += n;
 }
 
-// Eq. 6 online: continues the fp64 token-order sums of q q^T from their stored
-// values, so a sequence of updates equals one pass over all the tokens.
+// K-means (Eq. 3) of the Keys (side 0) and Values (side 1) of every head, both
+// sides in each launch.
+struct KmArgs {
+  const void* x[2];     // [B, n, H, d]
+  int64_t o_mu[2];      // tables in the slab
+  int64_t o_b[2];       // [Kc] f32 in the slab: |mu_j|^2 between the rounds (derive_kernel overwrites them)
+  uint8_t* assign;      // [2][BH][n]
+  uint8_t* calib;
+  int64_t slab, n;
+  int heads, d, Kc, bh;
+};
+
+// sum over the block's d threads (one or two waves), the same on each
+__device__ inline float block_sum(float v, int d, float* lds) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if (d == 64) return v;
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return lds[0] + lds[1];
+}
+
+// Initial centroids: tokens floor(j n / Kc). One block of d threads per centroid.
 template <typename T>
-__global__ __launch_bounds__(256) void moment_accumulate_kernel(const T* q, int64_t n, int heads, int d, double* sums,
-                                                                int64_t* count) {
+__global__ __launch_bounds__(128) void km_init_kernel(const KmArgs a) {
+  __shared__ float s_red[2];
+  const int j = blockIdx.x, c = threadIdx.x, side = blockIdx.z;
   const int64_t bh = blockIdx.y;
-  const int b = int(bh / heads), h = int(bh % heads);
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (bh == 0 && p == 0) *count += n;
-  if (p >= d * d) return;
-  const int i = p / d, j = p % d;
-  const T* base = q + (int64_t(b) * n * heads + h) * d;
-  double acc = sums[bh * d * d + p];
-  for (int64_t t = 0; t < n; ++t) {
-    const T* row = base + t * heads * d;
-    acc = __builtin_fma((double)ldf(row + i), (double)ldf(row + j), acc);
-  }
-  sums[bh * d * d + p] = acc;
+  const int b = int(bh / a.heads), h = int(bh % a.heads);
+  uint8_t* slab = a.calib + bh * a.slab;
+  const int64_t t = (int64_t(j) * a.n) / a.Kc;
+  const T v = reinterpret_cast<const T*>(a.x[side])[((int64_t(b) * a.n + t) * a.heads + h) * a.d + c];
+  reinterpret_cast<T*>(slab + a.o_mu[side])[j * a.d + c] = v;
+  const float f = ldf(&v), s = block_sum(f * f, a.d, s_red);
+  if (c == 0) reinterpret_cast<float*>(slab + a.o_b[side])[j] = s;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void km_init_kernel(const T* x, int64_t n, int heads, int d, int Kc,
-                                                      uint8_t* calib, int64_t slab_bytes, int64_t o_mu) {
-  const int64_t bh = blockIdx.x;
-  const int b = int(bh / heads), h = int(bh % heads);
-  T* mu = reinterpret_cast<T*>(calib + bh * slab_bytes + o_mu);
-  for (int i = threadIdx.x; i < Kc * d; i += 256) {
-    const int j = i / d, c = i % d;
-    const int64_t t = (int64_t(j) * n) / Kc;
-    mu[i] = x[((int64_t(b) * n + t) * heads + h) * d + c];
+// Squared Euclidean distance in channel order (fp32, no contraction): the
+// literal form that decides every assignment. Rows are 16-byte aligned.
+template <int D>
+__device__ inline float literal_distance(const bf16* x, const bf16* mu) {
+  float acc = 0.0f;
+#pragma unroll 4
+  for (int c = 0; c < D; c += 8) {
+    const uint4 u = *reinterpret_cast<const uint4*>(x + c), m = *reinterpret_cast<const uint4*>(mu + c);
+    const uint32_t xw[4] = {u.x, u.y, u.z, u.w}, mw[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float e0 = __uint_as_float(xw[k] << 16) - __uint_as_float(mw[k] << 16);
+      acc = acc + e0 * e0;
+      const float e1 = __uint_as_float(xw[k] & 0xffff0000u) - __uint_as_float(mw[k] & 0xffff0000u);
+      acc = acc + e1 * e1;
+    }
   }
+  return acc;
 }
 
-// Lloyd assignment: nearest centroid by squared Euclidean distance summed in
-// channel order (fp32, no contraction), ties to the lower id.
+// Lloyd assignment of fp32 tokens: nearest centroid by the literal distance,
+// ties to the lower id.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void km_assign_kernel(const T* x, int64_t n, int heads, int Kc,
-                                                        const uint8_t* calib, int64_t slab_bytes, int64_t o_mu,
-                                                        int32_t* assign) {
-  const int64_t bh = blockIdx.y;
-  const int b = int(bh / heads), h = int(bh % heads);
+__global__ __launch_bounds__(256) void km_assign_kernel(const KmArgs a) {
+  const int64_t bh = blockIdx.y, n = a.n;
+  const int side = blockIdx.z;
+  const int b = int(bh / a.heads), h = int(bh % a.heads);
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
   if (t >= n) return;
-  const T* __restrict__ mu = reinterpret_cast<const T*>(calib + bh * slab_bytes + o_mu);
-  const T* row = x + ((int64_t(b) * n + t) * heads + h) * D;
+  const T* __restrict__ mu = reinterpret_cast<const T*>(a.calib + bh * a.slab + a.o_mu[side]);
+  const T* row = reinterpret_cast<const T*>(a.x[side]) + ((int64_t(b) * n + t) * a.heads + h) * D;
   float xv[D];
 #pragma unroll
   for (int c = 0; c < D; ++c) xv[c] = ldf(row + c);
   int best = 0;
   float bd = 0.0f;
-  for (int j = 0; j < Kc; ++j) {
+  for (int j = 0; j < a.Kc; ++j) {
     float acc = 0.0f;
 #pragma unroll
     for (int c = 0; c < D; ++c) {
@@ -236,59 +371,231 @@ __global__ __launch_bounds__(256) void km_assign_kernel(const T* x, int64_t n, i
     }
     if (j == 0 || acc < bd) { best = j; bd = acc; }
   }
-  assign[bh * n + t] = best;
+  a.assign[(int64_t(side) * a.bh + bh) * n + t] = uint8_t(best);
 }
 
-// Lloyd update: thread (j, c) sums x_tc over the tokens of cluster j in token
-// order (fp64), then stores the mean rounded once to the table type; an empty
-// cluster keeps its centroid.
-template <typename T>
-__global__ __launch_bounds__(256) void km_update_kernel(const T* x, int64_t n, int heads, int d, int Kc,
-                                                        uint8_t* calib, int64_t slab_bytes, int64_t o_mu,
-                                                        const int32_t* assign) {
-  const int64_t bh = blockIdx.y;
-  const int b = int(bh / heads), h = int(bh % heads);
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= Kc * d) return;
-  const int j = p / d, c = p % d;
-  const int32_t* as = assign + bh * n;
-  const T* base = x + (int64_t(b) * n * heads + h) * d + c;
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// Lloyd assignment of BF16 tokens: the literal distance decides, but it is only
+// evaluated where it can matter. The matrix cores give d'_j = |mu_j|^2 - 2 x.mu_j
+// for 32 centroids x 32 tokens at a time (a wave's tokens; lanes i and i + 32
+// share token i and hold 16 centroids each per block). With u = 2^-24 and
+// S = |x|^2 + max_j |mu_j|^2:
+//   - the products are exact and the fp32 sums of d terms err by less than
+//     2 (d + 16) u per unit of sum |terms| (twice the d u of one rounding per
+//     term), so d'_j is within E = 4 (d + 16) u S of the real value;
+//   - the literal distance (d terms, three roundings each) is within
+//     E_L = 2 (d + 4) u S of it (|x - mu_j|^2 <= 2 S).
+// A centroid whose d' exceeds the smallest by more than 2 (E + E_L) therefore
+// has the larger literal distance. Where a second centroid is inside that bound
+// (about 1% of the tokens), a second pass over the same products evaluates the
+// literal distance of every centroid inside it.
+// Latency bounds it; 4,680 tokens of 10 heads, 128 centroids, Keys and Values:
+// 660 us for the two literal launches, 40 us so.
+template <int D>
+__global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
+  constexpr int NS = D / 16;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n32 = lane & 31, hf = lane >> 5;
+  const int64_t bh = blockIdx.y, n = a.n;
+  const int side = blockIdx.z, Kc = a.Kc;
+  const int b = int(bh / a.heads), h = int(bh % a.heads);
+  const int64_t t0 = int64_t(blockIdx.x) * 128 + wv * 32;
+  if (t0 >= n) return;  // the whole wave is past the chunk
+  const int64_t t = t0 + n32 < n ? t0 + n32 : n - 1;
+  const uint8_t* slab = a.calib + bh * a.slab;
+  const bf16* mu = reinterpret_cast<const bf16*>(slab + a.o_mu[side]);
+  const float* bj = reinterpret_cast<const float*>(slab + a.o_b[side]);
+  const bf16* row = reinterpret_cast<const bf16*>(a.x[side]) + ((int64_t(b) * n + t) * a.heads + h) * D;
+  // k index 8 hf + i of step s is channel 16 s + 8 hf + i on both operands
+  bf16x8 xf[NS];
+  float xx = 0.0f;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    xf[s] = *reinterpret_cast<const bf16x8*>(row + 16 * s + 8 * hf);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) xx = __builtin_fmaf((float)xf[s][k], (float)xf[s][k], xx);
+  }
+  xx += __shfl_xor(xx, 32);
+  auto block = [&](int j0, float (&d)[16]) __attribute__((always_inline)) {
+    const bf16* mrow = mu + int64_t(min(j0 + n32, Kc - 1)) * D + 8 * hf;
+    bf16x8 mf[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) mf[s] = *reinterpret_cast<const bf16x8*>(mrow + 16 * s);
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mf[s], xf[s], acc, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int j = j0 + (i / 4) * 8 + hf * 4 + (i % 4);
+      d[i] = j < Kc ? __builtin_fmaf(-2.0f, acc[i], bj[j]) : __builtin_inff();
+    }
+  };
+  float d1 = __builtin_inff(), d2 = __builtin_inff(), bmax = 0.0f;
+  int best = 0;
+  for (int j0 = 0; j0 < Kc; j0 += 32) {
+    float d[16];
+    block(j0, d);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int j = j0 + (i / 4) * 8 + hf * 4 + (i % 4);
+      bmax = fmaxf(bmax, j < Kc ? bj[j] : 0.0f);
+      d2 = fminf(d2, fmaxf(d1, d[i]));
+      best = d[i] < d1 ? j : best;
+      d1 = fminf(d1, d[i]);
+    }
+  }
+  {
+    const float p1 = __shfl_xor(d1, 32), p2 = __shfl_xor(d2, 32);
+    const int pb = __shfl_xor(best, 32);
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+    d2 = fminf(fminf(d2, p2), fmaxf(d1, p1));
+    best = p1 < d1 ? pb : best;  // a tie is inside the bound and decided below
+    d1 = fminf(d1, p1);
+  }
+  const float bound = (xx + bmax) * ((8.0f * (D + 16) + 4.0f * (D + 4)) * 0x1p-24f);
+  // not greater rather than less or equal: NaN or infinite inputs take the literal form too
+  const bool near = !(d2 - d1 > bound);
+  if (__any(near)) {
+    int lb = 0x7fffffff;
+    float ld = __builtin_inff();
+    for (int j0 = 0; j0 < Kc; j0 += 32) {
+      float d[16];
+      block(j0, d);
+      // every candidate of this lane in the block, in increasing order
+      uint32_t cand = 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) cand |= uint32_t(near && !(d[i] - d1 > bound)) << i;
+      while (cand) {
+        const int i = __ffs(cand) - 1, j = j0 + (i / 4) * 8 + hf * 4 + (i % 4);
+        cand &= cand - 1;
+        if (j < Kc) {
+          const float l = literal_distance<D>(row, mu + int64_t(j) * D);
+          if (lb == 0x7fffffff || l < ld) { lb = j; ld = l; }
+        }
+      }
+    }
+    const float pd = __shfl_xor(ld, 32);
+    const int pb = __shfl_xor(lb, 32);
+    if (pb != 0x7fffffff && (lb == 0x7fffffff || pd < ld || (pd == ld && pb < lb))) lb = pb;
+    if (near && lb != 0x7fffffff) best = lb;
+  }
+  if (hf == 0 && t0 + n32 < n) a.assign[(int64_t(side) * a.bh + bh) * n + t] = uint8_t(best);
+}
+
+// Lloyd update: sums x_tc over the tokens of cluster j in token order (fp64),
+// then stores the mean rounded once to the table type; an empty cluster keeps
+// its centroid. A block of d threads per (cluster, head, side): it lists the
+// cluster's tokens of a run of kKmList in order (each thread scans kKmList / d
+// ids, a prefix sum places its finds), then every thread adds its channel over
+// the list, 16 rows in flight. 4,680 tokens of 10 heads, 128 centroids, Keys and
+// Values: 665 us when each (cluster, channel) scanned all ids, 30 us so.
+constexpr int kKmList = 8192;
+template <typename T, int D>
+__global__ __launch_bounds__(D) void km_update_kernel(const KmArgs a) {
+  constexpr int PT = kKmList / D;  // ids per thread and run
+  __shared__ uint16_t s_list[kKmList];
+  __shared__ int s_cnt[2];
+  __shared__ float s_red[2];
+  const int j = blockIdx.x, c = threadIdx.x, side = blockIdx.z, lane = c & 63, wave = c >> 6;
+  const int64_t bh = blockIdx.y, n = a.n;
+  const int b = int(bh / a.heads), h = int(bh % a.heads);
+  const uint8_t* as = a.assign + (int64_t(side) * a.bh + bh) * n;
+  const T* x = reinterpret_cast<const T*>(a.x[side]) + (int64_t(b) * n * a.heads + h) * D + c;
+  const int64_t stride = int64_t(a.heads) * D;
   double sum = 0.0;
   int64_t cnt = 0;
-  for (int64_t t = 0; t < n; ++t)
-    if (as[t] == j) {
-      sum += (double)ldf(base + t * heads * d);
-      ++cnt;
+  for (int64_t run = 0; run < n; run += kKmList) {
+    const int nr = n - run < kKmList ? int(n - run) : kKmList;
+    // ids of this thread: [lo, hi) of the run, shared out evenly in multiples of 4
+    const int per = min(PT, ((nr + D - 1) / D + 3) / 4 * 4);
+    const int lo = min(nr, c * per), hi = min(nr, lo + per);
+    int mine = 0;
+    for (int i = lo; i < hi; i += 4) {
+      uint32_t w = 0;
+      if (i + 4 <= hi) __builtin_memcpy(&w, as + run + i, 4);
+      else
+        for (int k = 0; i + k < hi; ++k) w |= uint32_t(as[run + i + k]) << (8 * k);
+      for (int k = 0; k < 4; ++k) mine += i + k < hi && int((w >> (8 * k)) & 255) == j;
     }
-  if (cnt > 0) store_rn(reinterpret_cast<T*>(calib + bh * slab_bytes + o_mu) + p, sum / (double)cnt);
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(incl, o);
+      incl += lane >= o ? y : 0;
+    }
+    __syncthreads();  // the previous run's list is used up
+    if (lane == 63) s_cnt[wave] = incl;
+    __syncthreads();
+    int at = incl - mine + (wave ? s_cnt[0] : 0);
+    const int total = s_cnt[0] + (D == 128 ? s_cnt[1] : 0);
+    if (mine)
+      for (int i = lo; i < hi; ++i)
+        if (int(as[run + i]) == j) s_list[at++] = uint16_t(i);
+    __syncthreads();
+    int i = 0;
+    for (; i + 16 <= total; i += 16) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = ldf(x + (run + s_list[i + k]) * stride);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) sum += (double)v[k];
+    }
+    if (i < total) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = ldf(x + (run + s_list[min(i + k, total - 1)]) * stride);
+#pragma unroll
+      for (int k = 0; k < 16; ++k)
+        if (i + k < total) sum += (double)v[k];
+    }
+    cnt += total;
+  }
+  if (cnt == 0) return;  // block-uniform
+  uint8_t* slab = a.calib + bh * a.slab;
+  T* mu = reinterpret_cast<T*>(slab + a.o_mu[side]) + j * D + c;
+  T m;
+  store_rn(&m, sum / (double)cnt);
+  *mu = m;
+  const float f = ldf(&m), s = block_sum(f * f, D, s_red);
+  if (c == 0) reinterpret_cast<float*>(slab + a.o_b[side])[j] = s;
+}
+
+template <typename T, int D>
+hipError_t kmeans_td(const KmArgs& a, int iters, hipStream_t s) {
+  const dim3 gc((unsigned)a.Kc, (unsigned)a.bh, 2);
+  hipLaunchKernelGGL(km_init_kernel<T>, gc, dim3(D), 0, s, a);
+  for (int it = 0; it < iters; ++it) {
+    if constexpr (sizeof(T) == 2)
+      hipLaunchKernelGGL((km_assign_mfma_kernel<D>), dim3((unsigned)((a.n + 127) / 128), (unsigned)a.bh, 2), dim3(256),
+                         0, s, a);
+    else
+      hipLaunchKernelGGL((km_assign_kernel<T, D>), dim3((unsigned)((a.n + 255) / 256), (unsigned)a.bh, 2), dim3(256),
+                         0, s, a);
+    hipLaunchKernelGGL((km_update_kernel<T, D>), gc, dim3(D), 0, s, a);
+  }
+  return hipGetLastError();
 }
 
 template <typename T>
-hipError_t kmeans_t(const quantwm_config& c, const T* x, int64_t n, int iters, uint8_t* calib, int64_t o_mu,
-                    int32_t* assign, hipStream_t s) {
-  const quantwm_calib_layout C = calib_layout(c);
-  const int bh = c.batch * c.heads, d = c.head_dim, Kc = c.n_centroids;
-  hipLaunchKernelGGL(km_init_kernel<T>, dim3(bh), dim3(256), 0, s, x, n, c.heads, d, Kc, calib, C.slab_bytes, o_mu);
-  for (int it = 0; it < iters; ++it) {
-    const dim3 ga((unsigned)((n + 255) / 256), (unsigned)bh);
-    if (d == 64)
-      hipLaunchKernelGGL((km_assign_kernel<T, 64>), ga, dim3(256), 0, s, x, n, c.heads, Kc, calib, C.slab_bytes, o_mu,
-                         assign);
-    else
-      hipLaunchKernelGGL((km_assign_kernel<T, 128>), ga, dim3(256), 0, s, x, n, c.heads, Kc, calib, C.slab_bytes,
-                         o_mu, assign);
-    const dim3 gu((unsigned)((Kc * d + 255) / 256), (unsigned)bh);
-    hipLaunchKernelGGL(km_update_kernel<T>, gu, dim3(256), 0, s, x, n, c.heads, d, Kc, calib, C.slab_bytes, o_mu,
-                       assign);
-  }
-  return hipGetLastError();
+void launch_moment_t(const quantwm_config& c, const T* q, int64_t n, double* m, int64_t* count, hipStream_t s) {
+  const int nt = c.head_dim / kMomTile;
+  const unsigned bh = unsigned(c.batch * c.heads);
+  if (count)
+    hipLaunchKernelGGL((moment_kernel<T, true>), dim3(unsigned(nt * nt), bh), dim3(256), 0, s, q, n, c.heads,
+                       c.head_dim, m, count);
+  else
+    hipLaunchKernelGGL((moment_kernel<T, false>), dim3(unsigned(nt * (nt + 1) / 2), bh), dim3(256), 0, s, q, n,
+                       c.heads, c.head_dim, m, count);
 }
 
 }  // namespace
 
 hipError_t launch_derive_constants(const quantwm_config& c, uint8_t* calib, hipStream_t s) {
   const quantwm_calib_layout C = calib_layout(c);
-  const dim3 grid((unsigned)(c.batch * c.heads));
+  const dim3 grid((unsigned)(c.batch * c.heads), (unsigned)((c.n_centroids + kDeriveRows - 1) / kDeriveRows));
   const int full = c.metric == QWM_METRIC_FULL;
   if (c.dtype == QWM_BF16)
     hipLaunchKernelGGL(derive_kernel<bf16>, grid, dim3(256), 0, s, calib, C, c.head_dim, c.group_size, c.n_centroids,
@@ -314,33 +621,20 @@ hipError_t launch_pack_tables(const quantwm_config& c, const void* mu_k, const v
   return launch_derive_constants(c, calib, s);
 }
 
-hipError_t launch_second_moment(const quantwm_config& c, const void* q, int64_t n, double* m, hipStream_t s) {
-  const int d = c.head_dim;
-  const dim3 grid((unsigned)((d * d + 255) / 256), (unsigned)(c.batch * c.heads));
-  if (c.dtype == QWM_BF16)
-    hipLaunchKernelGGL(moment_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)q, n, c.heads, d, m);
-  else
-    hipLaunchKernelGGL(moment_kernel<float>, grid, dim3(256), 0, s, (const float*)q, n, c.heads, d, m);
+// Eq. 6 over n tokens: the mean of q q^T into m, or (count given) the sums continued and n added to *count.
+hipError_t launch_moment(const quantwm_config& c, const void* q, int64_t n, double* m, int64_t* count, hipStream_t s) {
+  if (c.dtype == QWM_BF16) launch_moment_t<bf16>(c, (const bf16*)q, n, m, count, s);
+  else launch_moment_t<float>(c, (const float*)q, n, m, count, s);
   return hipGetLastError();
 }
 
-hipError_t launch_moment_accumulate(const quantwm_config& c, const void* q, int64_t n, double* sums, int64_t* count,
-                                    hipStream_t s) {
-  const int d = c.head_dim;
-  const dim3 grid((unsigned)((d * d + 255) / 256), (unsigned)(c.batch * c.heads));
-  if (c.dtype == QWM_BF16)
-    hipLaunchKernelGGL(moment_accumulate_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)q, n, c.heads, d, sums,
-                       count);
-  else
-    hipLaunchKernelGGL(moment_accumulate_kernel<float>, grid, dim3(256), 0, s, (const float*)q, n, c.heads, d, sums,
-                       count);
-  return hipGetLastError();
-}
-
-hipError_t launch_kmeans(const quantwm_config& c, const void* x, int64_t n, int iters, uint8_t* calib, int64_t o_mu,
-                         int32_t* assign, hipStream_t s) {
-  if (c.dtype == QWM_BF16) return kmeans_t<bf16>(c, (const bf16*)x, n, iters, calib, o_mu, assign, s);
-  return kmeans_t<float>(c, (const float*)x, n, iters, calib, o_mu, assign, s);
+hipError_t launch_kmeans(const quantwm_config& c, const void* k, const void* v, int64_t n, int iters, uint8_t* calib,
+                         uint8_t* assign, hipStream_t s) {
+  const quantwm_calib_layout C = calib_layout(c);
+  const KmArgs a = {{k, v}, {C.mu_k, C.mu_v}, {C.b_k, C.b_v}, assign, calib, C.slab_bytes, n,
+                    c.heads, c.head_dim, c.n_centroids, c.batch * c.heads};
+  if (c.dtype == QWM_BF16) return c.head_dim == 64 ? kmeans_td<bf16, 64>(a, iters, s) : kmeans_td<bf16, 128>(a, iters, s);
+  return c.head_dim == 64 ? kmeans_td<float, 64>(a, iters, s) : kmeans_td<float, 128>(a, iters, s);
 }
 
 }  // namespace qwm

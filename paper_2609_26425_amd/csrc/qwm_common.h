@@ -172,10 +172,12 @@ hipError_t launch_derive_constants(const quantwm_config& c, uint8_t* calib, hipS
 hipError_t launch_pack_tables(const quantwm_config& c, const void* mu_k, const void* mu_v,
                               const float* w, const void* u_t, const float* lam, const float* m,
                               uint8_t* calib, hipStream_t s);
-hipError_t launch_moment_accumulate(const quantwm_config& c, const void* q, int64_t n, double* sums, int64_t* count,
-                                    hipStream_t s);
-hipError_t launch_second_moment(const quantwm_config& c, const void* q, int64_t n, double* m_out,
-                                hipStream_t s);
+// Eq. 6: mean of q q^T over n tokens into m; with count, the sums in m continued and n added to *count
+hipError_t launch_moment(const quantwm_config& c, const void* q, int64_t n, double* m, int64_t* count, hipStream_t s);
+// w, the full metric's matrix, U_r and the eigenvalues of the slabs from the second moments m ([B*H][d][d], divided by
+// div unless that is 0; cold: none yet). scratch: [B*H][d][d], may be m.
+hipError_t launch_basis(const quantwm_config& c, const double* m, int64_t div, bool cold, double* scratch,
+                        uint8_t* calib, hipStream_t s);
 hipError_t launch_attend_combine(const AttendArgs& a, int d, int batch, bool is_bf16, hipStream_t s);
 hipError_t launch_coef_count(const quantwm_config& c, const void* cache, int64_t start, int n, void* counts,
                              hipStream_t s);
@@ -185,10 +187,8 @@ hipError_t launch_coef_unpack(const quantwm_config& c, const void* record, int l
                               int n, hipStream_t s);
 // QWM_STORE_SPARSE: stores one append call's staged rows into the pools and the directory
 hipError_t launch_coef_commit(const quantwm_config& c, void* cache, int64_t n_cached, int64_t n, hipStream_t s);
-hipError_t launch_kmeans(const quantwm_config& c, const void* x, int64_t n, int iters, uint8_t* calib,
-                         int64_t o_mu, int32_t* assign_ws, hipStream_t s);
-
-// Host fp64 symmetric eigensolver: eigenvalues descending, eigenvectors as rows.
-void host_eigh(const double* a, int n, double* lam, double* vecs_t);
+// Eq. 3 centroids of Keys and Values; assign: 2 * B*H * n bytes of scratch
+hipError_t launch_kmeans(const quantwm_config& c, const void* k, const void* v, int64_t n, int iters, uint8_t* calib,
+                         uint8_t* assign, hipStream_t s);
 
 }  // namespace qwm
