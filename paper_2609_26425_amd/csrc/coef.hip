@@ -195,9 +195,18 @@ namespace {
 // scale (sparse), whichever is smaller with one mask bit per slot as the sparse
 // index (ties dense); rows in slot order after the rows of the slots below; a
 // row past the pool's end is counted and not stored. Then the directory of the
-// chunk's tiles: the tile holding n_cached keeps its rows below n_cached. One
-// wave per 64-slot tile, four tiles per pass.
-__global__ __launch_bounds__(256) void coef_commit_kernel(uint8_t* cache, CacheLayout L, int64_t n_cached, int n) {
+// chunk's tiles: the tile holding n_cached keeps its rows below n_cached.
+//
+// A block takes a run of 64-slot tiles, four (one per wave) at a time, and counts
+// the chunk's kept rows before them itself (2 bytes per row, from L2), so no
+// block waits for another; at most kCommitBlocks blocks per head bound that
+// repeated count. 120 heads x 3,120 rows of rank 32: 100 us with one block per head and
+// byte copies, 10 us so. Blocks read the entry of the tile below n_cached while
+// the chunk's first block may rewrite it, but only its base and the mask bits
+// below n_cached, which stay as they are.
+constexpr int kCommitTiles = 4, kCommitBlocks = 64;
+__global__ __launch_bounds__(64 * kCommitTiles) void coef_commit_kernel(uint8_t* cache, CacheLayout L,
+                                                                        int64_t n_cached, int n, int64_t per_block) {
   const int64_t bh = blockIdx.x;
   const int r = L.r, tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
   const int64_t tiles = L.slots / 64;
@@ -206,55 +215,76 @@ __global__ __launch_bounds__(256) void coef_commit_kernel(uint8_t* cache, CacheL
   const uint8_t* st_s = cache + L.k_st_scale + bh * L.stage * 2;
   uint8_t* pc = cache + L.k_coef + bh * L.pool * r;
   uint8_t* ps = cache + L.k_cscale + bh * L.pool * 2;
-  __shared__ uint32_t s_cnt[4];
-  __shared__ int64_t s_fill;
-  __shared__ uint32_t s_kept;
-  // pool rows used by the slots below n_cached (read before this block writes)
-  if (tid == 0) {
-    int64_t f = 0;
-    if (n_cached > 0) {
-      const int64_t T = (n_cached - 1) / 64;
-      const int used = int(n_cached - 64 * T);
-      const uint64_t below = used == 64 ? ~uint64_t(0) : ((uint64_t(1) << used) - 1);
-      const uint8_t* e = dir + T * 16;
-      const uint64_t m = uint64_t(ld32(e + 8)) | (uint64_t(ld32(e + 12)) << 32);
-      f = int64_t(ld32(e)) + __popcll(m & below);
-    }
-    s_fill = f;
-    s_kept = 0;
+  const int64_t T0 = n_cached / 64, T1 = (n_cached + n + 63) / 64;  // the chunk's tiles [T0, T1)
+  // this block's: [Tb, Te)
+  const int64_t Tb = T0 + int64_t(blockIdx.y) * per_block, Te = Tb + per_block < T1 ? Tb + per_block : T1;
+  // kept rows of the chunk, and of its part before this block's tiles
+  const int64_t t_before = Tb * 64 > n_cached ? Tb * 64 - n_cached : 0;
+  __shared__ uint32_t s_kept[kCommitTiles], s_bef[kCommitTiles], s_cnt[kCommitTiles];
+  uint32_t kept_l = 0, bef_l = 0;
+  for (int t = tid; t < n; t += 64 * kCommitTiles) {
+    const uint32_t k = ld16(st_s + 2 * t) != 0;
+    kept_l += k;
+    bef_l += t < t_before ? k : 0;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    kept_l += __shfl_xor(kept_l, o);
+    bef_l += __shfl_xor(bef_l, o);
+  }
+  if (lane == 0) {
+    s_kept[wave] = kept_l;
+    s_bef[wave] = bef_l;
+  }
+  // pool rows used by the slots below n_cached
+  int64_t fill = 0;
+  if (n_cached > 0) {
+    const int64_t T = (n_cached - 1) / 64;
+    const int used = int(n_cached - 64 * T);
+    const uint64_t below = used == 64 ? ~uint64_t(0) : ((uint64_t(1) << used) - 1);
+    const uint8_t* e = dir + T * 16;
+    const uint64_t m = uint64_t(ld32(e + 8)) | (uint64_t(ld32(e + 12)) << 32);
+    fill = int64_t(ld32(e)) + __popcll(m & below);
   }
   __syncthreads();
-  uint32_t c = 0;
-  for (int t = tid; t < n; t += 256) c += ld16(st_s + 2 * t) != 0;
-  atomicAdd(&s_kept, c);
-  __syncthreads();
-  const int64_t kept = s_kept, fill = s_fill;
+  int64_t kept = 0, before = 0;
+  for (int w = 0; w < kCommitTiles; ++w) {
+    kept += s_kept[w];
+    before += s_bef[w];
+  }
   const bool sparse = kept * (r + 2) + (n + 7) / 8 < int64_t(n) * (r + 2);
-  const int64_t T0 = n_cached / 64, T1 = (n_cached + n + 63) / 64;  // the chunk's tiles [T0, T1)
-  int64_t stored_before = 0;  // stored rows of the chunk before the current pass
-  uint32_t over = 0;
-  for (int64_t Tp = T0; Tp < T1; Tp += 4) {
+  if (!sparse) before = t_before < n ? t_before : n;
+  for (int64_t Tp = Tb; Tp < Te; Tp += kCommitTiles) {
     const int64_t T = Tp + wave;
     const int64_t slot = T * 64 + lane, t = slot - n_cached;
-    const bool in = T < T1 && t >= 0 && t < n;
+    const bool in = T < Te && t >= 0 && t < n;
     const bool stored = in && (!sparse || ld16(st_s + 2 * t) != 0);
     const uint64_t sb = __ballot(stored);
     const int64_t rank = __popcll(sb & ((uint64_t(1) << lane) - 1));  // stored rows of this tile below the lane
     if (lane == 0) s_cnt[wave] = __popcll(sb);
     __syncthreads();
-    int64_t before = stored_before;  // stored rows of the chunk before tile T
-    for (int w = 0; w < wave; ++w) before += s_cnt[w];
-    const int64_t pass_total = int64_t(s_cnt[0]) + s_cnt[1] + s_cnt[2] + s_cnt[3];
-    const int64_t pos = fill + before + rank;
+    int64_t first = before;  // stored rows of the chunk before tile T
+    for (int w = 0; w < kCommitTiles; ++w) {
+      if (w < wave) first += s_cnt[w];
+      before += s_cnt[w];
+    }
+    __syncthreads();  // s_cnt is reused by the next pass
+    const int64_t pos = fill + first + rank;
     const bool fit = stored && pos < L.pool;
-    if (stored && !fit) ++over;
     if (fit) {
-      for (int i = 0; i < r; ++i) pc[pos * r + i] = st_c[t * r + i];
-      ps[pos * 2] = st_s[2 * t];
-      ps[pos * 2 + 1] = st_s[2 * t + 1];
+      const uint8_t* src = st_c + t * r;
+      uint8_t* dst = pc + pos * r;
+      if (r % 16 == 0) {
+        for (int i = 0; i < r; i += 16) *reinterpret_cast<uint4*>(dst + i) = *reinterpret_cast<const uint4*>(src + i);
+      } else if (r % 4 == 0) {
+        for (int i = 0; i < r; i += 4) *reinterpret_cast<uint32_t*>(dst + i) = *reinterpret_cast<const uint32_t*>(src + i);
+      } else {
+        for (int i = 0; i < r; ++i) dst[i] = src[i];
+      }
+      *reinterpret_cast<uint16_t*>(ps + pos * 2) = *reinterpret_cast<const uint16_t*>(st_s + 2 * t);
     }
     const uint64_t fb = __ballot(fit);
-    if (lane == 0 && T < T1) {
+    if (lane == 0 && T < Te) {
       uint8_t* e = dir + T * 16;
       uint64_t m = fb;
       if (T * 64 < n_cached) {
@@ -263,31 +293,28 @@ __global__ __launch_bounds__(256) void coef_commit_kernel(uint8_t* cache, CacheL
         const uint64_t old = uint64_t(ld32(e + 8)) | (uint64_t(ld32(e + 12)) << 32);
         m |= old & ((uint64_t(1) << i0) - 1);
       } else {
-        const int64_t b0 = fill + before < L.pool ? fill + before : L.pool;
+        const int64_t b0 = fill + first < L.pool ? fill + first : L.pool;
         st32(e, uint32_t(b0));
         st32(e + 4, 0);
       }
       st32(e + 8, uint32_t(m));
       st32(e + 12, uint32_t(m >> 32));
+      // rows without room in the pool
+      const uint32_t over = __popcll(sb) - __popcll(fb);
+      if (over) atomicAdd(reinterpret_cast<uint32_t*>(cache + L.k_over + bh * 4), over);
     }
-    stored_before += pass_total;
-    __syncthreads();  // s_cnt is reused by the next pass
   }
-  // rows without room in the pool, summed over the block
-  __shared__ uint32_t s_over;
-  if (tid == 0) s_over = 0;
-  __syncthreads();
-  if (over) atomicAdd(&s_over, over);
-  __syncthreads();
-  if (tid == 0 && s_over) st32(cache + L.k_over + bh * 4, ld32(cache + L.k_over + bh * 4) + s_over);
 }
 
 }  // namespace
 
 hipError_t launch_coef_commit(const quantwm_config& c, void* cache, int64_t n_cached, int64_t n, hipStream_t s) {
   const CacheLayout L = cache_layout(c);
-  hipLaunchKernelGGL(coef_commit_kernel, dim3(unsigned(int64_t(c.batch) * c.heads)), dim3(256), 0, s,
-                     static_cast<uint8_t*>(cache), L, n_cached, int(n));
+  const int64_t tiles = (n_cached + n + 63) / 64 - n_cached / 64;
+  const int64_t per = ((tiles + kCommitBlocks - 1) / kCommitBlocks + kCommitTiles - 1) / kCommitTiles * kCommitTiles;
+  const dim3 grid(unsigned(int64_t(c.batch) * c.heads), unsigned((tiles + per - 1) / per));
+  hipLaunchKernelGGL(coef_commit_kernel, grid, dim3(64 * kCommitTiles), 0, s, static_cast<uint8_t*>(cache), L, n_cached,
+                     int(n), per);
   return hipGetLastError();
 }
 
