@@ -82,8 +82,7 @@ typedef struct {
  *   order, lam from the calibration block); otherwise the row and its scale are
  *   stored as zeros.
  * Every attention call decodes both options, in every form (plain, key split,
- * active chunk in one launch or two parts, calibration epochs in one launch or
- * per epoch). */
+ * active chunk, calibration epochs). */
 #define QWM_STORE_SCALE_I8 1
 #define QWM_STORE_GATE 2
 /* QWM_STORE_SPARSE (needs rank >= 1 and coef_stage >= 1): the per-chunk choice
@@ -275,25 +274,23 @@ quantwm_status quantwm_attend(const quantwm_config* cfg, const void* calib, cons
  * are k_act / v_act ([B, n_act, H, d] dtype, device, 16-byte aligned), used
  * exactly, with no PSAC term. Positions are concatenated: the mask is that of
  * quantwm_attend over n_cache + n_act keys, and q_start <= n_cache + n_act.
- * n_act <= 2^26. With n_act == 0 this is quantwm_attend. With a workspace of
- * quantwm_attend_active_workspace_bytes(cfg, n_cache, n_act, n_q) bytes or more
- * (256-byte aligned) the call runs in two parts merged by log-sum-exp (the LSE
- * merge of the streaming setting): the packed keys of whole 64-key tiles
- * through the plain attention kernel, the remaining keys (the last packed tile
- * and the active chunk) through the general one. With a smaller workspace it
- * takes quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q) as for
- * quantwm_attend, and NULL runs one launch. All forms give the same result up
- * to fp32 rounding order. */
+ * n_act <= 2^26. With n_act == 0 this is quantwm_attend. One launch runs the
+ * packed keys, then the exact ones, with one softmax state. The workspace
+ * serves the key split as in quantwm_attend:
+ * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q) bytes (256-byte
+ * aligned) or more let a small launch split; NULL or fewer bytes mean no split,
+ * with the same result up to fp32 rounding order. */
 quantwm_status quantwm_attend_active(const quantwm_config* cfg, const void* calib, const void* cache,
                                      int64_t n_cache, const void* k_act, const void* v_act, int64_t n_act,
                                      const void* q, int64_t n_q, int64_t q_start, int32_t frame_tokens,
                                      void* out, float* lse_out, void* workspace, size_t workspace_bytes,
                                      void* stream);
 
-/* Workspace bytes for quantwm_attend_active: the larger of the two-part form's
- * (two or more fp32 partial planes; none without an active chunk or with fewer
- * than 64 packed keys) and the split workspace of
- * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q). */
+/* A workspace size that covers quantwm_attend_active: the larger of fp32 partial
+ * planes for the packed keys and the active chunk apart (none without an active
+ * chunk or with fewer than 64 packed keys) and the split workspace of
+ * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q). The call itself
+ * uses the latter only. */
 size_t quantwm_attend_active_workspace_bytes(const quantwm_config* cfg, int64_t n_cache, int64_t n_act,
                                              int64_t n_q);
 
@@ -312,16 +309,12 @@ quantwm_status quantwm_attend_epochs(const quantwm_config* cfg, const void* cali
                                      int64_t n_q, int64_t q_start, int32_t frame_tokens, void* out,
                                      float* lse_out, void* workspace, size_t workspace_bytes, void* stream);
 
-/* Workspace bytes for the per-epoch form of quantwm_attend_epochs (n_epochs >=
- * 2; 0 otherwise): each
- * epoch's packed keys run through the plain attention kernel with that epoch's
- * calibration block as partial results of their own; with an active chunk, the
- * last whole packed tile on runs through the general kernel; everything merges
- * by log-sum-exp. epoch_start is the host array of the call. Given at least
- * this much (256-byte aligned) the call takes that form; otherwise the
- * one-launch form, with the split workspace of
- * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q). Both give the same
- * result up to fp32 rounding order. */
+/* A workspace size that covers quantwm_attend_epochs (n_epochs >= 2; 0
+ * otherwise): the larger of an fp32 partial plane (or its key splits) per
+ * epoch, one more for an active chunk, and the split workspace of
+ * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q). epoch_start is the
+ * host array of the call. The call runs every epoch in one launch and uses the
+ * split workspace only, as quantwm_attend_active does. */
 size_t quantwm_attend_epochs_workspace_bytes(const quantwm_config* cfg, int32_t n_epochs,
                                              const int64_t* epoch_start, int64_t n_cache, int64_t n_act,
                                              int64_t n_q);

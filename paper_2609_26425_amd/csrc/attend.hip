@@ -66,10 +66,15 @@ __device__ inline auto vget(const V& v, int j) {
 
 // Packed fields of one key tile held by one producer thread between their load
 // and their dequantisation, as loaded (codes, centroid ids, zero-point bytes,
-// binary16 scales), plus the active-chunk flags. Nothing is derived from a
-// loaded value until the tile is dequantised, so the loads stay in flight.
-// Marker: the coefficient-load form is chosen at run time.
-struct AnyAlign {};
+// binary16 scales). Nothing is derived from a loaded value until the tile is
+// dequantised, so the loads stay in flight.
+// How a tile's coefficient rows are read: whole words (r a multiple of a
+// thread's ranks), single bytes, through the sparse-row directory, or chosen at
+// run time.
+struct WholeRows {};
+struct ByteRows {};
+struct SparseRows {};
+struct AnyRows {};
 
 template <int NSUB>
 struct TileRegs {
@@ -78,7 +83,22 @@ struct TileRegs {
   uint32_t k_zb[NSUB], v_zb[2];
   _Float16 k_s[NSUB], v_s[2], c_s;  // loaded bits, reinterpreted (no arithmetic)
   uint32_t k_cb[NSUB], v_cb[2];     // 8-bit group-scale codes (App. D.1 SI8 form only)
-  bool k_on_act, v_on_act[2];
+};
+
+// Rows of the exact active chunk held by one producer thread between their load
+// and their copy into a tile buffer: one key's channels, two keys' channels.
+template <int KW, int VW>
+struct ActRegs {
+  uint32_t k[KW], v[2][VW];
+};
+
+// A run of keys [lo, hi) with one calibration block: the packed keys of an epoch,
+// or the exact active chunk. Its tiles start at key `base` (the 64-slot tile of
+// lo for packed keys, lo itself for the active chunk).
+struct Segment {
+  int64_t lo, hi, base, tiles;
+  int epoch;
+  bool act;
 };
 
 // Row of the 32x32 accumulator held by accumulator slot i of a lane in half hf.
@@ -216,21 +236,6 @@ __device__ inline void dequant_codes(uint32_t cw, S s, uint32_t zz, const float 
   }
 }
 
-// N values of type T held as raw 32-bit words -> floats (exact).
-template <typename T, int N>
-__device__ inline void raw_to_float(const uint32_t* w, float (&x)[N]) {
-  if constexpr (sizeof(T) == 2) {
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) {
-      x[2 * i] = __uint_as_float(w[i] << 16);
-      x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i) x[i] = __uint_as_float(w[i]);
-  }
-}
-
 // Builds a bf16x8 MFMA operand from 8 floats with paired conversions.
 template <typename V>
 __device__ inline V pack_operand(const float* x) {
@@ -242,9 +247,17 @@ __device__ inline V pack_operand(const float* x) {
   }
 }
 
-// GEN: the launch has an exact active chunk after the packed keys and/or packed
-// keys in several calibration epochs (a separate instance, so plain launches
-// carry none of its code).
+// GEN: the launch has an exact active chunk after the packed keys, packed keys in
+// several calibration epochs and/or sparse PSAC rows (a separate instance, so
+// plain launches carry none of its code). Its workgroups run the segments of
+// their key range one after the other, each through the same tile loops as a
+// plain launch; the softmax state stays in registers. Between two segments the
+// producers stage the next tables while the consumers finish the last tile, so a
+// segment costs a pipeline fill (about three tiles) and nothing else. 40 heads x
+// 4,680 Queries, d = 128, 32,760 keys in 7 epochs: 3.41 ms, against 4.10 ms with a
+// plain launch per epoch and a merge of their partial planes. 28,080 packed keys
+// with 8-bit scales + 4,680 exact ones: 3.39 ms, against 5.00 ms in two merged
+// parts. (A plain launch over as many packed keys takes 3.24 ms.)
 template <typename T, int D, int RP, bool LOGITS, bool TAB, bool GEN, bool SI8>
 __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   typedef Mfma<T> MF;
@@ -283,19 +296,6 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   const int64_t bh = int64_t(b) * a.heads + h;
   // calibration slab of this head in epoch e
   auto epoch_slab = [&](int e) { return a.calib + int64_t(e) * a.calib_stride + bh * a.slab; };
-  // epoch of a (wave-uniform) key, and the first key past epoch e
-  // epoch of a key at or after the start of epoch e (epochs only advance with
-  // the key, so the search starts from the last one found)
-  auto epoch_from = [&](int e, int64_t key) {
-    if constexpr (GEN)
-      while (e + 1 < a.n_epochs && key >= a.epoch_start[e + 1]) ++e;
-    return e;
-  };
-  auto epoch_at = [&](int64_t key) { return epoch_from(0, key); };
-  auto epoch_end = [&](int e) -> int64_t {
-    return GEN && e + 1 < a.n_epochs ? a.epoch_start[e + 1] : (int64_t(1) << 62);
-  };
-  auto epoch_begin = [&](int e) -> int64_t { return GEN ? a.epoch_start[e] : 0; };
   auto tab_of = [&](int e, int64_t off) { return reinterpret_cast<const T*>(epoch_slab(e) + off); };
   const CacheLayout& L = a.L;
   const uint8_t* cache = a.cache;
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   const bool producer = wave >= NC;
 
   // ---- key range of this workgroup: Query block bx / n_split, and the
-  // split-th of n_split equal runs of its key tiles
+  // split-th of n_split equal runs of its key tiles (counted over the segments)
   // keys [0, npk) are packed; keys [npk, nc) are the exact active chunk
   const int64_t F = a.frame_tokens, qs = a.q_start, npk = a.n_cache, nc = a.n_cache + a.n_act;
   const int split = int(bx) % a.n_split;
@@ -317,23 +317,53 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   const int64_t qoff = LOGITS ? a.q_row0 : 0;
   int64_t kfull = qs + ((qa + qoff) / F + 1) * F;  // keys below are visible to every Query of the workgroup
   if (kfull > nc) kfull = nc;
-  const int64_t ntile_all = (kend + KT - 1) / KT;
-  // this launch covers tiles [tile_lo, ntile_all) (tile_lo is 0 unless the
-  // caller splits the key range over launches)
-  const int64_t tlo = a.tile_lo < ntile_all ? a.tile_lo : ntile_all;
-  const int64_t per_split = (ntile_all - tlo + a.n_split - 1) / a.n_split;
-  const int64_t t0 = tlo + split * per_split < ntile_all ? tlo + split * per_split : ntile_all;
-  const int64_t ntile = t0 + per_split < ntile_all ? t0 + per_split : ntile_all;  // this split: tiles [t0, ntile)
-  const int64_t nfull = npk / KT;  // tiles [0, nfull) hold packed keys only
+  const int n_seg = GEN ? a.n_epochs + (a.n_act > 0 ? 1 : 0) : 1;
+  auto segment = [&](int i) {
+    Segment g{0, kend, 0, (kend + KT - 1) / KT, 0, false};
+    if constexpr (GEN) {
+      g.act = i == a.n_epochs;
+      g.epoch = g.act ? 0 : i;
+      g.lo = g.act ? npk : a.epoch_start[i];
+      const int64_t hi = g.act ? nc : (i + 1 < a.n_epochs ? a.epoch_start[i + 1] : npk);
+      g.hi = hi < kend ? hi : kend;
+      g.base = g.act ? npk : g.lo / KT * KT;
+      g.tiles = g.hi > g.lo ? (g.hi - g.base + KT - 1) / KT : 0;
+    }
+    return g;
+  };
+  int64_t v_all = 0;
+  for (int i = 0; i < n_seg; ++i) v_all += segment(i).tiles;
+  const int64_t per_split = (v_all + a.n_split - 1) / a.n_split;
+  const int64_t v0 = split * per_split < v_all ? split * per_split : v_all;
+  const int64_t v1 = v0 + per_split < v_all ? v0 + per_split : v_all;  // this split: tiles [v0, v1)
+  // calls f(segment, first tile, end tile, buffer parity of tile 0, first of the
+  // workgroup) for every segment with tiles of this split; tile t sits in
+  // buffer (t + parity) & 1, alternating across segments
+  auto each_segment = [&](auto&& f) __attribute__((always_inline)) {
+    if constexpr (!GEN) {
+      f(segment(0), v0, v1, 0, true);
+    } else {
+      int64_t vb = 0;
+      int done = 0;
+      for (int i = 0; i < n_seg; ++i) {
+        const Segment g = segment(i);
+        const int64_t ta = v0 > vb ? v0 - vb : 0, te = v1 - vb < g.tiles ? v1 - vb : g.tiles;
+        vb += g.tiles;
+        if (ta >= te) continue;
+        f(g, ta, te, (done - int(ta)) & 1, done == 0);
+        done += int(te - ta);
+      }
+    }
+  };
 
   // ---- stage the centroid tables of one epoch (App. D.1: BF16 centroids) with
   // threads [first, first + count) of the workgroup
-  // Plain BF16 instances stage the binary16 copies of the tables, which hold
+  // BF16 instances stage the binary16 copies of the tables, which hold
   // mu 2^-e (e per table, from the calibration block): Keys and Values then
   // dequantise as mu 2^-e + (s 2^-e)(q - z), i.e. scaled by 2^-e exactly, and
   // the Query fragment (times 2^e_k) and the output (times 2^e_v) undo it, so
   // every product and sum of the attention is that of the BF16 tables.
-  constexpr bool H16 = TAB && !GEN && sizeof(T) == 2;
+  constexpr bool H16 = TAB && sizeof(T) == 2;
   auto stage_tables = [&](int e, int first, int count) {
     constexpr int PER_ROW = D * int(sizeof(T)) / 16;  // 16-byte chunks per centroid row
     const uint4* sk = reinterpret_cast<const uint4*>(tab_of(e, H16 ? a.o_mu_k16 : a.o_mu_k));
@@ -344,19 +374,16 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       *reinterpret_cast<uint4*>(tabV + row * LY::TS + ch * (16 / int(sizeof(T)))) = sv[i];
     }
   };
-  // the staged epoch: that of the tile being dequantised (both roles track it)
-  int se = epoch_at(t0 * KT);
-  // 2^-e of the staged binary16 tables (1 without them)
-  float sck = 1.0f, scv = 1.0f;
-  int ek = 0, ev = 0;
-  if constexpr (H16) {
-    const int32_t* e16 = reinterpret_cast<const int32_t*>(epoch_slab(se) + a.o_e16);
-    ek = e16[0];
-    ev = e16[1];
-    sck = ldexpf(1.0f, -ek);
-    scv = ldexpf(1.0f, -ev);
-  }
-  if constexpr (TAB) stage_tables(se, 0, NT);
+  // exponents of the binary16 tables of epoch e (0 without them)
+  auto table_exps = [&](int e, int& ek, int& ev) {
+    ek = ev = 0;
+    if constexpr (H16) {
+      const int32_t* e16 = reinterpret_cast<const int32_t*>(epoch_slab(e) + a.o_e16);
+      ek = e16[0];
+      ev = e16[1];
+    }
+  };
+  if constexpr (TAB && !GEN) stage_tables(0, 0, NT);
 
   // ======================= producer state (waves NC .. NC+NP-1)
   const int ptid = producer ? tid - NC * 64 : 0;
@@ -380,16 +407,13 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
     p.c_w[0] = p.c_w[1] = 0;
     p.c_s = 0;
     p.k_idb = 0;
-    p.k_on_act = false;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      p.v_cw[e] = 0; p.v_idb[e] = 0; p.v_zb[e] = 0; p.v_s[e] = 0; p.v_cb[e] = 0; p.v_on_act[e] = false;
+      p.v_cw[e] = 0; p.v_idb[e] = 0; p.v_zb[e] = 0; p.v_s[e] = 0; p.v_cb[e] = 0;
     }
   };
   clear_regs(P0);
   clear_regs(P1);
-  // keys of the active chunk are read in dequant itself (only the flags travel
-  // from one tile to the next), so they cost no registers across the loop
   constexpr int KW = CHK * int(sizeof(T)) / 4, VW = CHV * int(sizeof(T)) / 4;
   const T* __restrict__ k_act = reinterpret_cast<const T*>(a.k_act);
   const T* __restrict__ v_act = reinterpret_cast<const T*>(a.v_act);
@@ -399,10 +423,10 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   // vector offset (fixed for all tiles) and the tile's byte offset as the scalar
   // offset, so advancing a tile costs no vector instruction.
   // group-scale bytes per token: binary16 steps, or 8-bit codes (SI8)
-  const uint32_t zpb = L.zpb, sstride = SI8 ? L.ng : 2 * L.ng, ncu = uint32_t(nc);
-  // active-chunk row of key `key` (>= npk) at channel c0: [B, n_act, H, d]
-  auto act_row = [&](const T* base, uint32_t key, int c0) {
-    return base + ((int64_t(b) * a.n_act + (key - npku)) * a.heads + h) * D + c0;
+  const uint32_t zpb = L.zpb, sstride = SI8 ? L.ng : 2 * L.ng;
+  // row i of the active chunk at channel c0: [B, n_act, H, d]
+  auto act_row = [&](const T* base, int64_t i, int c0) {
+    return base + ((int64_t(b) * a.n_act + i) * a.heads + h) * D + c0;
   };
   auto load_words = [&](const T* src, uint32_t* w, int nw) {
     const uint4* p = reinterpret_cast<const uint4*>(src);
@@ -441,13 +465,12 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   for (int u = 0; u < NSUB; ++u) kgrp[u] = (kch0 + 16 * u) / G;
   const int vzsh = 2 * (vg % 4);
   // Placeholder fields (all zero) decode to centroid 0 with scale 0.
-  // align_tag: std::true_type / std::false_type when the caller knows whether
-  // r is a multiple of RCH (one whole-word coefficient load), else AnyAlign
-  auto load_raw = [&](TileRegs<NSUB>& p, auto full_tag, uint32_t k0, auto align_tag) __attribute__((always_inline)) {
+  auto load_raw = [&](TileRegs<NSUB>& p, auto full_tag, uint32_t k0, auto rows_tag) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full_tag)::value;
-    using AT = decltype(align_tag);
-    constexpr int AL = std::is_same_v<AT, std::true_type> ? 1 : std::is_same_v<AT, std::false_type> ? 0 : -1;
-    const bool aligned = AL == 1 || (AL == -1 && raligned);
+    using RT = decltype(rows_tag);
+    constexpr bool ANY = std::is_same_v<RT, AnyRows>;
+    const bool aligned = std::is_same_v<RT, WholeRows> || (ANY && raligned);
+    const bool sparse = std::is_same_v<RT, SparseRows> || (GEN && ANY && L.sparse);
     const int k0i = int(k0);
     // fields are gathered in locals and stored into the set once, at the end
     uint32_t kid = 0, kzb[NSUB], kcw[NSUB], kcb[NSUB], cw2[2] = {0, 0};
@@ -455,8 +478,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
     _Float16 ksb[NSUB], csb = 0, vsb[2] = {0, 0};
 #pragma unroll
     for (int u = 0; u < NSUB; ++u) { kzb[u] = 0; ksb[u] = 0; kcw[u] = 0; kcb[u] = 0; }
-    const bool kact = GEN && !FULL && k0 + kkey >= npku && k0 + kkey < ncu;
-    if (!kact && (FULL || k0 + kkey < npku)) {
+    if (FULL || k0 + kkey < npku) {
       kid = __builtin_amdgcn_raw_buffer_load_b8(r_ki, kkey, k0i, 0);
 #pragma unroll
       for (int u = 0; u < NSUB; ++u) {
@@ -479,7 +501,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       }
     }
     if constexpr (RP > 0) {
-      if (GEN && L.sparse && crole && (FULL || k0 + ckey < npku)) {
+      if (sparse && crole && (FULL || k0 + ckey < npku)) {
         // the key's row through the directory entry of its 64-key tile: present
         // iff its mask bit is set, at pool row base + (set bits below it)
         const uint32_t* e = dir + (k0 / 64) * 4;
@@ -509,12 +531,10 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         }
       }
     }
-    bool vact[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const uint32_t key = k0 + 2 * vkp + e;
-      vact[e] = GEN && !FULL && key >= npku && key < ncu;
-      if (!vact[e] && (FULL || key < npku)) {
+      if (FULL || key < npku) {
         vid[e] = __builtin_amdgcn_raw_buffer_load_b8(r_vi, 2 * vkp + e, k0i, 0);
         vzb[e] = __builtin_amdgcn_raw_buffer_load_b8(r_vz, o_vz + e * int(zpb), k0i * int(zpb), 0);
         if constexpr (SI8) {
@@ -527,7 +547,6 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         else vcw[e] = __builtin_amdgcn_raw_buffer_load_b16(r_vc, o_vc + e * (D / 4), k0i * (D / 4), 0);
       }
     }
-    p.k_on_act = kact;
     p.k_idb = kid;
 #pragma unroll
     for (int u = 0; u < NSUB; ++u) { p.k_zb[u] = kzb[u]; p.k_s[u] = ksb[u]; p.k_cw[u] = kcw[u]; p.k_cb[u] = kcb[u]; }
@@ -536,21 +555,19 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
     p.c_w[1] = cw2[1];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      p.v_on_act[e] = vact[e]; p.v_idb[e] = vid[e]; p.v_zb[e] = vzb[e]; p.v_s[e] = vsb[e]; p.v_cw[e] = vcw[e];
+      p.v_idb[e] = vid[e]; p.v_zb[e] = vzb[e]; p.v_s[e] = vsb[e]; p.v_cw[e] = vcw[e];
       p.v_cb[e] = vcb[e];
     }
   };
 
   // rebuild khat_0 = mu + s (q - z) (Eq. 4), chat = code * cscale and vhat into
-  // tile buffer `buf`. s (q - z) is exact in fp32, so the fma rounds once,
+  // tile buffer `buf`, with the tables of epoch e (sck, scv: 2^-exponent of its
+  // binary16 copies). s (q - z) is exact in fp32, so the fma rounds once,
   // exactly like mu + s (q - z).
-  auto dequant_tile = [&](TileRegs<NSUB>& p, auto full_tag, int64_t t) __attribute__((always_inline)) {
-    // FULL: every key of the tile is packed, so no active-chunk branch
-    constexpr bool FULL = decltype(full_tag)::value;
+  auto dequant_tile = [&](TileRegs<NSUB>& p, int buf, int e, float sck, float scv) __attribute__((always_inline)) {
     const uint32_t (&k_cw)[NSUB] = p.k_cw;
     const uint32_t (&c_w)[2] = p.c_w;
     const uint32_t (&v_cw)[2] = p.v_cw;
-    const bool k_on_act = p.k_on_act, v_on_act[2] = {p.v_on_act[0], p.v_on_act[1]};
     // fields as the decode takes them: clamped ids, (1024 + z) pairs, binary16 scales
     const int k_id = int(p.k_idb) < Kc ? int(p.k_idb) : Kc - 1;
     uint32_t k_z[NSUB], v_z[2];
@@ -571,36 +588,18 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       else v_s[e] = p.v_s[e];
     }
     const float c_s = (float)p.c_s;
-    const int buf = int(t & 1);
-    const uint32_t k0 = uint32_t(t * KT);
     T* kt = smem + tile0 + buf * LY::tile_elems;
     T* ct = kt + KT * LY::KS;
     T* vt = ct + KT * LY::CS;
-    // centroids: the staged epoch se (LDS tables when they fit); a tile may end in
-    // the next epoch, whose keys read that epoch's tables from global memory
-    const int64_t b1 = epoch_end(se);
-    const int se1 = se + 1 < a.n_epochs ? se + 1 : se;
-    const T* gK0 = tab_of(se, a.o_mu_k);
-    const T* gK1 = tab_of(se1, a.o_mu_k);
-    const T* gV0 = tab_of(se, a.o_mu_v);
-    const T* gV1 = tab_of(se1, a.o_mu_v);
-    const bool k_e1 = GEN && !FULL && int64_t(k0) + kkey >= b1;
-    bool v_e1[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) v_e1[e] = GEN && !FULL && int64_t(k0) + 2 * vkp + e >= b1;
+    const T* gK = tab_of(e, a.o_mu_k);  // without tables in LDS
+    const T* gV = tab_of(e, a.o_mu_v);
 #pragma unroll
     for (int u = 0; u < NSUB; ++u) {
       float mu[16], x[16];
-      if (TAB && !k_e1) load_tab<H16, T, 16>(tabK + k_id * LY::TS + kch0 + 16 * u, mu);
-      else load_vals<T, 16>((k_e1 ? gK1 : gK0) + k_id * D + kch0 + 16 * u, mu);
-      if (GEN && !FULL && k_on_act) {
-        uint32_t w[16 * sizeof(T) / 4];
-        load_words(act_row(k_act, k0 + kkey, kch0 + 16 * u), w, 16 * int(sizeof(T)) / 4);
-        raw_to_float<T, 16>(w, x);
-      } else {
-        const _Float16 cb = (_Float16)p.k_cb[u];
-        dequant_codes<16, SI8>(k_cw[u], k_s[u], k_z[u], mu, x, f16x2{cb, cb});
-      }
+      if constexpr (TAB) load_tab<H16, T, 16>(tabK + k_id * LY::TS + kch0 + 16 * u, mu);
+      else load_vals<T, 16>(gK + k_id * D + kch0 + 16 * u, mu);
+      const _Float16 cb = (_Float16)p.k_cb[u];
+      dequant_codes<16, SI8>(k_cw[u], k_s[u], k_z[u], mu, x, f16x2{cb, cb});
       store_vals<T, 16>(kt + kkey * LY::KS + kch0 + 16 * u, x);
     }
     if constexpr (RP > 0) {
@@ -616,28 +615,15 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       float mu0[CHV], mu1[CHV];
       const _Float16 vc0 = (_Float16)p.v_cb[0], vc1 = (_Float16)p.v_cb[1];
       const f16x2 vcm0 = {vc0, vc0}, vcm1 = {vc1, vc1};
-      if (TAB && !v_e1[0]) load_tab<H16, T, CHV>(tabV + v_id[0] * LY::TS + vch0, mu0);
-      else load_vals<T, CHV>((v_e1[0] ? gV1 : gV0) + v_id[0] * D + vch0, mu0);
-      if (TAB && !v_e1[1]) load_tab<H16, T, CHV>(tabV + v_id[1] * LY::TS + vch0, mu1);
-      else load_vals<T, CHV>((v_e1[1] ? gV1 : gV0) + v_id[1] * D + vch0, mu1);
-      if (GEN && !FULL && (v_on_act[0] || v_on_act[1])) {
-        uint32_t w[VW];
-        if (v_on_act[0]) {
-          load_words(act_row(v_act, k0 + 2 * vkp, vch0), w, VW);
-          raw_to_float<T, CHV>(w, x0);
-        } else {
-          dequant_codes<CHV, SI8>(v_cw[0], v_s[0], v_z[0], mu0, x0, vcm0);
-        }
-        if (v_on_act[1]) {
-          load_words(act_row(v_act, k0 + 2 * vkp + 1, vch0), w, VW);
-          raw_to_float<T, CHV>(w, x1);
-        } else {
-          dequant_codes<CHV, SI8>(v_cw[1], v_s[1], v_z[1], mu1, x1, vcm1);
-        }
+      if constexpr (TAB) {
+        load_tab<H16, T, CHV>(tabV + v_id[0] * LY::TS + vch0, mu0);
+        load_tab<H16, T, CHV>(tabV + v_id[1] * LY::TS + vch0, mu1);
       } else {
-        dequant_codes<CHV, SI8>(v_cw[0], v_s[0], v_z[0], mu0, x0, vcm0);
-        dequant_codes<CHV, SI8>(v_cw[1], v_s[1], v_z[1], mu1, x1, vcm1);
+        load_vals<T, CHV>(gV + v_id[0] * D + vch0, mu0);
+        load_vals<T, CHV>(gV + v_id[1] * D + vch0, mu1);
       }
+      dequant_codes<CHV, SI8>(v_cw[0], v_s[0], v_z[0], mu0, x0, vcm0);
+      dequant_codes<CHV, SI8>(v_cw[1], v_s[1], v_z[1], mu1, x1, vcm1);
 #pragma unroll
       for (int c = 0; c < CHV; ++c) store_pair<T>(vt + (vch0 + c) * LY::VS + 2 * vkp, x0[c], x1[c]);
     }
@@ -646,9 +632,51 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   using Full = std::integral_constant<bool, true>;
   using Tail = std::integral_constant<bool, false>;
 
-  auto prefetch = [&](TileRegs<NSUB>& p, int64_t t) __attribute__((always_inline)) {
-    if (t < nfull) load_raw(p, Full{}, uint32_t(t * KT), AnyAlign{});
-    else load_raw(p, Tail{}, uint32_t(t * KT), AnyAlign{});
+  // rows of the active chunk: keys 64 t .. 64 t + 63 of it; past its end the last
+  // row again (the mask hides those keys). The row is clamped, not guarded: with
+  // a guard the compiler folded the per-lane condition into the tile loop, and
+  // the lanes of a wave reached its barrier apart.
+  auto load_act = [&](ActRegs<KW, VW>& p, int64_t t) __attribute__((always_inline)) {
+    const int64_t r0 = t * KT, last = a.n_act - 1;
+    load_words(act_row(k_act, r0 + kkey < last ? r0 + kkey : last, kch0), p.k, KW);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int64_t i = r0 + 2 * vkp + e;
+      load_words(act_row(v_act, i < last ? i : last, vch0), p.v[e], VW);
+    }
+  };
+  auto store_act = [&](const ActRegs<KW, VW>& p, int buf) __attribute__((always_inline)) {
+    T* kt = smem + tile0 + buf * LY::tile_elems;
+    T* ct = kt + KT * LY::KS;
+    T* vt = ct + KT * LY::CS;
+    T* krow = kt + kkey * LY::KS + kch0;
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+      for (int i = 0; i < KW; i += 4)
+        reinterpret_cast<uint4*>(krow)[i / 4] = make_uint4(p.k[i], p.k[i + 1], p.k[i + 2], p.k[i + 3]);
+#pragma unroll
+      for (int i = 0; i < VW; ++i) {
+        // channels vch0 + 2 i, + 1 of the two keys, as key pairs
+        *reinterpret_cast<uint32_t*>(vt + (vch0 + 2 * i) * LY::VS + 2 * vkp) =
+            __builtin_amdgcn_perm(p.v[1][i], p.v[0][i], 0x05040100u);
+        *reinterpret_cast<uint32_t*>(vt + (vch0 + 2 * i + 1) * LY::VS + 2 * vkp) =
+            __builtin_amdgcn_perm(p.v[1][i], p.v[0][i], 0x07060302u);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < KW; ++i) krow[i] = __uint_as_float(p.k[i]);
+#pragma unroll
+      for (int i = 0; i < VW; ++i)
+        store_pair<T>(vt + (vch0 + i) * LY::VS + 2 * vkp, __uint_as_float(p.v[0][i]), __uint_as_float(p.v[1][i]));
+    }
+    if constexpr (RP > 0) {  // no PSAC term
+      if (ptid < KT * RPT) {
+        float x[RCH];
+#pragma unroll
+        for (int k = 0; k < RCH; ++k) x[k] = 0.0f;
+        store_vals8<T, RCH>(ct + ckey * LY::CS + cr0, x);
+      }
+    }
   };
 
   // ======================= consumer state (waves 0 .. NC-1)
@@ -659,21 +687,19 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   // (wave-uniform): it keeps the barriers of every tile and computes nothing
   const bool idle = !producer && qa + int64_t(wave) * 32 >= a.n_q;
   V qreg[D / KSTEP];
-  V ureg[RP > 0 ? RP / KSTEP : 1];   // q U_r of epoch ue
-  int ue = se;
+  V ureg[RP > 0 ? RP / KSTEP : 1];   // q U_r of the segment's epoch
   // u = q U_r of epoch e on matrix cores (A operand: rows = ranks of U_r^T);
   // every lane takes part, so callers stay wave-uniform
   auto compute_u = [&](int e, V (&dst)[RP > 0 ? RP / KSTEP : 1]) {
-    const T* gU = tab_of(e, a.o_u_t);
+    const T* urow = tab_of(e, a.o_u_t) + int64_t(l32 < r ? l32 : 0) * D + hf * KPL;
     f32x16 uacc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) uacc[i] = 0.0f;
 #pragma unroll
     for (int st = 0; st < D / KSTEP; ++st) {
-      V av;
-#pragma unroll
-      for (int j = 0; j < KPL; ++j)
-        vset(av, j, l32 < r ? gU[int64_t(l32) * D + st * KSTEP + hf * KPL + j] : T(0.0f));
+      // one whole-fragment load (2-byte loads cost a small launch about 3 us)
+      V av = *reinterpret_cast<const V*>(urow + st * KSTEP);
+      if (l32 >= r) av = V{};
       uacc = MF::run(av, qreg[st], uacc);
     }
     // slot i holds rank acc_row(i, hf): round to the MFMA type (the operand of Eq. 17)
@@ -685,22 +711,44 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   float m_run = -__builtin_inff(), l_run = 0.0f;
   f32x16 oacc[D / 32];
   int lim = int(nc);
-  if (!producer) {
-    // Query fragment (B operand: k = channel, column = Query)
-    const T* qrow = reinterpret_cast<const T*>(a.q) + ((int64_t(b) * a.n_q + (qvalid ? qi : 0)) * a.heads + h) * D;
+  int ev = 0;  // O is held times 2^-ev (the binary16 Value table's scale)
+  // Query fragment (B operand: k = channel, column = Query) and q U_r for epoch e;
+  // act: the active chunk, whose keys are unscaled and carry no PSAC term
+  auto begin_queries = [&](int e, bool act, bool first) __attribute__((always_inline)) {
+    const T* qrow = reinterpret_cast<const T*>(a.q) + ((int64_t(b) * a.n_q + (qvalid ? qi : 0)) * a.heads + h) * D + hf * KPL;
 #pragma unroll
     for (int st = 0; st < D / KSTEP; ++st) {
-#pragma unroll
-      for (int j = 0; j < KPL; ++j) vset(qreg[st], j, qvalid ? qrow[st * KSTEP + hf * KPL + j] : T(0.0f));
+      qreg[st] = *reinterpret_cast<const V*>(qrow + st * KSTEP);
+      if (!qvalid) qreg[st] = V{};
     }
-    if constexpr (RP > 0) compute_u(se, ureg);
+    int ek, en;
+    table_exps(e, ek, en);
+    if (GEN && act) ek = en = 0;
+    if constexpr (RP > 0) {
+      if (GEN && act) {
+#pragma unroll
+        for (int st = 0; st < RP / KSTEP; ++st) ureg[st] = V{};
+      } else {
+        compute_u(e, ureg);
+      }
+    }
     if constexpr (H16) {
       // q 2^e_k (exact in BF16) against the Keys scaled by 2^-e_k
 #pragma unroll
       for (int st = 0; st < D / KSTEP; ++st)
 #pragma unroll
         for (int j = 0; j < KPL; ++j) vset(qreg[st], j, T(ldexpf(float(vget(qreg[st], j)), ek)));
+      if (GEN && !first && en != ev) {
+#pragma unroll
+        for (int cb = 0; cb < D / 32; ++cb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[cb][i] = ldexpf(oacc[cb][i], ev - en);
+      }
     }
+    ev = en;
+  };
+  if (!producer) {
+    if constexpr (!GEN) begin_queries(0, false, true);
 #pragma unroll
     for (int cb = 0; cb < D / 32; ++cb)
 #pragma unroll
@@ -712,94 +760,100 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   }
   const float mscale = 1.4426950408889634f / sqrtf((float)D);  // logits are exponentiated as 2^(S log2(e)/sqrt(d))
 
-  // Producers and consumers run separate loops with one barrier per tile each,
-  // so neither keeps the other's registers live.
-  // Every thread staged part of the centroid tables: they must be complete
-  // before the first dequantisation. The producers' first packed loads are
-  // already in flight across this barrier.
-  if (producer && t0 < ntile) {
-    prefetch(P0, t0);
-    if (t0 + 1 < ntile) prefetch(P1, t0 + 1);
-  }
-  if constexpr (TAB) __syncthreads();
-
+  // Producers and consumers run separate loops with one barrier per tile each
+  // (and one per segment once its tables are staged), so neither keeps the
+  // other's registers live.
   if (producer) {
     // Producers issue first: their vector work fills the matrix-core phases of
     // the consumers, and a late tile would stall all eight consumers.
-    __builtin_amdgcn_s_setprio(2);
-    if (t0 < ntile) {
-      dequant_tile(P0, Tail{}, t0);  // the general form is right for any tile
-      if (t0 + 2 < ntile) prefetch(P0, t0 + 2);
-    }
-    // One step per key tile `it`, after its barrier (buffer it&1 is complete and
-    // every consumer is done with buffer (it+1)&1): dequantise tile it + 1 from
-    // its register set, then refill that set with tile it + 3. Every call names
-    // its set statically (a set chosen at run time would be kept in memory).
-    auto refill = [&](TileRegs<NSUB>& p, int64_t it, auto full_tag) __attribute__((always_inline)) {
-      dequant_tile(p, full_tag, it + 1);
-      if (it + 3 < ntile) prefetch(p, it + 3);
-    };
-    // The steady loops take two tiles per trip with the sets in fixed places, so
-    // the wait before each dequantisation covers only the older set's loads.
-    if constexpr (GEN) {
-      auto gstep = [&](int64_t it, TileRegs<NSUB>& p) __attribute__((always_inline)) {
-        __syncthreads();
-        if constexpr (TAB) {
-          // the next tile opens another epoch: restage its tables (every producer
-          // is done with the old ones after the barrier above), then sync
-          if (it + 1 < ntile) {
-            const int en = epoch_from(se, (it + 1) * KT);
-            if (en != se) {
-              se = en;
-              stage_tables(se, NC * 64, PT);
-              __syncthreads();
-            }
+    if constexpr (GEN) __builtin_amdgcn_s_setprio(2);
+    each_segment([&](const Segment& g, int64_t ta, int64_t te, int par, bool first) __attribute__((always_inline)) {
+      if (GEN && g.act) {
+        // exact keys: copied a tile ahead, in registers for one tile
+        ActRegs<KW, VW> A;
+        load_act(A, ta);
+        store_act(A, int(ta + par) & 1);
+        if (ta + 1 < te) load_act(A, ta + 1);
+        for (int64_t it = ta; it < te; ++it) {
+          __syncthreads();
+          if (it + 1 < te) {
+            store_act(A, int(it + 1 + par) & 1);
+            if (it + 2 < te) load_act(A, it + 2);
           }
-        } else {
-          if (it + 1 < ntile) se = epoch_from(se, (it + 1) * KT);
         }
-        if (it + 1 < ntile) {
-          // a tile of packed keys inside one epoch takes the plain form
-          const int64_t kn = (it + 1) * KT;
-          if (kn + KT <= npk && kn + KT <= epoch_end(se)) refill(p, it, Full{});
-          else refill(p, it, Tail{});
+        return;
+      }
+      const int64_t nfull = (npk - g.base) / KT;  // tiles [0, nfull) of the segment hold packed keys only
+      auto prefetch = [&](TileRegs<NSUB>& p, int64_t t) __attribute__((always_inline)) {
+        if (t < nfull) load_raw(p, Full{}, uint32_t(g.base + t * KT), AnyRows{});
+        else load_raw(p, Tail{}, uint32_t(g.base + t * KT), AnyRows{});
+      };
+      int ek, en;
+      table_exps(g.epoch, ek, en);
+      // 2^-e of the staged binary16 tables (1 without them)
+      const float sck = H16 ? ldexpf(1.0f, -ek) : 1.0f, scv = H16 ? ldexpf(1.0f, -en) : 1.0f;
+      auto dequant = [&](TileRegs<NSUB>& p, int64_t t) __attribute__((always_inline)) {
+        dequant_tile(p, int(t + par) & 1, g.epoch, sck, scv);
+      };
+      // The first packed loads are in flight while the tables are staged. Every
+      // thread of the workgroup stages the first ones; later ones are the
+      // producers' (all of them are past their last dequantisation with the old
+      // tables: the last tile's barrier lies between).
+      if (ta < te) {
+        prefetch(P0, ta);
+        if (ta + 1 < te) prefetch(P1, ta + 1);
+      }
+      if constexpr (TAB) {
+        if constexpr (GEN) {
+          if (first) stage_tables(g.epoch, 0, NT);
+          else stage_tables(g.epoch, NC * 64, PT);
+        }
+        __syncthreads();
+      }
+      if constexpr (!GEN) __builtin_amdgcn_s_setprio(2);
+      if (ta < te) {
+        dequant(P0, ta);
+        if (ta + 2 < te) prefetch(P0, ta + 2);
+      }
+      // One step per key tile `it`, after its barrier (its buffer is complete and
+      // every consumer is done with the other one): dequantise tile it + 1 from
+      // its register set, then refill that set with tile it + 3. Every call names
+      // its set statically (a set chosen at run time would be kept in memory).
+      auto refill = [&](TileRegs<NSUB>& p, int64_t it) __attribute__((always_inline)) {
+        dequant(p, it + 1);
+        if (it + 3 < te) prefetch(p, it + 3);
+      };
+      // Steady state, two tiles per trip with the sets in fixed places (so the wait
+      // before each dequantisation covers only the older set's loads): the
+      // dequantised tile and the prefetched one (it + 3) are both all packed, so
+      // every load is issued unconditionally and the loads of one set stay in
+      // flight across the other set's dequantisation. The loop is compiled once
+      // per coefficient-load form.
+      const int64_t nsteady = (nfull < te ? nfull : te) - 3;  // it < nsteady: it + 3 < min(nfull, te)
+      int64_t it = ta;
+      auto steady = [&](auto rows_tag) __attribute__((always_inline)) {
+        for (; it + 1 < nsteady; it += 2) {
+          __syncthreads();
+          dequant(P1, it + 1);
+          load_raw(P1, Full{}, uint32_t(g.base + (it + 3) * KT), rows_tag);
+          __syncthreads();
+          dequant(P0, it + 2);
+          load_raw(P0, Full{}, uint32_t(g.base + (it + 4) * KT), rows_tag);
         }
       };
-      int64_t it = t0;
-      for (; it + 1 < ntile; it += 2) {
-        gstep(it, P1);
-        gstep(it + 1, P0);
-      }
-      if (it < ntile) gstep(it, P1);
-      return;
-    }
-    // Steady state: the dequantised tile and the prefetched one (it + 3) are both
-    // all packed, so every load is issued unconditionally and the loads of one
-    // set stay in flight across the other set's dequantisation. The loop is
-    // compiled once per coefficient-load form.
-    const int64_t nsteady = (nfull < ntile ? nfull : ntile) - 3;  // it < nsteady: it + 3 < min(nfull, ntile)
-    int64_t it = t0;
-    auto steady = [&](auto align_tag) __attribute__((always_inline)) {
-      for (; it + 1 < nsteady; it += 2) {
+      if (GEN && RP > 0 && L.sparse) steady(SparseRows{});
+      else if (raligned) steady(WholeRows{});
+      else steady(ByteRows{});
+      // the last steps (it - ta is even here) in the general form
+      for (; it < te; it += 2) {
         __syncthreads();
-        dequant_tile(P1, Full{}, it + 1);
-        load_raw(P1, Full{}, uint32_t((it + 3) * KT), align_tag);
-        __syncthreads();
-        dequant_tile(P0, Full{}, it + 2);
-        load_raw(P0, Full{}, uint32_t((it + 4) * KT), align_tag);
+        if (it + 1 < te) refill(P1, it);
+        if (it + 1 < te) {
+          __syncthreads();
+          if (it + 2 < te) refill(P0, it + 1);
+        }
       }
-    };
-    if (raligned) steady(std::true_type{});
-    else steady(std::false_type{});
-    // the last steps (it - t0 is even here) in the general form
-    for (; it < ntile; it += 2) {
-      __syncthreads();
-      if (it + 1 < ntile) refill(P1, it, Tail{});
-      if (it + 1 < ntile) {
-        __syncthreads();
-        if (it + 2 < ntile) refill(P0, it + 1, Tail{});
-      }
-    }
+    });
     return;
   }
 
@@ -811,36 +865,15 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
 
   // Tiles below kfull need no mask: they run as a separate instance of the tile
   // code without the mask branches, so nothing splits its instruction stream.
-  auto tile = [&](int64_t it, auto mask_tag) {
+  // it: tile of segment g, in buffer `buf`
+  auto tile = [&](const Segment& g, int64_t it, int buf, auto mask_tag) {
     constexpr bool MASKED = decltype(mask_tag)::value;
-    const int64_t k0 = it * KT;
+    const int64_t k0 = g.base + it * KT;
     __syncthreads();
-    if constexpr (GEN && TAB) {
-      // mirror of the producers' restage of the centroid tables (one more barrier)
-      if (it + 1 < ntile) {
-        const int en = epoch_from(se, (it + 1) * KT);
-        if (en != se) {
-          se = en;
-          __syncthreads();
-        }
-      }
-    }
     if (idle) return;
-    const T* kt = smem + tile0 + int(it & 1) * LY::tile_elems;
+    const T* kt = smem + tile0 + buf * LY::tile_elems;
     const T* ct = kt + KT * LY::KS;
     const T* vt = ct + KT * LY::CS;
-    // PSAC terms use q U_r of the key's epoch (ureg holds that of epoch ue): the
-    // tile's first epoch here, and where a half crosses into the next epoch at
-    // b1, u is recomputed for it in the middle of that half's product
-    int64_t b1 = int64_t(1) << 62;
-    if constexpr (GEN && RP > 0) {
-      const int e0 = epoch_from(ue, k0);
-      if (e0 != ue) {
-        compute_u(e0, ureg);
-        ue = e0;
-      }
-      b1 = epoch_end(e0) < npk ? epoch_end(e0) : (int64_t(1) << 62);
-    }
 
     // logits S^T of the 32 keys k0 + 32 kb + row (rows x Queries) on matrix cores
     auto k_part = [&](f32x16 acc, int kb) __attribute__((always_inline)) {
@@ -865,31 +898,6 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         for (int st = 0; st < RP / KSTEP; ++st)
 #pragma unroll
           for (int j = 0; j < KPL; ++j) vset(av[st], j, crow[acc_row(st * KPL + j, hf)]);
-        const int64_t h0 = k0 + kb * 32;
-        if (GEN && b1 >= h0 && b1 < h0 + 32) {
-          // the half crosses into the next epoch: this lane's A row is key
-          // h0 + l32, whose chat goes with its own epoch's u. u of the next
-          // epoch is computed first, while no accumulator is live, and the PSAC
-          // term goes in before q . khat_0
-          V un[RP > 0 ? RP / KSTEP : 1];
-          compute_u(ue + 1, un);
-          const bool first = h0 + l32 < b1;
-#pragma unroll
-          for (int st = 0; st < RP / KSTEP; ++st) {
-            V a0, a1;
-#pragma unroll
-            for (int j = 0; j < KPL; ++j) {
-              vset(a0, j, first ? vget(av[st], j) : T(0.0f));
-              vset(a1, j, first ? T(0.0f) : vget(av[st], j));
-            }
-            acc = MF::run(a0, ureg[st], acc);
-            acc = MF::run(a1, un[st], acc);
-          }
-#pragma unroll
-          for (int st = 0; st < RP / KSTEP; ++st) ureg[st] = un[st];
-          ue = ue + 1;
-          return k_part(acc, kb);
-        }
         acc = k_part(acc, kb);
 #pragma unroll
         for (int st = 0; st < RP / KSTEP; ++st) acc = MF::run(av[st], ureg[st], acc);
@@ -915,15 +923,15 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         }
       }
     } else {
-      // masked keys (only in tiles past kfull, and a first tile that starts
-      // below key_lo) -> -inf
+      // masked keys (only in tiles past kfull, and the first and last tile of a
+      // segment, which may hold keys of its neighbours) -> -inf
       auto mask_half = [&](f32x16& sv, int kb) {
         if constexpr (MASKED) {
-          const int klo = int(a.key_lo);
+          const int klo = int(g.lo), khi = GEN && int(g.hi) < lim ? int(g.hi) : lim;
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int key = int(k0) + kb * 32 + acc_row(i, hf);
-            if (key >= lim || key < klo) sv[i] = -__builtin_inff();
+            if (key >= khi || (GEN && key < klo)) sv[i] = -__builtin_inff();
           }
         }
       };
@@ -983,52 +991,49 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         }
       };
 
-      if constexpr (!GEN) {
-        // the tile's two halves of 32 keys: the second half's logits products
-        // are issued before the first half's exponentials, which need none of
-        // them, so the matrix cores run while the vector unit computes
-        // probabilities. The running max of the second half is raised only
-        // after the first half's P V is in O (a rescale must cover it).
-        f32x16 s0 = logits_half(0);
-        mask_half(s0, 0);
-        raise_max(s0);
-        f32x16 s1 = logits_half(1);
-        probs(s0);
-        pv_half(s0, 0);
-        mask_half(s1, 1);
-        raise_max(s1);
-        probs(s1);
-        pv_half(s1, 1);
-      } else {
-        // streaming forms: one half at a time (the epoch-crossing path of the
-        // logits leaves no room for a second live half)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-          f32x16 sv = logits_half(kb);
-          mask_half(sv, kb);
-          raise_max(sv);
-          probs(sv);
-          pv_half(sv, kb);
-        }
-      }
+      // the tile's two halves of 32 keys: the second half's logits products
+      // are issued before the first half's exponentials, which need none of
+      // them, so the matrix cores run while the vector unit computes
+      // probabilities. The running max of the second half is raised only
+      // after the first half's P V is in O (a rescale must cover it).
+      f32x16 s0 = logits_half(0);
+      mask_half(s0, 0);
+      raise_max(s0);
+      f32x16 s1 = logits_half(1);
+      probs(s0);
+      pv_half(s0, 0);
+      mask_half(s1, 1);
+      raise_max(s1);
+      probs(s1);
+      pv_half(s1, 1);
     }
   };
-  const int64_t nclean = kfull / KT < ntile ? kfull / KT : ntile;
-  int64_t it = t0;
-  if (it < ntile && a.key_lo > it * KT) {  // the first tile holds keys below key_lo
-    tile(it, std::integral_constant<bool, true>{});
-    ++it;
-  }
-  for (; it < nclean; ++it) tile(it, std::integral_constant<bool, false>{});
-  for (; it < ntile; ++it) tile(it, std::integral_constant<bool, true>{});
+  each_segment([&](const Segment& g, int64_t ta, int64_t te, int par, bool first) __attribute__((always_inline)) {
+    if constexpr (GEN) {
+      if (TAB && !g.act && first) stage_tables(g.epoch, 0, NT);
+      begin_queries(g.epoch, g.act, first);
+      if (TAB && !g.act) __syncthreads();
+    } else if constexpr (TAB) {
+      __syncthreads();
+    }
+    const int64_t top = kfull < g.hi ? kfull : g.hi;
+    const int64_t nclean = (top - g.base) / KT < te ? (top - g.base) / KT : te;
+    int64_t it = ta;
+    if (GEN && it == 0 && g.lo > g.base) {  // the first tile holds keys of the segment before
+      tile(g, it, int(it + par) & 1, std::integral_constant<bool, true>{});
+      ++it;
+    }
+    for (; it < nclean; ++it) tile(g, it, int(it + par) & 1, std::integral_constant<bool, false>{});
+    for (; it < te; ++it) tile(g, it, int(it + par) & 1, std::integral_constant<bool, true>{});
+  });
 
   if constexpr (!LOGITS) {
     const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (a.n_split > 1 || a.partial) {
+    if (a.n_split > 1) {
       // partial result of this split: unnormalised O, the running max (raw logit
       // units) and the sum; attend_combine merges the splits
       if (qvalid) {
-        const int64_t row = (int64_t(a.split_base + split) * a.heads * gridDim.z + bh) * a.n_q + qi;
+        const int64_t row = (int64_t(split) * a.heads * gridDim.z + bh) * a.n_q + qi;
         float* po = a.part_o + row * D;
 #pragma unroll
         for (int cb = 0; cb < D / 32; ++cb)

@@ -63,7 +63,7 @@ hipError_t launch_d(const AttendArgs& a, int batch, bool logits, hipStream_t s) 
   if (a.rank == 0) e = launch_attend_rp<T, D, 0>(a, batch, logits, s);
   else if (a.rank <= 16) e = launch_attend_rp<T, D, 16>(a, batch, logits, s);
   else e = launch_attend_rp<T, D, 32>(a, batch, logits, s);
-  if (e != hipSuccess || logits || a.n_split == 1 || a.partial) return e;
+  if (e != hipSuccess || logits || a.n_split == 1) return e;
   hipLaunchKernelGGL((attend_combine<T, D>), dim3((unsigned)((a.n_q + 3) / 4), (unsigned)a.heads, (unsigned)batch),
                      dim3(256), 0, s, a);
   return hipGetLastError();
@@ -108,21 +108,6 @@ hipError_t launch_attend_f32(const AttendArgs& a, int d, int batch, bool logits,
   if (d == 64) return launch_d<float, 64>(a, batch, logits, s);
   if (d == 128) return launch_d<float, 128>(a, batch, logits, s);
   return hipErrorInvalidValue;
-}
-
-// merges the a.n_split partial planes of a.part_o / a.part_ml into a.out and a.lse
-hipError_t launch_attend_combine(const AttendArgs& a, int d, int batch, bool is_bf16, hipStream_t s) {
-  const dim3 grid((unsigned)((a.n_q + 3) / 4), (unsigned)a.heads, (unsigned)batch);
-  if (is_bf16) {
-    if (d == 64) hipLaunchKernelGGL((attend_combine<bf16, 64>), grid, dim3(256), 0, s, a);
-    else if (d == 128) hipLaunchKernelGGL((attend_combine<bf16, 128>), grid, dim3(256), 0, s, a);
-    else return hipErrorInvalidValue;
-  } else {
-    if (d == 64) hipLaunchKernelGGL((attend_combine<float, 64>), grid, dim3(256), 0, s, a);
-    else if (d == 128) hipLaunchKernelGGL((attend_combine<float, 128>), grid, dim3(256), 0, s, a);
-    else return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
 }
 
 hipError_t launch_attend_bf16(const AttendArgs& a, int d, int batch, bool logits, hipStream_t s) {

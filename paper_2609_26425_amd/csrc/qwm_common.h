@@ -143,12 +143,6 @@ struct AttendArgs {
   int64_t epoch_start[64];
   float* part_o;  // [n_split][B*H][n_q][d] unnormalised partial outputs (n_split > 1)
   float* part_ml; // [n_split][B*H][n_q][2] running max (raw logits) and sum per partial
-  // a launch that covers key tiles [tile_lo, ...) only and writes its partial
-  // results at planes split_base + split; the caller merges them (partial = 1)
-  int64_t tile_lo;
-  int split_base;
-  int partial;
-  int64_t key_lo;  // keys below are masked (a launch over one calibration epoch's keys)
   int64_t q_row0;  // logits hook only: chunk row of the first Query (frame count of the mask)
 };
 
@@ -178,7 +172,6 @@ hipError_t launch_moment(const quantwm_config& c, const void* q, int64_t n, doub
 // div unless that is 0; cold: none yet). scratch: [B*H][d][d], may be m.
 hipError_t launch_basis(const quantwm_config& c, const double* m, int64_t div, bool cold, double* scratch,
                         uint8_t* calib, hipStream_t s);
-hipError_t launch_attend_combine(const AttendArgs& a, int d, int batch, bool is_bf16, hipStream_t s);
 hipError_t launch_coef_count(const quantwm_config& c, const void* cache, int64_t start, int n, void* counts,
                              hipStream_t s);
 hipError_t launch_coef_pack(const quantwm_config& c, const void* cache, int64_t start, int n, void* record,

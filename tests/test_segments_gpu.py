@@ -1,0 +1,94 @@
+"""Attention over several segments (calibration epochs, an exact active chunk) in
+one launch, at the sizes where the walk over segments can go wrong: epochs of
+one tile, boundaries inside tiles, active chunks around a tile, no packed key at
+all, key splits that start inside any segment, tables in LDS or not, and epochs
+whose tables differ in magnitude by powers of two (the binary16 copies carry one
+exponent each)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_26425_amd import quantwm as qw
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _bf(x, dtype):
+    t = torch.from_numpy(np.ascontiguousarray(x, np.float32))
+    return (t.bfloat16().float() if dtype == "bf16" else t).numpy()
+
+
+# starts, packed keys, exact keys, storage, head_dim, centroids, rank, group, frame, dtype
+CASES = {
+    "one-tile-epochs": ([0, 64, 128, 192], 256, 0, 0, 128, 16, 8, 32, 30, "bf16"),
+    "odd-epochs": ([0, 65, 190, 319], 400, 1, 0, 128, 37, 12, 32, 30, "bf16"),
+    "act-63": ([0], 130, 63, 1, 128, 16, 16, 32, 30, "bf16"),
+    "act-65": ([0], 64, 65, 0, 64, 16, 4, 16, 30, "bf16"),
+    "act-only": ([0], 0, 200, 0, 128, 16, 8, 32, 50, "bf16"),
+    "act-1": ([0], 63, 1, 1, 128, 16, 8, 64, 1, "bf16"),
+    "split": ([0, 300, 777, 1000], 1500, 170, 0, 128, 20, 8, 32, 50, "bf16"),
+    "split-i8": ([0, 900], 1100, 333, 1, 128, 64, 16, 16, 50, "bf16"),
+    "no-tables": ([0, 100, 500], 1090, 129, 0, 128, 256, 32, 64, 50, "bf16"),
+    "no-tables-i8": ([0, 500], 1090, 20, 1, 128, 250, 24, 32, 50, "bf16"),
+    "rank-0": ([0, 70], 200, 90, 0, 128, 16, 0, 32, 50, "bf16"),
+    "f32": ([0, 100, 500], 1090, 129, 0, 64, 16, 4, 32, 50, "f32"),
+    "f32-128": ([0, 77], 200, 65, 1, 128, 16, 32, 32, 50, "f32"),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_segments(name):
+    starts, n_pk, n_act, st, d, kc, r, g, frame, dtype = CASES[name]
+    H, nq = 2, 290
+    total = n_pk + n_act
+    q_start = max(0, total - nq)
+    rng = np.random.default_rng(total + d + r)
+    ocfg = oracle.cfg_of(1, H, d, kc, g, r, 4, max(n_pk, 64), dtype == "bf16", st)
+    cfg = qw.make_config(1, H, d, kc, g, r, 4, max(n_pk, 64), dtype, st)
+    cache = oracle.new_cache(ocfg)
+    bounds, tables = list(starts) + [n_pk], []
+    vmax = 1.0
+    for e in range(len(starts)):
+        n = bounds[e + 1] - bounds[e]
+        # Keys and Values of this epoch at their own magnitude
+        ks, vs = 2.0 ** (-3 * (e % 2)), 2.0 ** (9 * (e % 3) - 9)
+        k, v = _bf(ks * rng.standard_normal((1, max(n, 1), H, d)), dtype), _bf(vs * rng.standard_normal((1, max(n, 1), H, d)), dtype)
+        mu = [_bf(s * rng.standard_normal((1, H, kc, d)), dtype) for s in (ks, vs)]
+        u = _bf(np.stack([np.linalg.qr(rng.standard_normal((d, d)))[0][:r] for _ in range(H)])[None], dtype)
+        t = (mu[0], mu[1], np.ones((1, H, d), np.float32), u, np.ones((1, H, r), np.float32))
+        if n:
+            oracle.append(ocfg, t, cache, bounds[e], k, v)
+            vmax = max(vmax, 5.0 * vs)
+        tables.append(t)
+    ka, va = (_bf(rng.standard_normal((1, n_act, H, d)), dtype) for _ in range(2)) if n_act else (None, None)
+    q = _bf(rng.standard_normal((1, nq, H, d)), dtype)
+    ref, rlse, _ = oracle.attend(ocfg, tables[0], cache, n_pk, q, q_start, frame, k_act=ka, v_act=va,
+                                 epochs=list(zip(starts, tables)))
+    ref, rlse = ref.reshape(1, H, nq, d).transpose(0, 2, 1, 3), rlse.reshape(1, H, nq)
+    dt = cfg.torch_dtype
+    T = lambda x, t=dt: torch.from_numpy(np.ascontiguousarray(x)).to(DEV, t)  # noqa: E731
+    cb = qw.quantwm_calib_bytes(cfg)
+    calibs = torch.zeros(cb * len(starts), dtype=torch.uint8, device=DEV)
+    for e, t in enumerate(tables):
+        qw.quantwm_calib_pack(cfg, T(t[0]), T(t[1]), T(t[2], torch.float32), T(t[3]) if r else None,
+                              T(t[4], torch.float32) if r else None, calibs[e * cb:(e + 1) * cb])
+    dcache, qd = torch.from_numpy(cache).to(DEV), T(q)
+    kd, vd = (T(ka), T(va)) if n_act else (None, None)
+    split = qw.quantwm_attend_workspace_bytes(cfg, total, nq)
+    # outputs are weighted means of Values up to vmax: BF16 rounds the weights and
+    # the result to 2^-9 each, fp32 sums err by 1e-5 (operand rounding of the
+    # correction adds to the logits: four times the sum of both)
+    tol = vmax * (4 * 2.0 ** -8 if dtype == "bf16" else 1e-4)
+    for nb in {0, split}:
+        ws = torch.empty(nb, dtype=torch.uint8, device=DEV) if nb else None
+        out, lse = torch.full_like(qd, 7.0), torch.empty((1, H, nq), dtype=torch.float32, device=DEV)
+        if len(starts) > 1:
+            qw.quantwm_attend_epochs(cfg, calibs, starts, dcache, n_pk, kd, vd, n_act, qd, nq, q_start, frame, out, lse, ws)
+        else:
+            qw.quantwm_attend_active(cfg, calibs, dcache, n_pk, kd, vd, n_act, qd, nq, q_start, frame, out, lse, ws)
+        torch.cuda.synchronize()
+        err = np.abs(out.float().cpu().numpy() - ref).max()
+        assert err <= tol, (nb, err, tol)
+        assert np.abs(lse.cpu().numpy() - rlse).max() <= 2e-2 if dtype == "bf16" else 1e-4
