@@ -64,7 +64,7 @@ __device__ inline void quant_stream(const T* __restrict__ xrow, const T* __restr
       }
     });
   };
-  float glo[SI8 ? NG : 1];
+  float glo[SI8 ? NG : 1], gabs[SI8 ? NG : 1];
   if constexpr (SI8) {
     float tg[NG], mx = 0.0f;
     static_for<0, NG>([&](auto gi) {
@@ -73,6 +73,7 @@ __device__ inline void quant_stream(const T* __restrict__ xrow, const T* __restr
       float lo, hi;
       range(gi, lo, hi);
       glo[g] = lo;
+      gabs[g] = hi > -lo ? hi : -lo;
       tg[g] = (hi - lo) / 3.0f;
       mx = tg[g] > mx ? tg[g] : mx;
     });
@@ -89,12 +90,14 @@ __device__ inline void quant_stream(const T* __restrict__ xrow, const T* __restr
     // keep each group's loads inside the group: hoisting them all ahead would
     // hold every chunk in registers at once
     __builtin_amdgcn_sched_barrier(0);
-    float lo;
+    float lo, amax;
     if constexpr (SI8) {
       lo = glo[g];
+      amax = gabs[g];
     } else {
       float hi;
       range(gi, lo, hi);
+      amax = hi > -lo ? hi : -lo;
       sg[g] = f16_round((hi - lo) / 3.0f);
     }
     const float s = sg[g];
@@ -108,7 +111,7 @@ __device__ inline void quant_stream(const T* __restrict__ xrow, const T* __restr
       load_row<T, CH>(xrow + c0, xv);
       load_row<T, CH>(mrow + c0, mu);
       float t[CH];
-      round_quotients<CH>(xv, mu, s, inv, t);
+      round_quotients<CH>(xv, mu, s, inv, amax * inv > 4.0f, t);
       uint32_t cw = 0;
 #pragma unroll
       for (int c = 0; c < CH; ++c) {

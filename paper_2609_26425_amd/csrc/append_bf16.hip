@@ -23,9 +23,18 @@
 // the result, the value the -2 v_c products would give (powers of two scale
 // every rounding exactly).
 //
-// Selection. Each lane keeps the M smallest (d', id) of its candidates in a
-// sorted list (ids arrive in increasing order within a lane); the pair merges
-// its two lists, both lanes ending with the same M candidates.
+// Selection. Each lane keeps only the M smallest distances of its candidates (one
+// v_med3_f32 per list position and candidate); the pair merges its two lists to
+// the M-th smallest distance T of the token, and the candidates are the ids with
+// d' <= T, gathered as a bit per centroid from the distances of the last four
+// blocks (still in registers) and, past 128 centroids, of a second run of the
+// earlier blocks' products. Carrying the ids in the lists took 17 instructions per
+// candidate instead of 6. Where more than M ids qualify (equal distances at T) the
+// wave redoes the search with lists of (d', id).
+//
+// Score. The M candidates' ranges are taken in one pass over the token, so their
+// rows load together and a token word is unpacked once for all of them; the
+// chosen one's ranges are those of the residual, which then needs no range pass.
 //
 // Residual and PSAC. Each lane quantises its half-row. Group ranges of a group
 // that spans both halves, the 8-bit scales' shared maximum and the Eq. 12 sum
@@ -39,13 +48,53 @@
 #include "append_common.h"
 #include "xcd_order.h"
 
+#include <atomic>
+
 namespace qwm {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kWaveTokens = 32, kBlockWaves = 4, kBlockTokens = kWaveTokens * kBlockWaves;
+constexpr int kWaveTokens = 32, kMaxWaves = 8, kMaxBlocks = 8;
+
+// A table of [rows][D] BF16 in LDS, in 16-byte pieces: piece p of row j sits in
+// slot p ^ key(j) of the row, so that the matrix-core operand reads (32 rows at
+// one piece) hit every bank once without padding, which the direct loads into
+// LDS do not allow.
+template <int D>
+struct Pieces {
+  static constexpr int PR = D / 8;  // per row
+  static __device__ inline int at(int j, int p) { return j * PR + (p ^ (D == 128 ? j & 15 : (j >> 1) & 7)); }
+  // pieces of a table of n rows, rounded to one load of a wave
+  static __host__ __device__ constexpr int size(int n) { return (n * PR + 63) / 64 * 64; }
+};
+// LDS of a workgroup, in 16-byte pieces: the Key table, then two buffers of a
+// block's three planes, which the Value table takes over after the Key search
+template <int D>
+inline int lds_pieces(int kc) {
+  const int v = Pieces<D>::size(kc), planes = 2 * 3 * Pieces<D>::size(32);
+  return v + (v > planes ? v : planes);
+}
+
+// Loads n rows of a [..][D] table into LDS pieces, row i from src_row(i), by the
+// whole workgroup; complete after a wait for the vector memory counter and a
+// barrier. Rows past n (up to the rounded size) repeat the last one.
+template <int D, typename F>
+__device__ inline void stage_rows(const bf16* src, uint4* dst, int n, int waves, int wave, int lane, F src_row) {
+  using P = Pieces<D>;
+  for (int base = wave * 64; base < P::size(n); base += waves * 64) {
+    const int i = base + lane, j = min(i / P::PR, n - 1), slot = i % P::PR;
+    const uint4* g = reinterpret_cast<const uint4*>(src + int64_t(src_row(j)) * D) + (P::at(j, slot) - j * P::PR);
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(g),
+                                     (__attribute__((address_space(3))) uint32_t*)(dst + base), 16, 0, 0);
+  }
+}
+// every direct load of this wave has landed, then the workgroup's
+__device__ inline void staged_barrier() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
 
 // centroid row (within the 32-row block) of accumulator slot i in lane half hf;
 // the lane's column (token) is lane % 32
@@ -86,6 +135,46 @@ __device__ inline void top_insert(float (&bd)[MM], int (&bi)[MM], float d, int j
   }
   bi[0] = lt[0] ? j : bi[0];
   bd[0] = lt[0] ? d : bd[0];
+}
+
+// Insert d into the sorted list of the MM smallest distances.
+template <int MM>
+__device__ inline void top_value(float (&bd)[MM], float d) {
+#pragma unroll
+  for (int p = MM - 1; p >= 1; --p) bd[p] = __builtin_amdgcn_fmed3f(bd[p - 1], d, bd[p]);
+  bd[0] = fminf(bd[0], d);
+}
+
+// The M-th smallest distance of the two lanes' lists (M <= MM, wave-uniform).
+template <int MM>
+__device__ inline float merged_rank(const float (&bd)[MM], int M, int hf) {
+  // the MM smallest of two sorted lists of MM are the pairwise minima of one with
+  // the other reversed: a bitonic sequence, which log2(MM) steps sort
+  float c[MM];
+#pragma unroll
+  for (int p = 0; p < MM; ++p) c[p] = fminf(bd[p], partner(bd[MM - 1 - p], hf));
+#pragma unroll
+  for (int o = MM / 2; o > 0; o /= 2)
+#pragma unroll
+    for (int p = 0; p < MM; ++p)
+      if (!(p & o)) {
+        const float lo = fminf(c[p], c[p + o]), hi = fmaxf(c[p], c[p + o]);
+        c[p] = lo;
+        c[p + o] = hi;
+      }
+  float t = c[MM - 1];
+#pragma unroll
+  for (int p = MM - 2; p >= 0; --p) t = M == p + 1 ? c[p] : t;
+  return t;
+}
+
+// Bit j of the result: centroid j of a 32-row block has d' <= t, over both lanes of the pair.
+__device__ inline uint32_t candidate_bits(const f32x16& acc, float t, int hf) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) m |= acc[i] <= t ? 1u << acc_row(i, 0) : 0u;
+  m <<= 4 * hf;
+  return m | partner_u32(m, hf);
 }
 
 // Insert (d, j) into a list sorted by (d, id) with any id order.
@@ -137,32 +226,39 @@ __device__ inline void forget(uint4 (&u)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(u[i].x), "+v"(u[i].y), "+v"(u[i].z), "+v"(u[i].w));
 }
 
-// Residual of the lane's BF16 half-row xh against the half-row mrow of centroid
-// z (Eq. 1-2 with q_min = 0, q_max = 3, the range extended to contain 0, the
+// Residual of the lane's BF16 half-row xh against the half-row of centroid z,
+// whose 16-byte piece i is mrow(i) (Eq. 1-2 with q_min = 0, q_max = 3, the range extended to contain 0, the
 // residual quantised with the stored scale). Fills the code words of the half
 // (16 channels per word), the zero-points, scales (SI8: 8-bit codes and the
 // secondary scale) of the lane's groups, and calls each(k, e) with
 // e = x_c - (mu_c + s (q_c - z)) for channel c = c0 + k of every 8-channel
 // chunk of the half (Eq. 4, Eq. 13), then chunk(c0). The centroid row is read
-// from memory 8 channels at a time in each pass (a cached table row); each
+// (from LDS) 8 channels at a time in each pass; each
 // group's range pass precedes its code pass, and with 8-bit scales every range
-// pass comes first (the groups share the secondary scale).
-template <int D, int G, bool SI8, typename F, typename FC>
-__device__ inline void residual_half(uint4 (&xh)[D / 16], const uint4* __restrict__ mrow, int hf,
+// pass comes first (the groups share the secondary scale). KNOWN: the groups'
+// literal ranges [gmin, gmax] are given, and there is no range pass.
+template <int D, int G, bool SI8, bool KNOWN, typename R, typename F, typename FC>
+__device__ inline void residual_half(uint4 (&xh)[D / 16], R mrow, int hf,
+                                     const float (&gmin)[Halves<D, G>::GL], const float (&gmax)[Halves<D, G>::GL],
                                      uint32_t (&cw)[D / 32], int (&zg)[Halves<D, G>::GL],
                                      float (&sg)[Halves<D, G>::GL], int (&cg)[Halves<D, G>::GL], float& sig,
                                      F each, FC chunk) {
   using H = Halves<D, G>;
   constexpr int GL = H::GL, GC = H::GC;
   forget(xh);
-  float glo[GL];
+  float glo[GL], gabs[GL];
   auto range = [&](auto gi, float& lo, float& hi) {
     constexpr int gl = decltype(gi)::value;
+    if constexpr (KNOWN) {
+      lo = fminf(0.0f, gmin[gl]);
+      hi = fmaxf(0.0f, gmax[gl]);
+      return;
+    }
     lo = 0.0f;
     hi = 0.0f;
     static_for<0, GC, 8>([&](auto ci) {
       constexpr int c0 = gl * GC + decltype(ci)::value;
-      const uint4 mu = mrow[c0 / 8];
+      const uint4 mu = mrow(c0 / 8);
       static_for<0, 8>([&](auto ki) {
         constexpr int k = decltype(ki)::value;
         const float r = bf_el<k>(xh[c0 / 8]) - bf_el<k>(mu);
@@ -185,17 +281,18 @@ __device__ inline void residual_half(uint4 (&xh)[D / 16], const uint4* __restric
     const float sd = s != 0.0f ? s : 1.0f;
     const int z = s != 0.0f ? (int)fminf(fmaxf(rintf(0.0f - glo[gl] / sd), 0.0f), 3.0f) : 0;
     const float inv = s != 0.0f ? 1.0f / s : 0.0f;
+    const bool big = gabs[gl] * inv > 4.0f;  // the group's largest |x / s|
     zg[gl] = z;
     static_for<0, GC, 8>([&](auto ci) {
       constexpr int c0 = gl * GC + decltype(ci)::value;
       float xv[8], mu[8], t[8];
-      const uint4 m0 = mrow[c0 / 8];
+      const uint4 m0 = mrow(c0 / 8);
       static_for<0, 8>([&](auto ki) {
         constexpr int k = decltype(ki)::value;
         xv[k] = bf_el<k>(xh[c0 / 8]);
         mu[k] = bf_el<k>(m0);
       });
-      round_quotients<8>(xv, mu, s, inv, t);
+      round_quotients<8>(xv, mu, s, inv, big, t);
       uint32_t w = 0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -215,6 +312,7 @@ __device__ inline void residual_half(uint4 (&xh)[D / 16], const uint4* __restric
       float lo, hi;
       range(gi, lo, hi);
       glo[gl] = lo;
+      gabs[gl] = fmaxf(-lo, hi);
       tg[gl] = (hi - lo) / 3.0f;
       mx = fmaxf(mx, tg[gl]);
     });
@@ -237,6 +335,7 @@ __device__ inline void residual_half(uint4 (&xh)[D / 16], const uint4* __restric
       float lo, hi;
       range(gi, lo, hi);
       glo[gl] = lo;
+      gabs[gl] = fmaxf(-lo, hi);
       sg[gl] = f16_round((hi - lo) / 3.0f);
       codes(gi);
     });
@@ -296,25 +395,40 @@ __device__ inline void store_half(const CacheLayout& L, uint8_t* __restrict__ ca
 }
 
 template <int D, int G, int RP, int MM, bool SI8>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void append_bf16_kernel(const AppendArgs a) {
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(2))) void append_bf16_kernel(const AppendArgs a) {
   using H = Halves<D, G>;
+  using P = Pieces<D>;
   constexpr int DH = H::DH, NS = D / 16, GL = H::GL;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n = lane & 31, hf = lane >> 5;
-  const int64_t ntb = (a.n_new + kBlockTokens - 1) / kBlockTokens;
+  extern __shared__ __attribute__((aligned(16))) uint4 lds[];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
+  const int waves = blockDim.x >> 6;
+  const int64_t wg_tokens = int64_t(waves) * kWaveTokens, ntb = (a.n_new + wg_tokens - 1) / wg_tokens;
   const uint32_t task = qwm_xcd_task(blockIdx.x, gridDim.x);
   const int64_t tb = task % ntb, bh = task / ntb;
   const int64_t b = bh / a.heads, h = bh % a.heads;
   const uint8_t* slab = a.calib + bh * a.slab;
 
-  const int64_t t0 = tb * kBlockTokens + wv * kWaveTokens;
-  if (t0 >= a.n_new) return;  // the whole wave is past the chunk
+  const int64_t t0 = tb * wg_tokens + wv * kWaveTokens;
+  const bool idle = t0 >= a.n_new;  // the whole wave is past the chunk: it stages and keeps the barriers
   const int64_t t = t0 + n;
   const bool active = t < a.n_new;
   const int64_t tt = active ? t : a.n_new - 1;  // idle lanes recompute a real token and store nothing
   const int64_t src = ((b * a.n_new + tt) * a.heads + h) * D + hf * DH;
   const int64_t slot = bh * a.L.slots + a.n_cached + tt;
   const int Kc = a.n_centroids, nb = (Kc + 31) / 32;
-  const int64_t KD = int64_t(Kc) * D;
+  const bf16* planes = reinterpret_cast<const bf16*>(slab + a.o_a_k3);
+  const bf16* muk = reinterpret_cast<const bf16*>(slab + a.o_mu_k);
+  const bf16* muv = reinterpret_cast<const bf16*>(slab + a.o_mu_v);
+  uint4* tabK = lds;
+  uint4* bufA = lds + P::size(Kc);  // two blocks' planes, then the Value table
+  constexpr int kPlane = P::size(32);
+  auto stage_planes = [&](int jb) {
+    for (int pl = 0; pl < 3; ++pl)
+      stage_rows<D>(planes + int64_t(pl) * Kc * D, bufA + ((jb & 1) * 3 + pl) * kPlane, 32, waves, wv, lane,
+                    [&](int j) { return min(jb * 32 + j, Kc - 1); });
+  };
+  stage_planes(0);
+  stage_rows<D>(muk, tabK, Kc, waves, wv, lane, [](int j) { return j; });
 
   // ---- QSAC candidate search (Eq. 9 expanded) on the matrix cores, top-M by (d', id)
   uint4 xk[NS];
@@ -323,99 +437,166 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
 #pragma unroll
     for (int s = 0; s < NS; ++s) xk[s] = p[s];
   }
-  float bd[MM];
+  const int M = a.top_m < Kc ? a.top_m : Kc;
   int bi[MM];
-  // ids start at 0, a valid row: with an infinite or NaN distance (inputs out of
-  // range) nothing enters the list, and the score below still reads real rows
-#pragma unroll
-  for (int p = 0; p < MM; ++p) { bd[p] = __builtin_inff(); bi[p] = 0; }
   {
     const float* __restrict__ bk = reinterpret_cast<const float*>(slab + a.o_b_k);
-    const bf16* __restrict__ planes = reinterpret_cast<const bf16*>(slab + a.o_a_k3);
-    for (int jb = 0; jb < nb; ++jb) {
+    // distances of the 32 centroids from 32 jb on (+inf past the last one), whose
+    // planes are in buffer jb & 1
+    auto search = [&](int jb) __attribute__((always_inline)) {
       const int j0 = jb * 32;
       f32x16 acc;
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[i] = bk[min(j0 + acc_row(i, hf), Kc - 1)];
-      const uint4* arow = reinterpret_cast<const uint4*>(planes + int64_t(min(j0 + n, Kc - 1)) * D + hf * DH);
-      // five steps' fragments in flight: steps s + 1 .. s + 4 load while step s multiplies
-      constexpr int PF = 5;
-      uint4 af[PF][3];
-      static_for<0, (PF - 1 < NS ? PF - 1 : NS)>([&](auto pi) {
-        constexpr int st = decltype(pi)::value;
+      if (j0 + 32 > Kc)
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) af[st][pl] = arow[pl * (KD / 8) + st];
-      });
-      static_for<0, NS>([&](auto si) {
-        constexpr int st = decltype(si)::value;
-        if constexpr (st + PF - 1 < NS) {
+        for (int i = 0; i < 16; ++i) acc[i] = j0 + acc_row(i, hf) < Kc ? acc[i] : __builtin_inff();
+      const uint4* A = bufA + (jb & 1) * 3 * kPlane;
 #pragma unroll
-          for (int pl = 0; pl < 3; ++pl) af[(st + PF - 1) % PF][pl] = arow[pl * (KD / 8) + st + PF - 1];
-        }
+      for (int st = 0; st < NS; ++st)
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(af[st % PF][pl]), as_frag(xk[st]), acc, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      });
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(A[pl * kPlane + P::at(n, hf * NS + st)]), as_frag(xk[st]),
+                                                         acc, 0, 0, 0);
+      return acc;
+    };
+    float bd[MM];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int j = j0 + acc_row(i, hf);
-        top_insert<MM>(bd, bi, j < Kc ? acc[i] : __builtin_inff(), j);
+    for (int p = 0; p < MM; ++p) bd[p] = __builtin_inff();
+    f32x16 kept[kMaxBlocks];
+    static_for<0, kMaxBlocks>([&](auto qi) {
+      constexpr int q = decltype(qi)::value;
+      if (q < nb) {
+        staged_barrier();  // block q is in LDS, and every wave is done with block q - 1
+        if (q + 1 < nb) stage_planes(q + 1);
+        if (!idle) {
+          kept[q] = search(q);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) top_value<MM>(bd, kept[q][i]);
+        }
       }
+    });
+    __syncthreads();  // the planes are used up
+    stage_rows<D>(muv, bufA, Kc, waves, wv, lane, [](int j) { return j; });
+    if (!idle) {
+    const float T = merged_rank<MM>(bd, M, hf);
+    // bit j % 32 of word j / 32: centroid j is a candidate
+    uint32_t cand[kMaxBlocks];
+    int found = 0;
+    static_for<0, kMaxBlocks>([&](auto qi) {
+      constexpr int q = decltype(qi)::value;
+      cand[q] = 0;
+      if (q < nb) cand[q] = candidate_bits(kept[q], T, hf);
+      found += __popc(cand[q]);
+    });
+    // the ids in increasing order: the lowest set bit of the first word that has one
+#pragma unroll
+    for (int m = 0; m < MM; ++m) {
+      uint32_t j = ~0u;
+      static_for<0, kMaxBlocks>([&](auto qi) {
+        constexpr int q = decltype(qi)::value;
+        if (q < nb) {
+          const bool here = j == ~0u && cand[q] != 0;
+          j = here ? uint32_t(32 * q + __ffs(cand[q]) - 1) : j;
+          cand[q] = here ? cand[q] & (cand[q] - 1) : cand[q];
+        }
+      });
+      // a valid row whatever the distances were (infinite or NaN inputs)
+      bi[m] = int(min(j, uint32_t(Kc - 1)));
+    }
+    if (__any(found != M)) {
+      // equal distances at T (or inputs out of range): lists of (d', id), lower ids
+      // first among equals. Ids start at 0, a valid row.
+#pragma unroll
+      for (int p = 0; p < MM; ++p) { bd[p] = __builtin_inff(); bi[p] = 0; }
+      static_for<0, kMaxBlocks>([&](auto qi) {
+        constexpr int q = decltype(qi)::value;
+        if (q < nb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) top_insert<MM>(bd, bi, kept[q][i], q * 32 + acc_row(i, hf));
+      });
+      merge_pair<MM>(bd, bi, hf);
+    }
     }
   }
-  merge_pair<MM>(bd, bi, hf);
 
+  float gmin[GL], gmax[GL];  // literal group ranges of the chosen centroid's residual
+  if (!idle) {
   // ---- QSAC score (Eq. 10, 12) over the M candidates; ties to the lower id
-  const bf16* __restrict__ muk = reinterpret_cast<const bf16*>(slab + a.o_mu_k);
   const float* __restrict__ wg = reinterpret_cast<const float*>(slab + a.o_wg);
-  const int M = a.top_m < Kc ? a.top_m : Kc;
   int z = 0;
   float zs = __builtin_inff();
-  static_for<0, MM>([&](auto mi) {
-    constexpr int m = decltype(mi)::value;
-    if (m >= M) return;
-    // one candidate row in flight at a time: hoisting all M of them spills
-    __builtin_amdgcn_sched_barrier(0);
-    const int j = bi[m];
-    const uint4* mrow = reinterpret_cast<const uint4*>(muk + int64_t(j) * D + hf * DH);
-    float tg[GL];
+#pragma unroll
+  for (int gl = 0; gl < GL; ++gl) gmin[gl] = gmax[gl] = 0.0f;
+  {
+    int row[MM];
+#pragma unroll
+    for (int m = 0; m < MM; ++m) row[m] = bi[m];
+    float mx[MM][GL], mn[MM][GL];
     static_for<0, GL>([&](auto gi) {
       constexpr int gl = decltype(gi)::value;
-      float mx = -__builtin_inff(), mn = __builtin_inff();
+#pragma unroll
+      for (int m = 0; m < MM; ++m) { mx[m][gl] = -__builtin_inff(); mn[m][gl] = __builtin_inff(); }
       static_for<0, H::GC / 8>([&](auto wi) {
-        constexpr int c0 = gl * H::GC + 8 * decltype(wi)::value;
-        const uint4 mu = mrow[c0 / 8];
-        static_for<0, 8>([&](auto ki) {
-          constexpr int k = decltype(ki)::value;
-          const float r = bf_el<k>(xk[c0 / 8]) - bf_el<k>(mu);
-          mx = fmaxf(mx, r);
-          mn = fminf(mn, r);
-        });
+        constexpr int c = gl * (H::GC / 8) + decltype(wi)::value;
+        // at most four chunks' rows in flight (two for eight candidates): the next
+        // ones' addresses wait for the ranges so far (more would spill)
+        if constexpr (c > 0 && c % (MM > 4 ? 2 : 4) == 0)
+#pragma unroll
+          for (int m = 0; m < MM; ++m) {
+            constexpr int done = (c - 1) / (H::GC / 8);
+            asm volatile("" : "+v"(row[m]), "+v"(mx[m][done]), "+v"(mn[m][done]));
+          }
+        float x[8];
+        static_for<0, 8>([&](auto ki) { x[decltype(ki)::value] = bf_el<decltype(ki)::value>(xk[c]); });
+#pragma unroll
+        for (int m = 0; m < MM; ++m) {
+          const uint4 mu = tabK[P::at(row[m], hf * NS + c)];
+          static_for<0, 8>([&](auto ki) {
+            constexpr int k = decltype(ki)::value;
+            const float r = x[k] - bf_el<k>(mu);
+            mx[m][gl] = fmaxf(mx[m][gl], r);
+            mn[m][gl] = fminf(mn[m][gl], r);
+          });
+        }
       });
-      if constexpr (H::SPAN) {
-        mx = fmaxf(mx, partner(mx, hf));
-        mn = fminf(mn, partner(mn, hf));
-      }
-      const float R = mx - mn;
-      tg[gl] = wg[H::group(hf, gl)] * (R * R);
     });
-    float S = 0.0f;
-    if constexpr (H::SPAN) {
-      S = S + tg[0];
-    } else {
-      float pt[GL];
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, MM>([&](auto mi) {
+      constexpr int m = decltype(mi)::value;
+      if (m >= M) return;  // entries past M repeat a row and are not scored
+      float tg[GL], S = 0.0f;
 #pragma unroll
-      for (int gl = 0; gl < GL; ++gl) pt[gl] = partner(tg[gl], hf);
+      for (int gl = 0; gl < GL; ++gl) {
+        if constexpr (H::SPAN) {
+          mx[m][gl] = fmaxf(mx[m][gl], partner(mx[m][gl], hf));
+          mn[m][gl] = fminf(mn[m][gl], partner(mn[m][gl], hf));
+        }
+        const float R = mx[m][gl] - mn[m][gl];
+        tg[gl] = wg[H::group(hf, gl)] * (R * R);
+      }
+      if constexpr (H::SPAN) {
+        S = S + tg[0];
+      } else {
+        float pt[GL];
 #pragma unroll
-      for (int gl = 0; gl < GL; ++gl) S = S + (hf ? pt[gl] : tg[gl]);
+        for (int gl = 0; gl < GL; ++gl) pt[gl] = partner(tg[gl], hf);
 #pragma unroll
-      for (int gl = 0; gl < GL; ++gl) S = S + (hf ? tg[gl] : pt[gl]);
-    }
-    const bool better = (S < zs) | ((S == zs) & (j < z));
-    zs = better ? S : zs;
-    z = better ? j : z;
-  });
+        for (int gl = 0; gl < GL; ++gl) S = S + (hf ? pt[gl] : tg[gl]);
+#pragma unroll
+        for (int gl = 0; gl < GL; ++gl) S = S + (hf ? tg[gl] : pt[gl]);
+      }
+      const int j = bi[m];
+      const bool better = (S < zs) | ((S == zs) & (j < z));
+      zs = better ? S : zs;
+      z = better ? j : z;
+#pragma unroll
+      for (int gl = 0; gl < GL; ++gl) {
+        gmin[gl] = better ? mn[m][gl] : gmin[gl];
+        gmax[gl] = better ? mx[m][gl] : gmax[gl];
+      }
+    });
+  }
 
   // ---- Keys: INT2 residual against mu_z, and PSAC (Eq. 13, 16): C = E U_r with
   // E_c = k_c - khat_0,c, on the matrix cores. Each residual chunk is the lane's
@@ -425,7 +606,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
   // product is exact and the fp32 accumulator holds ranks acc_row(i, hf).
   // INT8 rows with one FP16 scale (App. D.1).
   {
-    const uint4* mrow = reinterpret_cast<const uint4*>(muk + int64_t(z) * D + hf * DH);
+    auto mrow = [&](int i) { return tabK[P::at(z, hf * NS + i)]; };
     const bf16* __restrict__ ut = reinterpret_cast<const bf16*>(slab + a.o_u_t);
     const int r = a.rank;
     const uint4* urow = reinterpret_cast<const uint4*>(ut + int64_t(min(n, r > 0 ? r - 1 : 0)) * D + hf * DH);
@@ -437,8 +618,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     uint32_t cw[D / 32];
     int zg[GL], cg[GL];
     float sg[GL], sig = 0.0f;
-    residual_half<D, G, SI8>(
-        xk, mrow, hf, cw, zg, sg, cg, sig,
+    residual_half<D, G, SI8, true>(
+        xk, mrow, hf, gmin, gmax, cw, zg, sg, cg, sig,
         [&](int k, float e) {
           if constexpr (RP > 0) ech[k] = e;
         },
@@ -473,38 +654,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     store_half<D, G, SI8>(a.L, a.cache, a.L.k_codes, a.L.k_ids, a.L.k_zp, a.L.k_scale, a.L.k_sigma, slot, hf,
                           active, z, cw, zg, sg, cg, sig);
     if constexpr (RP > 0) {
-      // C in rank order on both lanes: rank k sits in slot (k / 8) * 4 + k % 4 of
-      // lane half (k / 4) % 2
-      float pc[RP / 2], C[RP];
-#pragma unroll
-      for (int i = 0; i < RP / 2; ++i) pc[i] = partner(cacc[i], hf);
-#pragma unroll
-      for (int k = 0; k < RP; ++k) {
-        const int i = (k / 8) * 4 + k % 4;
-        C[k] = ((k / 4) % 2 == hf) ? cacc[i] : pc[i];
-      }
+      // rank k sits in slot (k / 8) * 4 + k % 4 of lane half (k / 4) % 2: each lane
+      // quantises its own RP / 2 ranks, four consecutive ones per code word
       float amax = 0.0f;
 #pragma unroll
-      for (int k = 0; k < RP; ++k)
-        if (k < r) amax = fmaxf(amax, fabsf(C[k]));
+      for (int i = 0; i < RP / 2; ++i)
+        if (acc_row(i, hf) < r) amax = fmaxf(amax, fabsf(cacc[i]));
+      amax = fmaxf(amax, partner(amax, hf));
       const float s = f16_round(amax / 127.0f);
       const float sd = s != 0.0f ? s : 1.0f;
-      int qc[RP];
+      int qc[RP / 2];
 #pragma unroll
-      for (int k = 0; k < RP; ++k)
-        qc[k] = k < r && s != 0.0f ? (int)fminf(fmaxf(rintf(C[k] / sd), -127.0f), 127.0f) : 0;
+      for (int i = 0; i < RP / 2; ++i)
+        qc[i] = acc_row(i, hf) < r && s != 0.0f ? (int)fminf(fmaxf(rintf(cacc[i] / sd), -127.0f), 127.0f) : 0;
       // App. D.1 retention: keep the row only if it lowers the lam-weighted
       // error on the principal subspace (ranks in order, fp32)
       bool keep = true;
       if (a.gate) {
         const float* __restrict__ lam = reinterpret_cast<const float*>(slab + a.o_lam);
+        float tb[RP / 2], ta[RP / 2];
+#pragma unroll
+        for (int i = 0; i < RP / 2; ++i) {
+          const float e = cacc[i] - (float)qc[i] * s, l = lam[min(acc_row(i, hf), r - 1)];
+          tb[i] = l * (cacc[i] * cacc[i]);
+          ta[i] = l * (e * e);
+        }
         float before = 0.0f, after = 0.0f;
 #pragma unroll
         for (int k = 0; k < RP; ++k) {
+          const int i = (k / 8) * 4 + k % 4;
+          const float pb = partner(tb[i], hf), pa = partner(ta[i], hf);
           if (k < r) {
-            const float e = C[k] - (float)qc[k] * s;
-            before = before + lam[k] * (C[k] * C[k]);
-            after = after + lam[k] * (e * e);
+            before = before + ((k / 4) % 2 == hf ? tb[i] : pb);
+            after = after + ((k / 4) % 2 == hf ? ta[i] : pa);
           }
         }
         keep = after < before;
@@ -515,38 +697,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
         const int64_t crow = a.L.sparse ? bh * a.L.stage + tt : slot;
         uint8_t* code = a.cache + (a.L.sparse ? a.L.k_st_codes : a.L.k_coef) + crow * r;
         if (r == RP) {
-          // the lane's half of the row: RP / 2 bytes
-          uint32_t wds[RP / 8];
+          // words hf, 2 + hf, ...: ranks 8 q + 4 hf .. + 3
 #pragma unroll
           for (int q = 0; q < RP / 8; ++q) {
             uint32_t v = 0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const int c = hf ? qc[RP / 2 + 4 * q + k] : qc[4 * q + k];
-              v |= uint32_t(uint8_t(int8_t(keep ? c : 0))) << (8 * k);
-            }
-            wds[q] = v;
+            for (int k = 0; k < 4; ++k) v |= uint32_t(uint8_t(int8_t(keep ? qc[4 * q + k] : 0))) << (8 * k);
+            *reinterpret_cast<uint32_t*>(code + 8 * q + 4 * hf) = v;
           }
-          if constexpr (RP == 32) *reinterpret_cast<uint4*>(code + 16 * hf) = make_uint4(wds[0], wds[1], wds[2], wds[3]);
-          else *reinterpret_cast<uint2*>(code + 8 * hf) = make_uint2(wds[0], wds[1]);
-        } else if (hf == 0) {
+        } else {
 #pragma unroll
-          for (int k = 0; k < RP; ++k)
-            if (k < r) code[k] = uint8_t(int8_t(keep ? qc[k] : 0));
+          for (int i = 0; i < RP / 2; ++i)
+            if (acc_row(i, hf) < r) code[acc_row(i, hf)] = uint8_t(int8_t(keep ? qc[i] : 0));
+        }
+        if (a.coef_out) {
+          float* co = a.coef_out + (bh * a.n_new + tt) * r;
+#pragma unroll
+          for (int i = 0; i < RP / 2; ++i)
+            if (acc_row(i, hf) < r) co[acc_row(i, hf)] = cacc[i];
         }
         if (hf == 0) {
           *reinterpret_cast<uint16_t*>(a.cache + (a.L.sparse ? a.L.k_st_scale : a.L.k_cscale) + crow * 2) =
               f16_bits(keep ? s : 0.0f);
-          if (a.coef_out) {
-            float* co = a.coef_out + (bh * a.n_new + tt) * r;
-#pragma unroll
-            for (int k = 0; k < RP; ++k)
-              if (k < r) co[k] = C[k];
-          }
         }
       }
     }
   }
+
+  }
+  staged_barrier();  // the Value table is in LDS
+  if (idle) return;
 
   // ---- Values: nearest centroid (w = 1) on the matrix cores, then the same
   // residual path as Keys, no PSAC. (The barrier keeps the Value loads out of
@@ -558,65 +738,75 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
 #pragma unroll
     for (int s = 0; s < NS; ++s) xv[s] = p[s];
     const float* __restrict__ bv = reinterpret_cast<const float*>(slab + a.o_b_v);
-    const bf16* __restrict__ muv = reinterpret_cast<const bf16*>(slab + a.o_mu_v);
-    float dv = __builtin_inff();
+    // the largest mu.v - b/2 is the smallest distance (times -2, exactly)
+    float dv = -__builtin_inff();
     int zv = 0;
     for (int jb = 0; jb < nb; ++jb) {
       const int j0 = jb * 32;
       f32x16 acc;
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[i] = -0.5f * bv[min(j0 + acc_row(i, hf), Kc - 1)];
-      const uint4* arow = reinterpret_cast<const uint4*>(muv + int64_t(min(j0 + n, Kc - 1)) * D + hf * DH);
-      // the block's fragments all load at once (one per step)
-      uint4 af[NS];
+      if (j0 + 32 > Kc)
 #pragma unroll
-      for (int st = 0; st < NS; ++st) af[st] = arow[st];
+        for (int i = 0; i < 16; ++i) acc[i] = j0 + acc_row(i, hf) < Kc ? acc[i] : -__builtin_inff();
+      const int jr = min(j0 + n, Kc - 1);
 #pragma unroll
       for (int st = 0; st < NS; ++st)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(af[st]), as_frag(xv[st]), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(bufA[P::at(jr, hf * NS + st)]), as_frag(xv[st]), acc, 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const int j = j0 + acc_row(i, hf);
-        const float d = -2.0f * acc[i];
-        const bool better = (j < Kc) & (d < dv);  // ids increase: ties keep the lower one
-        dv = better ? d : dv;
-        zv = better ? j : zv;
+        const bool better = acc[i] > dv;  // ids increase: ties keep the lower one
+        dv = better ? acc[i] : dv;
+        zv = better ? j0 + acc_row(i, hf) : zv;
       }
     }
     {
       const float pd = partner(dv, hf);
       const int pz = partner(zv, hf);
-      const bool take = (pd < dv) | ((pd == dv) & (pz < zv));
-      dv = take ? pd : dv;
+      const bool take = (pd > dv) | ((pd == dv) & (pz < zv));
       zv = take ? pz : zv;
     }
-    const uint4* mrow = reinterpret_cast<const uint4*>(muv + int64_t(zv) * D + hf * DH);
+    auto mrow = [&](int i) { return bufA[P::at(zv, hf * NS + i)]; };
     uint32_t cw[D / 32];
     int zg[GL], cg[GL];
     float sg[GL], sig = 0.0f;
-    residual_half<D, G, SI8>(xv, mrow, hf, cw, zg, sg, cg, sig, [](int, float) {}, [](int) {});
+    residual_half<D, G, SI8, false>(xv, mrow, hf, gmin, gmax, cw, zg, sg, cg, sig, [](int, float) {}, [](int) {});
     store_half<D, G, SI8>(a.L, a.cache, a.L.v_codes, a.L.v_ids, a.L.v_zp, a.L.v_scale, a.L.v_sigma, slot, hf,
                           active, zv, cw, zg, sg, cg, sig);
   }
 }
 
+template <int D, int G, int RP, int MM, bool SI8>
+hipError_t launch_one(const AppendArgs& a, int batch, hipStream_t s) {
+  // the dynamic LDS limit is raised once per device for this instance
+  static std::atomic<uint64_t> raised{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? uint64_t(1) << dev : 0;
+  if (!bit || !(raised.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute((const void*)append_bf16_kernel<D, G, RP, MM, SI8>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 16 * lds_pieces<D>(256));
+    if (e != hipSuccess) return e;
+    raised.fetch_or(bit, std::memory_order_release);
+  }
+  // waves per workgroup: eight share the staged tables, fewer where that would
+  // leave compute units without a workgroup (256 on MI355X)
+  const int64_t bh = int64_t(a.heads) * batch, tw = (a.n_new + kWaveTokens - 1) / kWaveTokens;
+  int waves = kMaxWaves;
+  while (waves > 1 && (tw + waves - 1) / waves * bh < 256) waves /= 2;
+  const dim3 grid((unsigned)((tw + waves - 1) / waves * bh));
+  hipLaunchKernelGGL((append_bf16_kernel<D, G, RP, MM, SI8>), grid, dim3(64 * waves), 16 * lds_pieces<D>(a.n_centroids),
+                     s, a);
+  return hipGetLastError();
+}
+
 template <int D, int G, bool SI8>
 hipError_t launch_dgs(const AppendArgs& a, int batch, hipStream_t s) {
-  const int64_t ntb = (a.n_new + kBlockTokens - 1) / kBlockTokens;
-  const dim3 grid((unsigned)(ntb * a.heads * batch));
-  const int rp = a.rank == 0 ? 0 : (a.rank <= 16 ? 16 : 32);  // the [d][rs] stride of U_r
   const bool wide = a.top_m > 4;
-  if (rp == 32) {
-    if (wide) hipLaunchKernelGGL((append_bf16_kernel<D, G, 32, 8, SI8>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((append_bf16_kernel<D, G, 32, 4, SI8>), grid, dim3(256), 0, s, a);
-  } else if (rp == 16) {
-    if (wide) hipLaunchKernelGGL((append_bf16_kernel<D, G, 16, 8, SI8>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((append_bf16_kernel<D, G, 16, 4, SI8>), grid, dim3(256), 0, s, a);
-  } else {
-    if (wide) hipLaunchKernelGGL((append_bf16_kernel<D, G, 0, 8, SI8>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((append_bf16_kernel<D, G, 0, 4, SI8>), grid, dim3(256), 0, s, a);
-  }
-  return hipGetLastError();
+  if (a.rank > 16) return wide ? launch_one<D, G, 32, 8, SI8>(a, batch, s) : launch_one<D, G, 32, 4, SI8>(a, batch, s);
+  if (a.rank > 0) return wide ? launch_one<D, G, 16, 8, SI8>(a, batch, s) : launch_one<D, G, 16, 4, SI8>(a, batch, s);
+  return wide ? launch_one<D, G, 0, 8, SI8>(a, batch, s) : launch_one<D, G, 0, 4, SI8>(a, batch, s);
 }
 
 }  // namespace

@@ -34,24 +34,23 @@ __device__ inline uint16_t f16_bits(float exact) {
 // N full divisions. t = x * RN(1/s) lies within 3 * 2^-24 * |x/s| of RN(x/s);
 // every residual satisfies |x/s| <= 3.01 here (the range spans 3 steps), so the
 // two differ by less than 2^-20 and round to the same integer unless t is
-// within 2^-19 of a half-integer (or |t| > 4, out of this bound). If any lane
-// of the wave meets such a case the whole chunk takes the exact division.
+// within 2^-19 of a half-integer (or |t| > 4, out of this bound: `big`, from the
+// group's largest residual). If any lane of the wave meets such a case the whole
+// chunk takes the exact division.
 template <int N>
-__device__ inline void round_quotients(const float (&xv)[N], const float (&mu)[N], float s, float inv,
+__device__ inline void round_quotients(const float (&xv)[N], const float (&mu)[N], float s, float inv, bool big,
                                        float (&t)[N]) {
-  // the largest |q - k| and |q| of the chunk decide it: two compares instead of
-  // two per channel, each of which fed a scalar OR chain
-  float dmax = 0.0f, qmax = 0.0f;
+  // the largest |q - k| of the chunk decides it: one compare instead of one per
+  // channel, each of which fed a scalar OR chain
+  float dmax = 0.0f;
 #pragma unroll
   for (int c = 0; c < N; ++c) {
     const float q = (xv[c] - mu[c]) * inv;
     const float k = rintf(q);
     dmax = fmaxf(dmax, fabsf(q - k));
-    qmax = fmaxf(qmax, fabsf(q));
     t[c] = k;
   }
-  const bool near = dmax > 0.5f - 0x1p-19f || qmax > 4.0f;
-  if (__any(near)) {
+  if (__any(big || dmax > 0.5f - 0x1p-19f)) {
     const float sd = s != 0.0f ? s : 1.0f;
 #pragma unroll
     for (int c = 0; c < N; ++c) t[c] = rintf((xv[c] - mu[c]) / sd);
