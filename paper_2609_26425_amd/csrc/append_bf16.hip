@@ -4,8 +4,10 @@
 // residual for Values. The outputs are those of the fp32 kernel; the two
 // centroid searches run on the matrix cores.
 //
-// Mapping: a wave takes 32 consecutive tokens of one (b, h), four waves per
-// workgroup. Lanes i and i + 32 share token i and split its channels: lane half
+// Mapping: a wave takes 32 consecutive tokens of one (b, h); a workgroup of up to
+// eight waves shares the tables, staged in LDS: the Key table for the whole Key
+// part, the search planes of one 32-centroid block at a time (double-buffered),
+// then the Value table, loaded while the Keys are quantised. Lanes i and i + 32 share token i and split its channels: lane half
 // hf owns channels [hf d/2, (hf + 1) d/2).
 //
 // Searches. Both are dense products of a (Kc x d) table with the wave's (d x 32)
@@ -26,9 +28,8 @@
 // Selection. Each lane keeps only the M smallest distances of its candidates (one
 // v_med3_f32 per list position and candidate); the pair merges its two lists to
 // the M-th smallest distance T of the token, and the candidates are the ids with
-// d' <= T, gathered as a bit per centroid from the distances of the last four
-// blocks (still in registers) and, past 128 centroids, of a second run of the
-// earlier blocks' products. Carrying the ids in the lists took 17 instructions per
+// d' <= T, gathered as a bit per centroid from the distances, which stay in
+// registers. Carrying the ids in the lists took 17 instructions per
 // candidate instead of 6. Where more than M ids qualify (equal distances at T) the
 // wave redoes the search with lists of (d', id).
 //
@@ -45,6 +46,13 @@
 // Everything that turns a float into an integer follows the equations'
 // operation order in fp32 with IEEE division and round-to-nearest-even, as in
 // the fp32 kernel.
+//
+// What bounds it: vector issue (about 5,800 instructions per wave at 128
+// centroids, d = 128) and the latency of its chains at two waves per SIMD. With
+// every lane reading centroid rows from global memory the cache's tag lookups
+// did: 64 lines per load instruction. 40 heads x 4,680 tokens, 128 centroids,
+// r = 16: 162 us so, 94 us from LDS; 120 heads x 3,120, 256 centroids, r = 32,
+// 8-bit scales: 514 and 284 us; 12 heads x 880, 64 centroids: 24.8 and 19.8 us.
 #include "append_common.h"
 #include "xcd_order.h"
 
@@ -56,7 +64,14 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kWaveTokens = 32, kMaxWaves = 8, kMaxBlocks = 8;
+constexpr int kWaveTokens = 32;
+
+// Waves per workgroup for up to NB blocks of 32 centroids. Every Key distance stays
+// in registers through the selection (16 per block and lane): four blocks leave
+// three waves per SIMD, and two workgroups of six waves share a CU's LDS at 128
+// centroids and d = 128; eight blocks leave two waves per SIMD and one workgroup.
+template <int NB>
+constexpr int kMaxWaves = NB <= 4 ? 4 : 8;
 
 // A table of [rows][D] BF16 in LDS, in 16-byte pieces: piece p of row j sits in
 // slot p ^ key(j) of the row, so that the matrix-core operand reads (32 rows at
@@ -77,17 +92,21 @@ inline int lds_pieces(int kc) {
   return v + (v > planes ? v : planes);
 }
 
-// Loads n rows of a [..][D] table into LDS pieces, row i from src_row(i), by the
-// whole workgroup; complete after a wait for the vector memory counter and a
-// barrier. Rows past n (up to the rounded size) repeat the last one.
-template <int D, typename F>
-__device__ inline void stage_rows(const bf16* src, uint4* dst, int n, int waves, int wave, int lane, F src_row) {
+// Loads rows first .. first + n - 1 of a [..][D] table (the last of them, `last`,
+// in place of those past it) into LDS pieces, by the whole workgroup; complete
+// after a wait for the vector memory counter and a barrier. The LDS row count is
+// rounded up to whole loads. Addresses are a uniform base and 32-bit offsets.
+template <int D>
+__device__ inline void stage_rows(const bf16* src, uint4* dst, int first, int n, int last, int waves, int wave,
+                                  int lane) {
   using P = Pieces<D>;
-  for (int base = wave * 64; base < P::size(n); base += waves * 64) {
-    const int i = base + lane, j = min(i / P::PR, n - 1), slot = i % P::PR;
-    const uint4* g = reinterpret_cast<const uint4*>(src + int64_t(src_row(j)) * D) + (P::at(j, slot) - j * P::PR);
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(g),
-                                     (__attribute__((address_space(3))) uint32_t*)(dst + base), 16, 0, 0);
+  constexpr int RL = 64 / P::PR;  // rows per load of a wave
+  const char* base = reinterpret_cast<const char*>(src);
+  for (int r0 = wave * RL; r0 < n; r0 += waves * RL) {
+    const int j = r0 + lane / P::PR, p = P::at(j, lane % P::PR) - j * P::PR;
+    const uint32_t off = uint32_t(min(first + j, last)) * uint32_t(2 * D) + uint32_t(p) * 16;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t*)(base + off),
+                                     (__attribute__((address_space(3))) uint32_t*)(dst + r0 * P::PR), 16, 0, 0);
   }
 }
 // every direct load of this wave has landed, then the workgroup's
@@ -283,6 +302,7 @@ __device__ inline void residual_half(uint4 (&xh)[D / 16], R mrow, int hf,
     const float inv = s != 0.0f ? 1.0f / s : 0.0f;
     const bool big = gabs[gl] * inv > 4.0f;  // the group's largest |x / s|
     zg[gl] = z;
+    const float zf = (float)z;
     static_for<0, GC, 8>([&](auto ci) {
       constexpr int c0 = gl * GC + decltype(ci)::value;
       float xv[8], mu[8], t[8];
@@ -293,13 +313,17 @@ __device__ inline void residual_half(uint4 (&xh)[D / 16], R mrow, int hf,
         mu[k] = bf_el<k>(m0);
       });
       round_quotients<8>(xv, mu, s, inv, big, t);
-      uint32_t w = 0;
+      // Eq. 1 codes as floats: a zero step has inv = 0 and z = 0, so its codes are 0.
+      // The code word sums q 4^k (exact); mu + s (q - z) rounds once, as the
+      // product is exact (at most 21 significant bits)
+      float wf = 0.0f;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const int q = s != 0.0f ? (int)fminf(fmaxf(t[k] + (float)z, 0.0f), 3.0f) : 0;  // Eq. 1
-        w |= uint32_t(q) << (2 * k);
-        each(k, xv[k] - (mu[k] + s * (float)(q - z)));
+        const float q = fminf(fmaxf(t[k] + zf, 0.0f), 3.0f);
+        wf = __builtin_fmaf(q, float(1 << (2 * k)), wf);
+        each(k, xv[k] - __builtin_fmaf(s, q - zf, mu[k]));
       }
+      const uint32_t w = uint32_t(wf);
       if constexpr (c0 % 16 == 0) cw[c0 / 16] = w;
       else cw[c0 / 16] |= w << 16;
       chunk(c0);
@@ -394,8 +418,9 @@ __device__ inline void store_half(const CacheLayout& L, uint8_t* __restrict__ ca
   }
 }
 
-template <int D, int G, int RP, int MM, bool SI8>
-__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(2))) void append_bf16_kernel(const AppendArgs a) {
+template <int D, int G, int RP, int MM, int NB, bool SI8>
+__global__ __launch_bounds__(64 * kMaxWaves<NB>) __attribute__((amdgpu_waves_per_eu(2))) void
+append_bf16_kernel(const AppendArgs a) {
   using H = Halves<D, G>;
   using P = Pieces<D>;
   constexpr int DH = H::DH, NS = D / 16, GL = H::GL;
@@ -424,11 +449,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   constexpr int kPlane = P::size(32);
   auto stage_planes = [&](int jb) {
     for (int pl = 0; pl < 3; ++pl)
-      stage_rows<D>(planes + int64_t(pl) * Kc * D, bufA + ((jb & 1) * 3 + pl) * kPlane, 32, waves, wv, lane,
-                    [&](int j) { return min(jb * 32 + j, Kc - 1); });
+      stage_rows<D>(planes + int64_t(pl) * Kc * D, bufA + ((jb & 1) * 3 + pl) * kPlane, jb * 32, 32, Kc - 1, waves, wv, lane);
   };
   stage_planes(0);
-  stage_rows<D>(muk, tabK, Kc, waves, wv, lane, [](int j) { return j; });
+  stage_rows<D>(muk, tabK, 0, Kc, Kc - 1, waves, wv, lane);
 
   // ---- QSAC candidate search (Eq. 9 expanded) on the matrix cores, top-M by (d', id)
   uint4 xk[NS];
@@ -463,8 +487,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     float bd[MM];
 #pragma unroll
     for (int p = 0; p < MM; ++p) bd[p] = __builtin_inff();
-    f32x16 kept[kMaxBlocks];
-    static_for<0, kMaxBlocks>([&](auto qi) {
+    f32x16 kept[NB];
+    static_for<0, NB>([&](auto qi) {
       constexpr int q = decltype(qi)::value;
       if (q < nb) {
         staged_barrier();  // block q is in LDS, and every wave is done with block q - 1
@@ -477,13 +501,13 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       }
     });
     __syncthreads();  // the planes are used up
-    stage_rows<D>(muv, bufA, Kc, waves, wv, lane, [](int j) { return j; });
+    stage_rows<D>(muv, bufA, 0, Kc, Kc - 1, waves, wv, lane);
     if (!idle) {
     const float T = merged_rank<MM>(bd, M, hf);
     // bit j % 32 of word j / 32: centroid j is a candidate
-    uint32_t cand[kMaxBlocks];
+    uint32_t cand[NB];
     int found = 0;
-    static_for<0, kMaxBlocks>([&](auto qi) {
+    static_for<0, NB>([&](auto qi) {
       constexpr int q = decltype(qi)::value;
       cand[q] = 0;
       if (q < nb) cand[q] = candidate_bits(kept[q], T, hf);
@@ -493,7 +517,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
     for (int m = 0; m < MM; ++m) {
       uint32_t j = ~0u;
-      static_for<0, kMaxBlocks>([&](auto qi) {
+      static_for<0, NB>([&](auto qi) {
         constexpr int q = decltype(qi)::value;
         if (q < nb) {
           const bool here = j == ~0u && cand[q] != 0;
@@ -509,7 +533,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       // first among equals. Ids start at 0, a valid row.
 #pragma unroll
       for (int p = 0; p < MM; ++p) { bd[p] = __builtin_inff(); bi[p] = 0; }
-      static_for<0, kMaxBlocks>([&](auto qi) {
+      static_for<0, NB>([&](auto qi) {
         constexpr int q = decltype(qi)::value;
         if (q < nb)
 #pragma unroll
@@ -630,18 +654,19 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
             uint32_t p0[4], p1[4], p2[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              uint32_t w0[2], w1[2], w2[2];
+              // the upper halves of e, e - p0 and e - p0 - p1 (whose lower half is 0)
+              uint32_t e0[2], e1[2], e2[2];
 #pragma unroll
               for (int u = 0; u < 2; ++u) {
                 const float e = ech[2 * q + u];
-                w0[u] = __float_as_uint(e) & 0xffff0000u;
-                const float r1 = e - __uint_as_float(w0[u]);
-                w1[u] = __float_as_uint(r1) & 0xffff0000u;
-                w2[u] = __float_as_uint(r1 - __uint_as_float(w1[u])) & 0xffff0000u;
+                e0[u] = __float_as_uint(e);
+                const float r1 = e - __uint_as_float(e0[u] & 0xffff0000u);
+                e1[u] = __float_as_uint(r1);
+                e2[u] = __float_as_uint(r1 - __uint_as_float(e1[u] & 0xffff0000u));
               }
-              p0[q] = w0[1] | (w0[0] >> 16);
-              p1[q] = w1[1] | (w1[0] >> 16);
-              p2[q] = w2[1] | (w2[0] >> 16);
+              p0[q] = __builtin_amdgcn_perm(e0[1], e0[0], 0x07060302u);
+              p1[q] = __builtin_amdgcn_perm(e1[1], e1[0], 0x07060302u);
+              p2[q] = __builtin_amdgcn_perm(e2[1], e2[0], 0x07060302u);
             }
             cacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(uf), as_frag(make_uint4(p0[0], p0[1], p0[2], p0[3])),
                                                            cacc, 0, 0, 0);
@@ -776,7 +801,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
-template <int D, int G, int RP, int MM, bool SI8>
+template <int D, int G, int RP, int MM, int NB, bool SI8>
 hipError_t launch_one(const AppendArgs& a, int batch, hipStream_t s) {
   // the dynamic LDS limit is raised once per device for this instance
   static std::atomic<uint64_t> raised{0};
@@ -785,28 +810,32 @@ hipError_t launch_one(const AppendArgs& a, int batch, hipStream_t s) {
   if (e != hipSuccess) return e;
   const uint64_t bit = dev < 64 ? uint64_t(1) << dev : 0;
   if (!bit || !(raised.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute((const void*)append_bf16_kernel<D, G, RP, MM, SI8>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 16 * lds_pieces<D>(256));
+    e = hipFuncSetAttribute((const void*)append_bf16_kernel<D, G, RP, MM, NB, SI8>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 16 * lds_pieces<D>(32 * NB));
     if (e != hipSuccess) return e;
     raised.fetch_or(bit, std::memory_order_release);
   }
-  // waves per workgroup: eight share the staged tables, fewer where that would
-  // leave compute units without a workgroup (256 on MI355X)
+  // as many waves share the staged tables as leave no compute unit (256 on
+  // MI355X) without a workgroup
   const int64_t bh = int64_t(a.heads) * batch, tw = (a.n_new + kWaveTokens - 1) / kWaveTokens;
-  int waves = kMaxWaves;
+  int waves = kMaxWaves<NB>;
   while (waves > 1 && (tw + waves - 1) / waves * bh < 256) waves /= 2;
   const dim3 grid((unsigned)((tw + waves - 1) / waves * bh));
-  hipLaunchKernelGGL((append_bf16_kernel<D, G, RP, MM, SI8>), grid, dim3(64 * waves), 16 * lds_pieces<D>(a.n_centroids),
-                     s, a);
+  hipLaunchKernelGGL((append_bf16_kernel<D, G, RP, MM, NB, SI8>), grid, dim3(64 * waves),
+                     16 * lds_pieces<D>(a.n_centroids), s, a);
   return hipGetLastError();
+}
+
+template <int D, int G, int RP, bool SI8>
+hipError_t launch_rank(const AppendArgs& a, int batch, hipStream_t s) {
+  if (a.top_m > 4) return launch_one<D, G, RP, 8, 8, SI8>(a, batch, s);
+  return a.n_centroids > 128 ? launch_one<D, G, RP, 4, 8, SI8>(a, batch, s) : launch_one<D, G, RP, 4, 4, SI8>(a, batch, s);
 }
 
 template <int D, int G, bool SI8>
 hipError_t launch_dgs(const AppendArgs& a, int batch, hipStream_t s) {
-  const bool wide = a.top_m > 4;
-  if (a.rank > 16) return wide ? launch_one<D, G, 32, 8, SI8>(a, batch, s) : launch_one<D, G, 32, 4, SI8>(a, batch, s);
-  if (a.rank > 0) return wide ? launch_one<D, G, 16, 8, SI8>(a, batch, s) : launch_one<D, G, 16, 4, SI8>(a, batch, s);
-  return wide ? launch_one<D, G, 0, 8, SI8>(a, batch, s) : launch_one<D, G, 0, 4, SI8>(a, batch, s);
+  if (a.rank > 16) return launch_rank<D, G, 32, SI8>(a, batch, s);
+  return a.rank > 0 ? launch_rank<D, G, 16, SI8>(a, batch, s) : launch_rank<D, G, 0, SI8>(a, batch, s);
 }
 
 }  // namespace
