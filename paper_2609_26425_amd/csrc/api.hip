@@ -431,7 +431,7 @@ static int device_cus() {
 }
 
 static size_t attend_split_bytes(const quantwm_config* cfg, int64_t n_cache, int64_t n_q, int* splits) {
-  const int ns = qwm::attend_splits(n_q, cfg->heads, cfg->batch, n_cache, device_cus());
+  const int ns = qwm::attend_splits(n_q, cfg->heads, cfg->batch, n_cache, device_cus(), qwm::elem_bytes(*cfg));
   if (splits) *splits = ns;
   if (ns <= 1) return 0;
   const size_t rows = size_t(ns) * cfg->batch * cfg->heads * size_t(n_q);
@@ -462,7 +462,7 @@ size_t quantwm_attend_epochs_workspace_bytes(const quantwm_config* cfg, int32_t 
   for (int e = 0; e < n_epochs; ++e) {
     const int64_t hi0 = e + 1 < n_epochs ? epoch_start[e + 1] : n_cache, hi = hi0 < end ? hi0 : end;
     if (hi > epoch_start[e])
-      planes += qwm::attend_splits(n_q, cfg->heads, cfg->batch, hi - epoch_start[e], device_cus());
+      planes += qwm::attend_splits(n_q, cfg->heads, cfg->batch, hi - epoch_start[e], device_cus(), qwm::elem_bytes(*cfg));
   }
   const size_t per = planes_bytes(cfg, planes, n_q);
   const size_t split = attend_split_bytes(cfg, n_cache + n_act, n_q, nullptr);
@@ -475,7 +475,7 @@ size_t quantwm_attend_active_workspace_bytes(const quantwm_config* cfg, int64_t 
   const int64_t whole = n_cache / qwm::kAttendTileKeys * qwm::kAttendTileKeys;
   const size_t two = whole == 0 || n_act == 0
                          ? 0
-                         : planes_bytes(cfg, qwm::attend_splits(n_q, cfg->heads, cfg->batch, whole, device_cus()) + 1, n_q);
+                         : planes_bytes(cfg, qwm::attend_splits(n_q, cfg->heads, cfg->batch, whole, device_cus(), qwm::elem_bytes(*cfg)) + 1, n_q);
   const size_t split = attend_split_bytes(cfg, n_cache + n_act, n_q, nullptr);
   return two > split ? two : split;
 }

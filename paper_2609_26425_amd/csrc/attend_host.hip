@@ -77,21 +77,30 @@ size_t attend_lds_bytes(int d, int elem, int rank, int n_centroids, bool tables)
   return d == 64 ? attend_lds_bytes_t<float, 64>(rank, n_centroids, tables)
                  : attend_lds_bytes_t<float, 128>(rank, n_centroids, tables);
 }
-int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus) {
+int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus, int elem) {
   // Split the key range only when the launch gives fewer than two workgroups
   // per compute unit (one runs per CU). The split count minimises the rounds of
   // workgroups times each one's work: its share of the key tiles plus a fixed
   // cost of about 32 tiles (table staging, Query fragments, pipeline fill,
-  // partial write), up to 16 splits of at least 8 tiles.
+  // partial write), up to 16 splits of at least 8 tiles; 4 while all the
+  // workgroups still run at once, where a split only uses idle CUs (4 heads, 64
+  // Queries, 704 keys at d = 128: 29 us in one part, 20.5 us in two; 16 heads, 300
+  // Queries, 2,000 keys: 53 us with 3 splits, 35 us with 7, each with the faster
+  // start of the kernel). fp32 tiles take about eight times as long (matrix cores
+  // at 1/16 of the BF16 rate), so the fixed cost is 2 of them and a split may be a
+  // single tile (2 heads, 256 Queries, 1,024 keys at d = 64: 92 us with 2 splits,
+  // 33 us with 16).
+  const int fixed = elem == 4 ? 2 : 32;
   const int64_t wgs = (n_q + BQ - 1) / BQ * heads * batch;
   if (wgs <= 0 || wgs >= 2 * int64_t(cus)) return 1;
   const int64_t tiles = (n_cache + KT - 1) / KT;
   int best = 1;
   int64_t best_cost = -1;
   for (int ns = 1; ns <= 16; ++ns) {
-    if (ns > 1 && tiles / ns < 8) break;
+    const int least = elem == 4 ? 1 : (wgs * ns <= cus ? 4 : 8);
+    if (ns > 1 && tiles / ns < least) break;
     const int64_t rounds = (wgs * ns + cus - 1) / cus;
-    const int64_t cost = rounds * ((tiles + ns - 1) / ns + 32);
+    const int64_t cost = rounds * ((tiles + ns - 1) / ns + fixed);
     if (best_cost < 0 || cost < best_cost) {
       best = ns;
       best_cost = cost;

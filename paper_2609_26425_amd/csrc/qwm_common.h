@@ -114,6 +114,7 @@ struct AppendArgs {
   float* coef_out;
   int gate;        // QWM_STORE_GATE with r > 0
   int64_t o_lam;   // eigenvalues in the slab (read with the gate)
+  int split_sides; // Keys and Values in workgroups of their own (set by the launchers)
 };
 
 constexpr int kMaxEpochs = 64;
@@ -149,6 +150,13 @@ struct AttendArgs {
 // keys per attention tile
 constexpr int kAttendTileKeys = 64;
 
+// Append launches of at most this many waves (one per SIMD on MI355X) quantise Keys
+// and Values in workgroups of their own: the SIMDs are not all busy, and the two
+// chains run side by side (BF16, 12 heads x 880 tokens 19.7 -> 13.7 us, x 2,640
+// tokens 24 -> 15.2 us; fp32, 2 heads x 256 tokens 39 -> 29 us). Past one wave per
+// SIMD the second side would only queue.
+constexpr int64_t kSplitSideWaves = 1024;
+
 // Launchers. Append: one translation unit per (element type, head_dim, group
 // size); fp32 Keys and Values on the vector ALU, BF16 ones with the centroid
 // searches on the matrix cores.
@@ -159,7 +167,7 @@ hipError_t launch_append_bf16(const AppendArgs& a, int batch, hipStream_t s);
 hipError_t launch_attend_f32(const AttendArgs& a, int d, int batch, bool logits, hipStream_t s);
 hipError_t launch_attend_bf16(const AttendArgs& a, int d, int batch, bool logits, hipStream_t s);
 size_t attend_lds_bytes(int d, int elem, int rank, int n_centroids, bool tables_in_lds);
-int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus);
+int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus, int elem);
 bool attend_tables_fit(int d, int elem, int rank, int n_centroids);
 
 hipError_t launch_derive_constants(const quantwm_config& c, uint8_t* calib, hipStream_t s);
