@@ -170,7 +170,10 @@ __device__ inline void topm_insert(float (&bd)[MM], int (&bi)[MM], float dv, int
 template <typename T, int D, int G, int RP, int MM, bool SI8>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void append_kernel(const AppendArgs a) {
   constexpr int NG = D / G;
-  const int t = blockIdx.x * 256 + threadIdx.x;
+  // the second half of a split launch quantises the Values, the first the Keys
+  const unsigned n_tb = a.split_sides ? gridDim.x / 2 : gridDim.x;
+  const bool keys = blockIdx.x < n_tb, values = !a.split_sides || !keys;
+  const int t = (keys ? blockIdx.x : blockIdx.x - n_tb) * 256 + threadIdx.x;
   const int h = blockIdx.y, b = blockIdx.z;
   const bool active = t < a.n_new;
   const int64_t tt = active ? t : a.n_new - 1;  // idle lanes recompute a real token and store nothing
@@ -189,6 +192,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
   const int64_t slot = bh * a.L.slots + a.n_cached + tt;
 
   float x[D];
+  int z = 0;
+  if (keys) {
   load_row<T, D>(reinterpret_cast<const T*>(a.k) + src, x);
 
   // ---- QSAC candidate search (Eq. 9, expanded form), top-M by (d', id)
@@ -217,7 +222,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
 
   // ---- QSAC score (Eq. 10, 12) over the M candidates; ties to the lower id
   const int M = a.top_m < Kc ? a.top_m : Kc;
-  int z = 0;
   float zs = __builtin_inff();
   static_for<0, MM>([&](auto mi) {
     constexpr int m = decltype(mi)::value;
@@ -245,6 +249,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     if (S < zs || (S == zs && j < z)) { zs = S; z = j; }
   });
 
+  }
+
   // ---- Values: nearest centroid (w = 1). Both searches run before the first
   // store, so the compiler may keep their table loads on the scalar path.
   int zv = 0;
@@ -259,7 +265,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
       zv = better ? j + u : zv;
     }
   };
-  {
+  if (values) {
     load_row<T, D>(reinterpret_cast<const T*>(a.v) + src, x);
     for (int j = 0; j < Kc; j += 4) {
       float acc[4];
@@ -280,7 +286,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
   // E_c = k_c - khat_0,c (Eq. 13), C_k += E_c U_ck (Eq. 16). From here on the
   // key is re-read 16 channels at a time (L1 hits), so only the r accumulators
   // stay resident. INT8 rows with one FP16 scale (App. D.1).
-  {
+  if (keys) {
     const T* krow = reinterpret_cast<const T*>(a.k) + src;
     const T* mrow = muk + int64_t(z) * D;
     float C[RP > 0 ? RP : 1];
@@ -364,7 +370,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
   }
 
   // ---- Values: the same residual path as Keys, no PSAC
-  {
+  if (values) {
     int zg[NG], cg[NG];
     float sg[NG], sig = 0.0f;
     quant_stream<T, D, G, SI8>(reinterpret_cast<const T*>(a.v) + src, muv + int64_t(zv) * D,
@@ -380,18 +386,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
 
 template <typename T, int D, int G, bool SI8>
 hipError_t launch_dgs(const AppendArgs& a, int batch, hipStream_t s) {
-  const dim3 grid((unsigned)((a.n_new + 255) / 256), (unsigned)a.heads, (unsigned)batch);
+  AppendArgs args = a;
+  args.split_sides = (a.n_new + 63) / 64 * a.heads * batch <= kSplitSideWaves;
+  const dim3 grid((unsigned)((a.n_new + 255) / 256 * (args.split_sides ? 2 : 1)), (unsigned)a.heads, (unsigned)batch);
   const int rp = a.rank == 0 ? 0 : (a.rank <= 16 ? 16 : 32);  // the [d][rs] stride of U_r
   const bool wide = a.top_m > 4;
   if (rp == 32) {
-    if (wide) hipLaunchKernelGGL((append_kernel<T, D, G, 32, 8, SI8>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((append_kernel<T, D, G, 32, 4, SI8>), grid, dim3(256), 0, s, a);
+    if (wide) hipLaunchKernelGGL((append_kernel<T, D, G, 32, 8, SI8>), grid, dim3(256), 0, s, args);
+    else hipLaunchKernelGGL((append_kernel<T, D, G, 32, 4, SI8>), grid, dim3(256), 0, s, args);
   } else if (rp == 16) {
-    if (wide) hipLaunchKernelGGL((append_kernel<T, D, G, 16, 8, SI8>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((append_kernel<T, D, G, 16, 4, SI8>), grid, dim3(256), 0, s, a);
+    if (wide) hipLaunchKernelGGL((append_kernel<T, D, G, 16, 8, SI8>), grid, dim3(256), 0, s, args);
+    else hipLaunchKernelGGL((append_kernel<T, D, G, 16, 4, SI8>), grid, dim3(256), 0, s, args);
   } else {
-    if (wide) hipLaunchKernelGGL((append_kernel<T, D, G, 0, 8, SI8>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((append_kernel<T, D, G, 0, 4, SI8>), grid, dim3(256), 0, s, a);
+    if (wide) hipLaunchKernelGGL((append_kernel<T, D, G, 0, 8, SI8>), grid, dim3(256), 0, s, args);
+    else hipLaunchKernelGGL((append_kernel<T, D, G, 0, 4, SI8>), grid, dim3(256), 0, s, args);
   }
   return hipGetLastError();
 }

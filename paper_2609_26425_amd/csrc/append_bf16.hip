@@ -428,7 +428,10 @@ append_bf16_kernel(const AppendArgs a) {
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, hf = lane >> 5;
   const int waves = blockDim.x >> 6;
   const int64_t wg_tokens = int64_t(waves) * kWaveTokens, ntb = (a.n_new + wg_tokens - 1) / wg_tokens;
-  const uint32_t task = qwm_xcd_task(blockIdx.x, gridDim.x);
+  // the second half of a split launch quantises the Values, the first the Keys
+  const uint32_t n_task = a.split_sides ? gridDim.x / 2 : gridDim.x;
+  const bool keys = blockIdx.x < n_task, values = !a.split_sides || !keys;
+  const uint32_t task = qwm_xcd_task(keys ? blockIdx.x : blockIdx.x - n_task, n_task);
   const int64_t tb = task % ntb, bh = task / ntb;
   const int64_t b = bh / a.heads, h = bh % a.heads;
   const uint8_t* slab = a.calib + bh * a.slab;
@@ -451,8 +454,16 @@ append_bf16_kernel(const AppendArgs a) {
     for (int pl = 0; pl < 3; ++pl)
       stage_rows<D>(planes + int64_t(pl) * Kc * D, bufA + ((jb & 1) * 3 + pl) * kPlane, jb * 32, 32, Kc - 1, waves, wv, lane);
   };
-  stage_planes(0);
-  stage_rows<D>(muk, tabK, 0, Kc, Kc - 1, waves, wv, lane);
+  auto stage_values = [&]() { stage_rows<D>(muv, bufA, 0, Kc, Kc - 1, waves, wv, lane); };
+  float gmin[GL], gmax[GL];  // literal group ranges of the chosen centroid's residual
+  if (keys) {
+    stage_planes(0);
+    stage_rows<D>(muk, tabK, 0, Kc, Kc - 1, waves, wv, lane);
+  } else {
+    stage_values();
+  }
+
+  if (keys) {
 
   // ---- QSAC candidate search (Eq. 9 expanded) on the matrix cores, top-M by (d', id)
   uint4 xk[NS];
@@ -501,7 +512,7 @@ append_bf16_kernel(const AppendArgs a) {
       }
     });
     __syncthreads();  // the planes are used up
-    stage_rows<D>(muv, bufA, 0, Kc, Kc - 1, waves, wv, lane);
+    if (values) stage_values();
     if (!idle) {
     const float T = merged_rank<MM>(bd, M, hf);
     // bit j % 32 of word j / 32: centroid j is a candidate
@@ -544,7 +555,6 @@ append_bf16_kernel(const AppendArgs a) {
     }
   }
 
-  float gmin[GL], gmax[GL];  // literal group ranges of the chosen centroid's residual
   if (!idle) {
   // ---- QSAC score (Eq. 10, 12) over the M candidates; ties to the lower id
   const float* __restrict__ wg = reinterpret_cast<const float*>(slab + a.o_wg);
@@ -750,6 +760,8 @@ append_bf16_kernel(const AppendArgs a) {
   }
 
   }
+  if (!values) return;
+  }
   staged_barrier();  // the Value table is in LDS
   if (idle) return;
 
@@ -815,14 +827,19 @@ hipError_t launch_one(const AppendArgs& a, int batch, hipStream_t s) {
     if (e != hipSuccess) return e;
     raised.fetch_or(bit, std::memory_order_release);
   }
-  // as many waves share the staged tables as leave no compute unit (256 on
-  // MI355X) without a workgroup
+  AppendArgs args = a;
   const int64_t bh = int64_t(a.heads) * batch, tw = (a.n_new + kWaveTokens - 1) / kWaveTokens;
+  args.split_sides = tw * bh <= kSplitSideWaves;
+  // as many waves share the staged tables as leave no compute unit (256 on
+  // MI355X) without a workgroup; fewer waves would need a second round of
+  // workgroups for the LDS (12 heads x 2,640 tokens: 17.8 us with four, 23.9 us
+  // with two)
+  const int64_t sides = args.split_sides ? 2 : 1;
   int waves = kMaxWaves<NB>;
-  while (waves > 1 && (tw + waves - 1) / waves * bh < 256) waves /= 2;
-  const dim3 grid((unsigned)((tw + waves - 1) / waves * bh));
+  while (waves > 1 && (tw + waves - 1) / waves * bh * sides < 256) waves /= 2;
+  const dim3 grid((unsigned)((tw + waves - 1) / waves * bh * sides));
   hipLaunchKernelGGL((append_bf16_kernel<D, G, RP, MM, NB, SI8>), grid, dim3(64 * waves),
-                     16 * lds_pieces<D>(a.n_centroids), s, a);
+                     16 * lds_pieces<D>(a.n_centroids), s, args);
   return hipGetLastError();
 }
 
