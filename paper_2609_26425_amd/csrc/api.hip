@@ -552,7 +552,9 @@ static quantwm_status attend_common(const quantwm_config* cfg, const void* calib
       ns = split_cap;
       need = planes_bytes(cfg, ns, n_q);
     }
-    if (ns > 1 && workspace_bytes >= need) {
+    // a smaller workspace gets as many parts as it holds
+    while (ns > 1 && workspace_bytes < need) need = planes_bytes(cfg, --ns, n_q);
+    if (ns > 1) {
       const size_t rows = size_t(ns) * cfg->batch * cfg->heads * size_t(n_q);
       a.n_split = ns;
       a.part_o = static_cast<float*>(workspace);

@@ -12,7 +12,7 @@
 //     per eigenvalue narrow its interval 33-fold per round.
 //  3. Eigenvectors of T by two rounds of inverse iteration (LU with partial
 //     pivoting, one lane per eigenvalue) from fixed start vectors, each round
-//     followed by Gram-Schmidt (twice) against the larger eigenvalues' vectors,
+//     followed by modified Gram-Schmidt (twice) in order of the eigenvalues,
 //     so close or equal eigenvalues still give an orthonormal set.
 //  4. Back-transformation by the stored reflections, 16 lanes per vector.
 //
@@ -20,7 +20,7 @@
 // of length D); only the first r of the D eigenpairs are needed, which is why
 // neither QL on all vectors nor Jacobi sweeps (about 1,000 dependent rotation
 // rounds at D = 128) is used: a host Jacobi took 15 ms per head, all heads of a
-// launch together take 0.34 ms here (r = 8; 0.44 ms for r = 16) at D = 128. Every loop has a fixed trip count, so non-finite
+// launch together take 0.33 ms here (r = 8; 0.39 ms for r = 16) at D = 128. Every loop has a fixed trip count, so non-finite
 // input ends too. All sums have a fixed order: equal M give equal bits.
 #include "qwm_common.h"
 
@@ -87,6 +87,14 @@ __device__ inline double recip(double x) {
   return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
 }
 
+// sqrt(x), x > 0, to about one ulp (v_rsq_f64 and two Newton steps)
+__device__ inline double root(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = __builtin_fma(__builtin_fma(-x * y, y, 1.0), 0.5 * y, y);
+  const double r = x * y;
+  return __builtin_fma(__builtin_fma(-r, r, x), 0.5 * y, r);
+}
+
 // double -> bf16 with one rounding (nearest, ties to even), for normal values.
 __device__ inline void store_rn(float* p, double x) { *p = (float)x; }
 __device__ inline void store_rn(bf16* p, double x) {
@@ -102,7 +110,7 @@ template <int D>
 struct BasisLds {
   double row[D], vn[D], v[D], w[D], p[D];  // next row of M, vectors of the reflections, M v
   double al[D], be[D], bt[D];              // T (diagonal, off-diagonal) and 2 / v^T v of each reflection
-  double lam[kMaxRank], dot[kMaxRank];
+  double lam[kMaxRank];
   double red[kLanes / 64];
   double fd[D][kMaxRank], fu[D][kMaxRank], fl[D][kMaxRank];  // LU of T - lam: 1 / pivot, first super-diagonal, multipliers
   double z[kMaxRank][D + 2];                                 // vectors, one row per eigenvalue
@@ -227,10 +235,10 @@ __global__ __launch_bounds__(kLanes) void basis_kernel(const double* m_in, int64
       double off = k + 1 < D ? x1 : 0.0, v1 = 0.0;
       beta = 0.0;
       if (sigma > 0.0) {
-        const double nrm = sqrt(__builtin_fma(x1, x1, sigma));
+        const double nrm = root(__builtin_fma(x1, x1, sigma));
         off = x1 > 0.0 ? -nrm : nrm;
         v1 = x1 - off;
-        beta = 2.0 / __builtin_fma(v1, v1, sigma);
+        beta = 2.0 * recip(__builtin_fma(v1, v1, sigma));
       }
 #pragma unroll
       for (int e = 0; e < NE; ++e) {
@@ -304,9 +312,14 @@ __global__ __launch_bounds__(kLanes) void basis_kernel(const double* m_in, int64
       const double x = __builtin_fma(step, (double)(l32 + 1), lo);
       int below = 0;
       double q = 1.0, b2 = 0.0;
+      // q <- al - x - b2 / q, with 1 / q = y (1 + e + e^2) from a 24-bit y: the
+      // chain is v_rcp_f64 and three fmas
+#pragma unroll 16
       for (int i = 0; i < D; ++i) {
-        q = __builtin_fma(-b2, recip(q), S.al[i] - x);
-        if (fabs(q) < tiny) q = -tiny;
+        const double y = __builtin_amdgcn_rcp(q), f = S.al[i] - x, t = b2 * y;
+        const double e = __builtin_fma(-q, y, 1.0);
+        q = __builtin_fma(-t, __builtin_fma(e, e, e), f - t);
+        q = fabs(q) < tiny ? -tiny : q;
         below += q < 0.0;
         b2 = S.be[i] * S.be[i];
       }
@@ -394,33 +407,50 @@ __global__ __launch_bounds__(kLanes) void basis_kernel(const double* m_in, int64
       for (int i = 0; i < D; ++i) S.z[lane][i] *= sc;
     }
     __syncthreads();
-    // Gram-Schmidt in order of decreasing eigenvalue, each vector twice, then unit length
-    for (int e = 0; e < r; ++e) {
-      for (int pass = 0; pass < 2; ++pass) {
-        for (int i = wave; i < e; i += kLanes / 64) {
-          double s = 0.0;
+    // modified Gram-Schmidt in order of decreasing eigenvalue, the whole set twice:
+    // wave w holds vectors w, w + 8, ... in registers; vector e becomes a unit
+    // vector and goes through LDS to the waves, which take its part out of theirs
+    constexpr int NW = kLanes / 64, NV = kMaxRank / NW;
+    double z[NV][NE];
 #pragma unroll
-          for (int q = 0; q < NE; ++q) s = __builtin_fma(S.z[i][lane + 64 * q], S.z[e][lane + 64 * q], s);
-          s = group_sum<64>(s);
-          if (lane == 0) S.dot[i] = s;
-        }
-        __syncthreads();
-        if (wave == 0) {
-          double x[NE], s = 0.0;
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
-          for (int q = 0; q < NE; ++q) {
-            x[q] = S.z[e][lane + 64 * q];
-            for (int i = 0; i < e; ++i) x[q] = __builtin_fma(-S.dot[i], S.z[i][lane + 64 * q], x[q]);
-            s = __builtin_fma(x[q], x[q], s);
+      for (int q = 0; q < NE; ++q) z[v][q] = v * NW + wave < r ? S.z[v * NW + wave][lane + 64 * q] : 0.0;
+    for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+      for (int ev = 0; ev < NV; ++ev)
+        for (int ew = 0; ew < NW; ++ew) {
+          const int e = ev * NW + ew;
+          if (e >= r) break;
+          if (wave == ew) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < NE; ++q) s = __builtin_fma(z[ev][q], z[ev][q], s);
+            s = group_sum<64>(s);
+            const double inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+#pragma unroll
+            for (int q = 0; q < NE; ++q) {
+              z[ev][q] *= inv;
+              S.z[e][lane + 64 * q] = z[ev][q];
+            }
           }
-          s = group_sum<64>(s);
-          const double inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+          __syncthreads();
+          double u[NE];
 #pragma unroll
-          for (int q = 0; q < NE; ++q) S.z[e][lane + 64 * q] = x[q] * inv;
+          for (int q = 0; q < NE; ++q) u[q] = S.z[e][lane + 64 * q];
+#pragma unroll
+          for (int v = ev; v < NV; ++v) {
+            if (v * NW + wave <= e) continue;
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < NE; ++q) s = __builtin_fma(u[q], z[v][q], s);
+            s = group_sum<64>(s);
+#pragma unroll
+            for (int q = 0; q < NE; ++q) z[v][q] = __builtin_fma(-s, u[q], z[v][q]);
+          }
         }
-        __syncthreads();
-      }
     }
+    __syncthreads();
   }
 
   // ---- 4. back-transformation z := H_0 ... H_{D-3} z: 16 lanes per vector, lane

@@ -202,17 +202,21 @@ __device__ inline void load8(const bf16* p, double (&x)[8]) {
 // adds n to *count; otherwise the sums start at 0 and are divided by n, and the
 // tiles below the diagonal mirror those above (the product commutes).
 //
-// A block takes a 32 x 32 tile of one head's matrix, 2 x 2 elements per thread,
-// and stages 64 tokens at a time in LDS as doubles, the next 64 loading while
-// these multiply. The token order is a serial chain of n fmas per element, so
-// the tile is kept small to spread a head over many CUs, and 2 x 2 halves the
-// LDS reads per fma. 4,680 tokens of 10 heads at d = 128 (ACC): 1,230 us with a
-// thread per element and no staging, 260 us so.
-constexpr int kMomTile = 32, kMomTok = 64;
+// A block takes a 32 x 32 tile of one head's matrix, a wave 16 x 16 of it on the
+// fp64 matrix cores: v_mfma_f64_16x16x4 adds four tokens as a chain of fmas in
+// token order (the tests compare bits with that chain). 64 tokens at a time are
+// staged in LDS as doubles, the next 64 loading while these multiply; rows are
+// padded so that a wave's operand reads are free of bank conflicts. One matrix
+// instruction per four tokens and wave is the chain that bounds it, so the tiles
+// are small to spread a head over many CUs. 4,680 tokens of 10 heads at d = 128
+// (ACC): 1,230 us with a thread per element and no staging, 260 us with 2 x 2
+// elements per thread on the vector unit (bound by LDS reads), 124 us so.
+constexpr int kMomTile = 32, kMomTok = 64, kMomRow = kMomTile + 16;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <typename T, bool ACC>
 __global__ __launch_bounds__(256) void moment_kernel(const T* q, int64_t n, int heads, int d, double* m,
                                                      int64_t* count) {
-  __shared__ __attribute__((aligned(16))) double s_q[2][kMomTok][kMomTile];
+  __shared__ __attribute__((aligned(16))) double s_q[2][kMomTok][kMomRow];
   const int64_t bh = blockIdx.y;
   const int b = int(bh / heads), h = int(bh % heads), tid = threadIdx.x;
   const int nt = d / kMomTile;
@@ -226,24 +230,30 @@ __global__ __launch_bounds__(256) void moment_kernel(const T* q, int64_t n, int 
   }
   const T* base = q + (int64_t(b) * n * heads + h) * d;
   const int64_t stride = int64_t(heads) * d;
-  // staging: thread -> (token, eight channels) of each side
+  // staging: thread -> (token, eight channels) of each side; zeros past the last token
   const int st = tid / 4, sc = (tid % 4) * 8;
   double xi[8], xj[8];
   auto fetch = [&](int64_t t0) {
-    const int64_t t = t0 + st < n ? t0 + st : n - 1;
+    const bool in = t0 + st < n;
+    const int64_t t = in ? t0 + st : n - 1;
     load8(base + t * stride + ti * kMomTile + sc, xi);
     load8(base + t * stride + tj * kMomTile + sc, xj);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      xi[k] = in ? xi[k] : 0.0;
+      xj[k] = in ? xj[k] : 0.0;
+    }
   };
-  const int i2 = (tid / 16) * 2, j2 = (tid % 16) * 2;
+  // wave w: 16 x 16 elements at (16 (w / 2), 16 (w % 2)) of the tile; accumulator
+  // slot i of lane l is row 4 i + l / 16, column l % 16
+  const int lane = tid & 63, w = tid >> 6, l16 = lane & 15, lk = lane >> 4;
+  const int i0 = (w / 2) * 16, j0 = (w % 2) * 16;
   double* mh = m + bh * d * d;
-  const int gi = ti * kMomTile + i2, gj = tj * kMomTile + j2;
-  double a00 = 0.0, a01 = 0.0, a10 = 0.0, a11 = 0.0;
-  if constexpr (ACC) {
-    a00 = mh[gi * d + gj];
-    a01 = mh[gi * d + gj + 1];
-    a10 = mh[(gi + 1) * d + gj];
-    a11 = mh[(gi + 1) * d + gj + 1];
-  }
+  const int gi = ti * kMomTile + i0 + lk, gj = tj * kMomTile + j0 + l16;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  if constexpr (ACC)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = mh[(gi + 4 * i) * d + gj];
   fetch(0);
   for (int64_t t0 = 0; t0 < n; t0 += kMomTok) {
     __syncthreads();  // the previous tokens are used up
@@ -254,37 +264,15 @@ __global__ __launch_bounds__(256) void moment_kernel(const T* q, int64_t n, int 
     }
     __syncthreads();
     if (t0 + kMomTok < n) fetch(t0 + kMomTok);
-    const int nn = n - t0 < kMomTok ? int(n - t0) : kMomTok;
-    auto step = [&](int t) __attribute__((always_inline)) {
-      const double2 x = *reinterpret_cast<const double2*>(&s_q[0][t][i2]);
-      const double2 y = *reinterpret_cast<const double2*>(&s_q[1][t][j2]);
-      a00 = __builtin_fma(x.x, y.x, a00);
-      a01 = __builtin_fma(x.x, y.y, a01);
-      a10 = __builtin_fma(x.y, y.x, a10);
-      a11 = __builtin_fma(x.y, y.y, a11);
-    };
-    if (nn == kMomTok) {
-#pragma unroll 16
-      for (int t = 0; t < kMomTok; ++t) step(t);
-    } else {
-      for (int t = 0; t < nn; ++t) step(t);
-    }
+#pragma unroll
+    for (int t = 0; t < kMomTok; t += 4)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(s_q[0][t + lk][i0 + l16], s_q[1][t + lk][j0 + l16], acc, 0, 0, 0);
   }
-  if constexpr (!ACC) {
-    a00 /= (double)n;
-    a01 /= (double)n;
-    a10 /= (double)n;
-    a11 /= (double)n;
-  }
-  mh[gi * d + gj] = a00;
-  mh[gi * d + gj + 1] = a01;
-  mh[(gi + 1) * d + gj] = a10;
-  mh[(gi + 1) * d + gj + 1] = a11;
-  if (!ACC && ti != tj) {
-    mh[gj * d + gi] = a00;
-    mh[(gj + 1) * d + gi] = a01;
-    mh[gj * d + gi + 1] = a10;
-    mh[(gj + 1) * d + gi + 1] = a11;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double x = ACC ? acc[i] : acc[i] / (double)n;
+    mh[(gi + 4 * i) * d + gj] = x;
+    if (!ACC && ti != tj) mh[gj * d + gi + 4 * i] = x;
   }
   if (ACC && bh == 0 && blockIdx.x == 0 && tid == 0) *count += n;
 }
@@ -329,11 +317,11 @@ __global__ __launch_bounds__(128) void km_init_kernel(const KmArgs a) {
 // Squared Euclidean distance in channel order (fp32, no contraction): the
 // literal form that decides every assignment. Rows are 16-byte aligned.
 template <int D>
-__device__ inline float literal_distance(const bf16* x, const bf16* mu) {
+__device__ inline float literal_distance(const bf16* x, const uint4* mu) {
   float acc = 0.0f;
 #pragma unroll 4
   for (int c = 0; c < D; c += 8) {
-    const uint4 u = *reinterpret_cast<const uint4*>(x + c), m = *reinterpret_cast<const uint4*>(mu + c);
+    const uint4 u = *reinterpret_cast<const uint4*>(x + c), m = mu[c / 8];
     const uint32_t xw[4] = {u.x, u.y, u.z, u.w}, mw[4] = {m.x, m.y, m.z, m.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -380,33 +368,47 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // Lloyd assignment of BF16 tokens: the literal distance decides, but it is only
 // evaluated where it can matter. The matrix cores give d'_j = |mu_j|^2 - 2 x.mu_j
 // for 32 centroids x 32 tokens at a time (a wave's tokens; lanes i and i + 32
-// share token i and hold 16 centroids each per block). With u = 2^-24 and
-// S = |x|^2 + max_j |mu_j|^2:
-//   - the products are exact and the fp32 sums of d terms err by less than
-//     2 (d + 16) u per unit of sum |terms| (twice the d u of one rounding per
-//     term), so d'_j is within E = 4 (d + 16) u S of the real value;
-//   - the literal distance (d terms, three roundings each) is within
-//     E_L = 2 (d + 4) u S of it (|x - mu_j|^2 <= 2 S).
-// A centroid whose d' exceeds the smallest by more than 2 (E + E_L) therefore
-// has the larger literal distance. Where a second centroid is inside that bound
-// (about 1% of the tokens), a second pass over the same products evaluates the
-// literal distance of every centroid inside it.
-// Latency bounds it; 4,680 tokens of 10 heads, 128 centroids, Keys and Values:
-// 660 us for the two literal launches, 40 us so.
+// share token i and hold 16 centroids each per block). With u = 2^-24,
+// S = |x|^2 + max_j |mu_j|^2 and D_j the real squared distance:
+//   - the products are exact and the fp32 sum of the d terms of x.mu_j errs by at
+//     most (d + 16) u |x| |mu_j|, doubled here for a sum in any grouping; with the
+//     sum of |mu_j|^2 and the last rounding d'_j is within E = 2 (d + 32) u S;
+//   - the literal distance (three roundings per term, d terms) is within
+//     (d + 4) u D_j of D_j.
+// With D_1 the distance of the smallest d', a centroid whose d' exceeds that by
+// more than 2 E + 2 (d + 4) u (D_1 + E), and a little, has the larger literal
+// distance. Where a second centroid is inside that bound, a second pass over the
+// same products evaluates the literal distance of every centroid inside it.
+// The table is staged in LDS for the workgroup's 128 tokens (rows padded by 16
+// bytes: operand reads free of bank conflicts); read from global memory, a row
+// per lane, the loads' cache-line lookups bounded it. Latency does now; 4,680
+// tokens of 10 heads, 128 centroids, Keys and Values: 660 us for the two literal
+// launches, 39 us with the rows from global memory, 22 us so.
+template <int D>
+struct KmAssignLds {
+  uint4 mu[256 * (D / 8 + 1)];
+  float b[256];
+};
 template <int D>
 __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
-  constexpr int NS = D / 16;
+  constexpr int NS = D / 16, PR = D / 8 + 1;  // 16-byte pieces of a padded row
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  uint4* s_mu = reinterpret_cast<uint4*>(smem_raw);
+  float* s_b = reinterpret_cast<float*>(smem_raw + size_t(a.Kc) * PR * 16);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n32 = lane & 31, hf = lane >> 5;
   const int64_t bh = blockIdx.y, n = a.n;
   const int side = blockIdx.z, Kc = a.Kc;
   const int b = int(bh / a.heads), h = int(bh % a.heads);
   const int64_t t0 = int64_t(blockIdx.x) * 128 + wv * 32;
-  if (t0 >= n) return;  // the whole wave is past the chunk
   const int64_t t = t0 + n32 < n ? t0 + n32 : n - 1;
   const uint8_t* slab = a.calib + bh * a.slab;
   const bf16* mu = reinterpret_cast<const bf16*>(slab + a.o_mu[side]);
   const float* bj = reinterpret_cast<const float*>(slab + a.o_b[side]);
   const bf16* row = reinterpret_cast<const bf16*>(a.x[side]) + ((int64_t(b) * n + t) * a.heads + h) * D;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < Kc * (D / 8); i += 256)
+    s_mu[i / (D / 8) * PR + i % (D / 8)] = reinterpret_cast<const uint4*>(mu)[i];
+  for (int i = threadIdx.x; i < Kc; i += 256) s_b[i] = bj[i];
   // k index 8 hf + i of step s is channel 16 s + 8 hf + i on both operands
   bf16x8 xf[NS];
   float xx = 0.0f;
@@ -417,20 +419,19 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
     for (int k = 0; k < 8; ++k) xx = __builtin_fmaf((float)xf[s][k], (float)xf[s][k], xx);
   }
   xx += __shfl_xor(xx, 32);
+  __syncthreads();
+  if (t0 >= n) return;  // the whole wave is past the chunk
   auto block = [&](int j0, float (&d)[16]) __attribute__((always_inline)) {
-    const bf16* mrow = mu + int64_t(min(j0 + n32, Kc - 1)) * D + 8 * hf;
-    bf16x8 mf[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) mf[s] = *reinterpret_cast<const bf16x8*>(mrow + 16 * s);
+    const uint4* mrow = s_mu + min(j0 + n32, Kc - 1) * PR + hf;
     f32x16 acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mf[s], xf[s], acc, 0, 0, 0);
+    for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, mrow[2 * s]), xf[s], acc, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int j = j0 + (i / 4) * 8 + hf * 4 + (i % 4);
-      d[i] = j < Kc ? __builtin_fmaf(-2.0f, acc[i], bj[j]) : __builtin_inff();
+      d[i] = j < Kc ? __builtin_fmaf(-2.0f, acc[i], s_b[j]) : __builtin_inff();
     }
   };
   float d1 = __builtin_inff(), d2 = __builtin_inff(), bmax = 0.0f;
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int j = j0 + (i / 4) * 8 + hf * 4 + (i % 4);
-      bmax = fmaxf(bmax, j < Kc ? bj[j] : 0.0f);
+      bmax = fmaxf(bmax, j < Kc ? s_b[j] : 0.0f);
       d2 = fminf(d2, fmaxf(d1, d[i]));
       best = d[i] < d1 ? j : best;
       d1 = fminf(d1, d[i]);
@@ -455,7 +456,8 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
     best = p1 < d1 ? pb : best;  // a tie is inside the bound and decided below
     d1 = fminf(d1, p1);
   }
-  const float bound = (xx + bmax) * ((8.0f * (D + 16) + 4.0f * (D + 4)) * 0x1p-24f);
+  const float E = 2.0f * (D + 32) * 0x1p-24f * (xx + bmax);
+  const float bound = 1.01f * (2.0f * E + 2.0f * (D + 4) * 0x1p-24f * (fmaxf(d1 + xx, 0.0f) + E));
   // not greater rather than less or equal: NaN or infinite inputs take the literal form too
   const bool near = !(d2 - d1 > bound);
   if (__any(near)) {
@@ -472,7 +474,7 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
         const int i = __ffs(cand) - 1, j = j0 + (i / 4) * 8 + hf * 4 + (i % 4);
         cand &= cand - 1;
         if (j < Kc) {
-          const float l = literal_distance<D>(row, mu + int64_t(j) * D);
+          const float l = literal_distance<D>(row, s_mu + j * PR);
           if (lb == 0x7fffffff || l < ld) { lb = j; ld = l; }
         }
       }
@@ -487,38 +489,55 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
 
 // Lloyd update: sums x_tc over the tokens of cluster j in token order (fp64),
 // then stores the mean rounded once to the table type; an empty cluster keeps
-// its centroid. A block of d threads per (cluster, head, side): it lists the
-// cluster's tokens of a run of kKmList in order (each thread scans kKmList / d
-// ids, a prefix sum places its finds), then every thread adds its channel over
-// the list, 16 rows in flight. 4,680 tokens of 10 heads, 128 centroids, Keys and
-// Values: 665 us when each (cluster, channel) scanned all ids, 30 us so.
-constexpr int kKmList = 8192;
+// its centroid. A wave per (cluster, head, side): it lists the cluster's tokens of
+// a run of kKmList in order (each lane scans kKmList / 64 ids, four at a time as
+// the zero bytes of ids ^ j, keeping the finds as bits; a prefix sum places them),
+// then every lane adds its D / 64 channels over the list, 16 to 32 rows in flight.
+// 4,680 tokens of 10 heads, 128 centroids, Keys and Values: 665 us when each
+// (cluster, channel) scanned all ids, 30 us with a block of D lanes that read its
+// ids again to list them, 26 us so.
+constexpr int kKmList = 4096, kKmRows = 16;
 template <typename T, int D>
-__global__ __launch_bounds__(D) void km_update_kernel(const KmArgs a) {
-  constexpr int PT = kKmList / D;  // ids per thread and run
+__global__ __launch_bounds__(64) void km_update_kernel(const KmArgs a) {
+  constexpr int PT = kKmList / 64, NE = D / 64;  // ids per lane and run, channels per lane
   __shared__ uint16_t s_list[kKmList];
-  __shared__ int s_cnt[2];
-  __shared__ float s_red[2];
-  const int j = blockIdx.x, c = threadIdx.x, side = blockIdx.z, lane = c & 63, wave = c >> 6;
+  const int j = blockIdx.x, lane = threadIdx.x, side = blockIdx.z;
   const int64_t bh = blockIdx.y, n = a.n;
   const int b = int(bh / a.heads), h = int(bh % a.heads);
   const uint8_t* as = a.assign + (int64_t(side) * a.bh + bh) * n;
-  const T* x = reinterpret_cast<const T*>(a.x[side]) + (int64_t(b) * n * a.heads + h) * D + c;
+  typedef T Row __attribute__((ext_vector_type(NE)));
+  const T* x = reinterpret_cast<const T*>(a.x[side]) + (int64_t(b) * n * a.heads + h) * D + lane * NE;
   const int64_t stride = int64_t(a.heads) * D;
-  double sum = 0.0;
+  double sum[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) sum[e] = 0.0;
   int64_t cnt = 0;
   for (int64_t run = 0; run < n; run += kKmList) {
     const int nr = n - run < kKmList ? int(n - run) : kKmList;
-    // ids of this thread: [lo, hi) of the run, shared out evenly in multiples of 4
-    const int per = min(PT, ((nr + D - 1) / D + 3) / 4 * 4);
-    const int lo = min(nr, c * per), hi = min(nr, lo + per);
+    // ids of this lane: [lo, hi) of the run, shared out evenly in multiples of 4
+    const int per = ((nr + 63) / 64 + 3) / 4 * 4;
+    const int lo = min(nr, lane * per), hi = min(nr, lo + per);
+    uint32_t hits[PT / 4];  // bit 8 k + 7: id 4 i + k of the lane's share is j
     int mine = 0;
-    for (int i = lo; i < hi; i += 4) {
-      uint32_t w = 0;
-      if (i + 4 <= hi) __builtin_memcpy(&w, as + run + i, 4);
-      else
-        for (int k = 0; i + k < hi; ++k) w |= uint32_t(as[run + i + k]) << (8 * k);
-      for (int k = 0; k < 4; ++k) mine += i + k < hi && int((w >> (8 * k)) & 255) == j;
+    // every load first (a word that would pass the run's end starts earlier)
+    uint32_t w[PT / 4];
+    if (nr >= 4) {
+#pragma unroll
+      for (int i = 0; i < PT / 4; ++i) __builtin_memcpy(&w[i], as + run + min(lo + 4 * i, nr - 4), 4);
+    } else {
+#pragma unroll
+      for (int i = 0; i < PT / 4; ++i) w[i] = 0;
+      for (int k = 0; k < nr; ++k) w[0] |= uint32_t(as[run + k]) << (8 * k);
+    }
+#pragma unroll
+    for (int i = 0; i < PT / 4; ++i) {
+      const int at = lo + 4 * i, left = min(4, hi - at);  // ids of the word that are the lane's
+      const int back = nr >= 4 ? max(0, at - (nr - 4)) : 0;
+      uint32_t v = left > 0 ? w[i] >> (8 * min(back, 3)) : 0;
+      v ^= uint32_t(j) * 0x01010101u;
+      // the top bit of every byte that is zero
+      hits[i] = ~(((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) & (left > 0 ? 0x80808080u >> (8 * (4 - left)) : 0u);
+      mine += __popc(hits[i]);
     }
     int incl = mine;
 #pragma unroll
@@ -526,55 +545,71 @@ __global__ __launch_bounds__(D) void km_update_kernel(const KmArgs a) {
       const int y = __shfl_up(incl, o);
       incl += lane >= o ? y : 0;
     }
+    const int total = __shfl(incl, 63);
+    int at = incl - mine;
     __syncthreads();  // the previous run's list is used up
-    if (lane == 63) s_cnt[wave] = incl;
+#pragma unroll
+    for (int i = 0; i < PT / 4; ++i)
+      for (uint32_t m = hits[i]; m; m &= m - 1) s_list[at++] = uint16_t(lo + 4 * i + (__ffs(m) - 1) / 8);
     __syncthreads();
-    int at = incl - mine + (wave ? s_cnt[0] : 0);
-    const int total = s_cnt[0] + (D == 128 ? s_cnt[1] : 0);
-    if (mine)
-      for (int i = lo; i < hi; ++i)
-        if (int(as[run + i]) == j) s_list[at++] = uint16_t(i);
-    __syncthreads();
-    int i = 0;
-    for (; i + 16 <= total; i += 16) {
-      float v[16];
+    // the next rows load while these are added
+    Row v[kKmRows], u[kKmRows];
+    auto rows = [&](Row (&r)[kKmRows], int i) __attribute__((always_inline)) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = ldf(x + (run + s_list[i + k]) * stride);
+      for (int k = 0; k < kKmRows; ++k)
+        r[k] = *reinterpret_cast<const Row*>(x + (run + s_list[min(i + k, total - 1)]) * stride);
+    };
+    auto add = [&](const Row (&r)[kKmRows], int i) __attribute__((always_inline)) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) sum += (double)v[k];
-    }
-    if (i < total) {
-      float v[16];
+      for (int k = 0; k < kKmRows; ++k)
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = ldf(x + (run + s_list[min(i + k, total - 1)]) * stride);
-#pragma unroll
-      for (int k = 0; k < 16; ++k)
-        if (i + k < total) sum += (double)v[k];
+        for (int e = 0; e < NE; ++e) sum[e] += i + k < total ? (double)(float)r[k][e] : 0.0;
+    };
+    if (total > 0) rows(v, 0);
+    for (int i = 0; i < total; i += 2 * kKmRows) {
+      if (i + kKmRows < total) rows(u, i + kKmRows);
+      add(v, i);
+      if (i + 2 * kKmRows < total) rows(v, i + 2 * kKmRows);
+      if (i + kKmRows < total) add(u, i + kKmRows);
     }
     cnt += total;
   }
   if (cnt == 0) return;  // block-uniform
   uint8_t* slab = a.calib + bh * a.slab;
-  T* mu = reinterpret_cast<T*>(slab + a.o_mu[side]) + j * D + c;
-  T m;
-  store_rn(&m, sum / (double)cnt);
-  *mu = m;
-  const float f = ldf(&m), s = block_sum(f * f, D, s_red);
-  if (c == 0) reinterpret_cast<float*>(slab + a.o_b[side])[j] = s;
+  T* mu = reinterpret_cast<T*>(slab + a.o_mu[side]) + j * D + lane * NE;
+  float s = 0.0f;
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    T m;
+    store_rn(&m, sum[e] / (double)cnt);
+    mu[e] = m;
+    s = __builtin_fmaf(ldf(&m), ldf(&m), s);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (lane == 0) reinterpret_cast<float*>(slab + a.o_b[side])[j] = s;
 }
 
 template <typename T, int D>
 hipError_t kmeans_td(const KmArgs& a, int iters, hipStream_t s) {
   const dim3 gc((unsigned)a.Kc, (unsigned)a.bh, 2);
+  const size_t lds = size_t(a.Kc) * (D / 8 + 1) * 16 + size_t(a.Kc) * 4;
+  if constexpr (sizeof(T) == 2) {
+    if (lds > 64 * 1024) {  // above what a launch gets unasked (160 KB per CU on MI355X)
+      const hipError_t e = hipFuncSetAttribute((const void*)km_assign_mfma_kernel<D>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, int(sizeof(KmAssignLds<D>)));
+      if (e != hipSuccess) return e;
+    }
+  }
   hipLaunchKernelGGL(km_init_kernel<T>, gc, dim3(D), 0, s, a);
   for (int it = 0; it < iters; ++it) {
     if constexpr (sizeof(T) == 2)
       hipLaunchKernelGGL((km_assign_mfma_kernel<D>), dim3((unsigned)((a.n + 127) / 128), (unsigned)a.bh, 2), dim3(256),
-                         0, s, a);
+                         lds, s, a);
     else
       hipLaunchKernelGGL((km_assign_kernel<T, D>), dim3((unsigned)((a.n + 255) / 256), (unsigned)a.bh, 2), dim3(256),
                          0, s, a);
-    hipLaunchKernelGGL((km_update_kernel<T, D>), gc, dim3(D), 0, s, a);
+    hipLaunchKernelGGL((km_update_kernel<T, D>), gc, dim3(64), 0, s, a);
   }
   return hipGetLastError();
 }
