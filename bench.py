@@ -377,13 +377,10 @@ def main():
     ms_step = wall * 1000.0 / args.steps
 
     # the streaming forms, timed separately on the same inputs (skipped with
-    # --no-streaming, so that a kernel trace holds the step's launches only: the
-    # per-epoch and two-part forms launch the same plain attention kernel)
+    # --no-streaming, so that a kernel trace holds the step's launches only)
     act_ms = ep_ms = act_cfg = ep_cfg = None
     if not args.no_streaming:
-        # the last chunk stays exact (BF16) beside the packed history of the rest;
-        # with the two-part workspace: packed whole tiles through the plain kernel,
-        # the rest through the general one, merged by log-sum-exp
+        # the last chunk stays exact (BF16) beside the packed history of the rest
         n_pk = wl.n_cache - n_new
         ea, eb = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         ws_act = qw.quantwm_attend_active_workspace_bytes(cfg, n_pk, n_new, wl.n_q)
@@ -402,8 +399,7 @@ def main():
         act_ms = ea.elapsed_time(eb) / 5
 
         # calibration epochs: one per appended chunk (the timing does not depend on
-        # the tables' values, so every epoch reuses this calibration block); with
-        # the per-epoch workspace each epoch's keys go through the plain kernel
+        # the tables' values, so every epoch reuses this calibration block)
         starts = [s0 for s0, _ in wl.chunks()]
         calibs = calib.repeat(len(starts))
         ws_ep = qw.quantwm_attend_epochs_workspace_bytes(cfg, starts, wl.n_cache, 0, wl.n_q)
@@ -421,8 +417,8 @@ def main():
         torch.cuda.synchronize()
         ep_ms = ea.elapsed_time(eb) / 5
         del calibs, ep_ws, act_ws
-        act_cfg = f"{n_pk} packed + {n_new} exact BF16 keys, two-part workspace {ws_act} B"
-        ep_cfg = f"{len(starts)} calibration epochs, one per {wl.chunk}-token chunk, per-epoch workspace {ws_ep} B"
+        act_cfg = f"{n_pk} packed + {n_new} exact BF16 keys, workspace {ws_act} B"
+        ep_cfg = f"{len(starts)} calibration epochs, one per {wl.chunk}-token chunk, workspace {ws_ep} B"
 
     rec = kernel_record(wl, n_new, app_all, att_all, P.ws_bytes)
     bh = wl.batch * wl.heads

@@ -37,15 +37,18 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
                                                      int Kc, int r, int full) {
   uint8_t* slab = calib + int64_t(blockIdx.x) * C.slab_bytes;
   const int j0 = blockIdx.y * kDeriveRows, j1 = min(j0 + kDeriveRows, Kc);
-  const float* w = reinterpret_cast<const float*>(slab + C.w);
+  // the fields of a slab are disjoint: with the inputs marked so, the loops below
+  // load ahead of their stores
+  const float* __restrict__ w = reinterpret_cast<const float*>(slab + C.w);
   float* wg = reinterpret_cast<float*>(slab + C.wg);
-  const T* mk = reinterpret_cast<const T*>(slab + C.mu_k);
-  const T* mv = reinterpret_cast<const T*>(slab + C.mu_v);
+  const T* __restrict__ mk = reinterpret_cast<const T*>(slab + C.mu_k);
+  const T* __restrict__ mv = reinterpret_cast<const T*>(slab + C.mu_v);
   float* ak = reinterpret_cast<float*>(slab + C.a_k);
   float* bk = reinterpret_cast<float*>(slab + C.b_k);
-  float* av = reinterpret_cast<float*>(slab + C.a_v);
+  float* __restrict__ av = reinterpret_cast<float*>(slab + C.a_v);
   float* bv = reinterpret_cast<float*>(slab + C.b_v);
-  const float* mm = reinterpret_cast<const float*>(slab + C.m);
+  const float* __restrict__ mm = reinterpret_cast<const float*>(slab + C.m);
+#pragma unroll 8
   for (int i = j0 * d + threadIdx.x; i < j1 * d; i += 256) {
     const int c = i % d;
     const float mkv = ldf(mk + i), mvv = ldf(mv + i);
@@ -65,7 +68,8 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
     // p0 keeps a's top 8 significant bits (truncated), p1 the top 8 of the exact
     // remainder a - p0, and p2 = a - p0 - p1, which has at most 8 significant
     // bits left and so is a BF16 value (for |a| above 2^-110 or so)
-    uint16_t* pl = reinterpret_cast<uint16_t*>(slab + C.a_k3);
+    uint16_t* __restrict__ pl = reinterpret_cast<uint16_t*>(slab + C.a_k3);
+#pragma unroll 8
     for (int i = j0 * d + threadIdx.x; i < j1 * d; i += 256) {
       const float av0 = ak[i];
       const uint32_t u0 = __float_as_uint(av0) & 0xffff0000u;
@@ -139,8 +143,9 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
     int ek = 0, ev = 0;
     if (s_max[0][0] > 0.0f) { int x; frexpf(s_max[0][0], &x); ek = x - 15; }  // max in [2^(x-1), 2^x)
     if (s_max[1][0] > 0.0f) { int x; frexpf(s_max[1][0], &x); ev = x - 15; }
-    _Float16* hk = reinterpret_cast<_Float16*>(slab + C.mu_k16);
-    _Float16* hv = reinterpret_cast<_Float16*>(slab + C.mu_v16);
+    _Float16* __restrict__ hk = reinterpret_cast<_Float16*>(slab + C.mu_k16);
+    _Float16* __restrict__ hv = reinterpret_cast<_Float16*>(slab + C.mu_v16);
+#pragma unroll 8
     for (int i = j0 * d + threadIdx.x; i < j1 * d; i += 256) {
       hk[i] = (_Float16)ldexpf(ldf(mk + i), -ek);
       hv[i] = (_Float16)ldexpf(ldf(mv + i), -ev);
@@ -496,7 +501,7 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
 // 4,680 tokens of 10 heads, 128 centroids, Keys and Values: 665 us when each
 // (cluster, channel) scanned all ids, 30 us with a block of D lanes that read its
 // ids again to list them, 26 us so.
-constexpr int kKmList = 4096, kKmRows = 16;
+constexpr int kKmList = 8192, kKmRows = 16;
 template <typename T, int D>
 __global__ __launch_bounds__(64) void km_update_kernel(const KmArgs a) {
   constexpr int PT = kKmList / 64, NE = D / 64;  // ids per lane and run, channels per lane
@@ -560,10 +565,19 @@ __global__ __launch_bounds__(64) void km_update_kernel(const KmArgs a) {
         r[k] = *reinterpret_cast<const Row*>(x + (run + s_list[min(i + k, total - 1)]) * stride);
     };
     auto add = [&](const Row (&r)[kKmRows], int i) __attribute__((always_inline)) {
+      const int m = total - i;
+      if (m >= kKmRows) {
 #pragma unroll
-      for (int k = 0; k < kKmRows; ++k)
+        for (int k = 0; k < kKmRows; ++k)
 #pragma unroll
-        for (int e = 0; e < NE; ++e) sum[e] += i + k < total ? (double)(float)r[k][e] : 0.0;
+          for (int e = 0; e < NE; ++e) sum[e] += (double)(float)r[k][e];
+      } else {
+#pragma unroll
+        for (int k = 0; k < kKmRows; ++k)
+          if (k < m)
+#pragma unroll
+            for (int e = 0; e < NE; ++e) sum[e] += (double)(float)r[k][e];
+      }
     };
     if (total > 0) rows(v, 0);
     for (int i = 0; i < total; i += 2 * kKmRows) {
