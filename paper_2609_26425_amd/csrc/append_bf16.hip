@@ -31,7 +31,7 @@
 // d' <= T, gathered as a bit per centroid from the distances, which stay in
 // registers. Carrying the ids in the lists took 17 instructions per
 // candidate instead of 6. Where more than M ids qualify (equal distances at T) the
-// wave redoes the search with lists of (d', id).
+// wave redoes the selection with lists of (d', id).
 //
 // Score. The M candidates' ranges are taken in one pass over the token, so their
 // rows load together and a token word is unpacked once for all of them; the
@@ -42,7 +42,7 @@
 // over groups (added in group order) are combined across the pair with
 // v_permlane32_swap. The PSAC projection E U_r runs on the matrix cores as
 // well: the errors of each 8-channel residual chunk are the B operand of one k
-// step, and one exchange puts the coefficients in rank order on both lanes.
+// step, and each lane quantises the ranks that its accumulator holds.
 // Everything that turns a float into an integer follows the equations'
 // operation order in fp32 with IEEE division and round-to-nearest-even, as in
 // the fp32 kernel.
@@ -52,7 +52,8 @@
 // every lane reading centroid rows from global memory the cache's tag lookups
 // did: 64 lines per load instruction. 40 heads x 4,680 tokens, 128 centroids,
 // r = 16: 162 us so, 94 us from LDS; 120 heads x 3,120, 256 centroids, r = 32,
-// 8-bit scales: 514 and 284 us; 12 heads x 880, 64 centroids: 24.8 and 19.8 us.
+// 8-bit scales: 541 and 298 us; 12 heads x 880, 64 centroids: 24.8 and 19.8 us,
+// 13.7 us with Keys and Values in separate workgroups.
 #include "append_common.h"
 #include "xcd_order.h"
 

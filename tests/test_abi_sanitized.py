@@ -1,6 +1,6 @@
 """The host-side C ABI checks (tests/test_abi_cpu.py: size queries, argument
 validation, error paths; no kernel launch) against a build of the library whose
-host code (api.hip, the host eigensolver) carries AddressSanitizer and
+host code (api.hip) carries AddressSanitizer and
 UndefinedBehaviorSanitizer, any report fatal, in a child process that preloads
 clang's ASan runtime."""
 import glob
