@@ -314,7 +314,7 @@ __device__ inline void residual_half(uint4 (&xh)[D / 16], R mrow, int hf,
         mu[k] = bf_el<k>(m0);
       });
       round_quotients<8>(xv, mu, s, inv, big, t);
-      // Eq. 1 codes as floats: a zero step has inv = 0 and z = 0, so its codes are 0.
+      // Eq. 1 codes as floats: a zero step has t = 0 and z = 0, so its codes are 0.
       // The code word sums q 4^k (exact); mu + s (q - z) rounds once, as the
       // product is exact (at most 21 significant bits)
       float wf = 0.0f;

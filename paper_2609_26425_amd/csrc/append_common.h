@@ -36,7 +36,8 @@ __device__ inline uint16_t f16_bits(float exact) {
 // two differ by less than 2^-20 and round to the same integer unless t is
 // within 2^-19 of a half-integer (or |t| > 4, out of this bound: `big`, from the
 // group's largest residual). If any lane of the wave meets such a case the whole
-// chunk takes the exact division.
+// chunk takes the exact division. A zero step (s = 0, inv = 0) gives t = 0 on
+// either path: other lanes of the wave choose the path, so both must agree.
 template <int N>
 __device__ inline void round_quotients(const float (&xv)[N], const float (&mu)[N], float s, float inv, bool big,
                                        float (&t)[N]) {
@@ -51,7 +52,7 @@ __device__ inline void round_quotients(const float (&xv)[N], const float (&mu)[N
     t[c] = k;
   }
   if (__any(big || dmax > 0.5f - 0x1p-19f)) {
-    const float sd = s != 0.0f ? s : 1.0f;
+    const float sd = s != 0.0f ? s : __builtin_inff();  // x / inf = 0
 #pragma unroll
     for (int c = 0; c < N; ++c) t[c] = rintf((xv[c] - mu[c]) / sd);
   }

@@ -74,3 +74,33 @@ def test_append_bytes(name):
         # fp32 sums of d exact products: d 2^-24 of the terms' magnitudes, about |e| |u|
         tol = d * 2.0 ** -24 * np.abs(e).max() * 8 + 1e-6
         assert np.abs(coef.cpu().numpy() - e).max() <= tol
+
+
+@pytest.mark.parametrize("d,g", [(128, 16), (64, 32), (128, 64)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_zero_step_groups_store_zero_codes(d, g, dtype):
+    """8-bit scales: a group whose step rounds to code 0 stores zero codes, also when
+    its wave holds tokens whose quotients are exact halves (the wave then divides
+    instead of multiplying by the reciprocal, with a residual of 0.9 over no step)."""
+    H, n, kc = 2, 64, 1
+    rng = np.random.default_rng(d + g)
+    x = np.zeros((1, n, H, d), np.float32)
+    # even tokens: one group with a step of about 200, the others within [0, 0.875]
+    x[:, ::2] = rng.choice([0.0, 0.5, 0.625, 0.875], (1, n // 2, H, d))
+    x[:, ::2, :, 0], x[:, ::2, :, 1] = -304.0, 304.0
+    # odd tokens: every group has the step 255 (sigma = 1) and quotients at +-1/2
+    x[:, 1::2] = rng.choice([-127.5, 127.5], (1, n // 2, H, d))
+    x[:, 1::2, :, ::g], x[:, 1::2, :, 1::g] = 512.0, -253.0
+    mu = np.zeros((1, H, kc, d), np.float32)
+    tables = (mu, mu, np.ones((1, H, d), np.float32), None, None)
+    ocfg = oracle.cfg_of(1, H, d, kc, g, 0, 1, n, dtype == "bf16", 1)
+    ref = oracle.new_cache(ocfg)
+    oracle.append(ocfg, tables, ref, 0, x, x)
+    assert (ref[:H * n * d // 4].reshape(H, n, d // 4)[:, ::2, g // 4:] == 0).all()
+    cfg = qw.make_config(1, H, d, kc, g, 0, 1, n, dtype, 1)
+    T = lambda x, t=cfg.torch_dtype: torch.from_numpy(np.ascontiguousarray(x)).to(DEV, t)  # noqa: E731
+    calib = torch.zeros(qw.quantwm_calib_bytes(cfg), dtype=torch.uint8, device=DEV)
+    qw.quantwm_calib_pack(cfg, T(mu), T(mu), T(tables[2], torch.float32), None, None, calib)
+    cache = torch.zeros(qw.quantwm_cache_bytes(cfg), dtype=torch.uint8, device=DEV)
+    qw.quantwm_append(cfg, calib, cache, 0, T(x), T(x), n)
+    assert np.array_equal(cache.cpu().numpy(), ref)
