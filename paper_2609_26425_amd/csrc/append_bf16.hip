@@ -632,6 +632,33 @@ append_bf16_kernel(const AppendArgs a) {
       }
     });
   }
+  // every score overflowed (W_g R^2 past fp32: a residual of about 1.8e19 / sqrt(W_g)
+  // or more): centroid 0, with its own ranges
+  const bool none = !(zs < __builtin_inff());
+  if (__builtin_expect(__any(none), 0)) {
+    const uint4* krow = reinterpret_cast<const uint4*>(reinterpret_cast<const bf16*>(a.k) + src);
+    static_for<0, GL>([&](auto gi) {
+      constexpr int gl = decltype(gi)::value;
+      float mx = -__builtin_inff(), mn = __builtin_inff();
+#pragma unroll 1
+      for (int c = gl * (H::GC / 8); c < (gl + 1) * (H::GC / 8); ++c) {
+        const uint4 mu = tabK[P::at(0, hf * NS + c)];
+        const uint4 x = krow[c];
+        static_for<0, 8>([&](auto ki) {
+          constexpr int k = decltype(ki)::value;
+          const float r = bf_el<k>(x) - bf_el<k>(mu);
+          mx = fmaxf(mx, r);
+          mn = fminf(mn, r);
+        });
+      }
+      if constexpr (H::SPAN) {
+        mx = fmaxf(mx, partner(mx, hf));
+        mn = fminf(mn, partner(mn, hf));
+      }
+      gmin[gl] = none ? mn : gmin[gl];
+      gmax[gl] = none ? mx : gmax[gl];
+    });
+  }
 
   // ---- Keys: INT2 residual against mu_z, and PSAC (Eq. 13, 16): C = E U_r with
   // E_c = k_c - khat_0,c, on the matrix cores. Each residual chunk is the lane's

@@ -104,3 +104,32 @@ def test_zero_step_groups_store_zero_codes(d, g, dtype):
     cache = torch.zeros(qw.quantwm_cache_bytes(cfg), dtype=torch.uint8, device=DEV)
     qw.quantwm_append(cfg, calib, cache, 0, T(x), T(x), n)
     assert np.array_equal(cache.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("d,g,m,kc,st", [(128, 32, 4, 40, 0), (128, 16, 8, 20, 1), (64, 64, 1, 16, 0), (64, 16, 4, 150, 1)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_keys_whose_scores_overflow(d, g, m, kc, st, dtype):
+    """One channel at 3e19: W_g R^2 is infinite for every candidate, and so is the
+    literal distance, so the choice is centroid 0. The outlier's group saturates and
+    the token's other groups keep their residual (with 8-bit scales the shared scale
+    saturates, and their steps are 0)."""
+    H, n = 3, 70
+    rng = np.random.default_rng(d + g + kc)
+    bf = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.float32)).bfloat16().float().numpy()  # noqa: E731
+    k, v = bf(rng.integers(-8, 9, (1, n, H, d)) / 4.0), bf(rng.integers(-8, 9, (1, n, H, d)) / 4.0)
+    k[:, ::3, :, 5], k[:, 1::3, :, d - 1] = bf(np.float32(3e19)), bf(np.float32(-3e19))
+    mu_k, mu_v = (bf(rng.integers(-8, 9, (1, H, kc, d)) / 4.0) for _ in range(2))
+    tables = (mu_k, mu_v, np.ones((1, H, d), np.float32), None, None)
+    ocfg = oracle.cfg_of(1, H, d, kc, g, 0, m, n, dtype == "bf16", st)
+    ref = oracle.new_cache(ocfg)
+    diag = oracle.append(ocfg, tables, ref, 0, k, v, diagnostics=True)
+    big = np.abs(k).max(axis=3) > 1e19
+    ids = diag["k_ids"].transpose(0, 2, 1)
+    assert (ids[big] == 0).all() and (ids[~big] != 0).any()
+    cfg = qw.make_config(1, H, d, kc, g, 0, m, n, dtype, st)
+    T = lambda x, t=cfg.torch_dtype: torch.from_numpy(np.ascontiguousarray(x)).to(DEV, t)  # noqa: E731
+    calib = torch.zeros(qw.quantwm_calib_bytes(cfg), dtype=torch.uint8, device=DEV)
+    qw.quantwm_calib_pack(cfg, T(mu_k), T(mu_v), T(tables[2], torch.float32), None, None, calib)
+    cache = torch.zeros(qw.quantwm_cache_bytes(cfg), dtype=torch.uint8, device=DEV)
+    qw.quantwm_append(cfg, calib, cache, 0, T(k), T(v), n)
+    assert np.array_equal(cache.cpu().numpy(), ref)
