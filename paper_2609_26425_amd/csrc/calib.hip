@@ -413,7 +413,8 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
 #pragma unroll 8
   for (int i = threadIdx.x; i < Kc * (D / 8); i += 256)
     s_mu[i / (D / 8) * PR + i % (D / 8)] = reinterpret_cast<const uint4*>(mu)[i];
-  for (int i = threadIdx.x; i < Kc; i += 256) s_b[i] = bj[i];
+  // a NaN norm (a NaN centroid) counts as infinite, so that the bound below is too
+  for (int i = threadIdx.x; i < Kc; i += 256) s_b[i] = bj[i] == bj[i] ? bj[i] : __builtin_inff();
   // k index 8 hf + i of step s is channel 16 s + 8 hf + i on both operands
   bf16x8 xf[NS];
   float xx = 0.0f;
@@ -463,7 +464,8 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
   }
   const float E = 2.0f * (D + 32) * 0x1p-24f * (xx + bmax);
   const float bound = 1.01f * (2.0f * E + 2.0f * (D + 4) * 0x1p-24f * (fmaxf(d1 + xx, 0.0f) + E));
-  // not greater rather than less or equal: NaN or infinite inputs take the literal form too
+  // not greater rather than less or equal: with NaN or infinite inputs the bound is NaN or
+  // infinite, and the token takes the literal form over every centroid
   const bool near = !(d2 - d1 > bound);
   if (__any(near)) {
     int lb = 0x7fffffff;
@@ -480,7 +482,7 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
         cand &= cand - 1;
         if (j < Kc) {
           const float l = literal_distance<D>(row, s_mu + j * PR);
-          if (lb == 0x7fffffff || l < ld) { lb = j; ld = l; }
+          if (j == 0 || l < ld) { lb = j; ld = l; }  // as the serial scan: a NaN only stays as id 0
         }
       }
     }
