@@ -379,7 +379,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 //     most (d + 16) u |x| |mu_j|, doubled here for a sum in any grouping; with the
 //     sum of |mu_j|^2 and the last rounding d'_j is within E = 2 (d + 32) u S;
 //   - the literal distance (three roundings per term, d terms) is within
-//     (d + 4) u D_j of D_j.
+//     (d + 4) u D_j of D_j;
+//   - a product or a sum below the normal range may lose up to 2^-126 each time, on
+//     either side: E also carries 4 (d + 32) 2^-126.
 // With D_1 the distance of the smallest d', a centroid whose d' exceeds that by
 // more than 2 E + 2 (d + 4) u (D_1 + E), and a little, has the larger literal
 // distance. Where a second centroid is inside that bound, a second pass over the
@@ -462,7 +464,7 @@ __global__ __launch_bounds__(256) void km_assign_mfma_kernel(const KmArgs a) {
     best = p1 < d1 ? pb : best;  // a tie is inside the bound and decided below
     d1 = fminf(d1, p1);
   }
-  const float E = 2.0f * (D + 32) * 0x1p-24f * (xx + bmax);
+  const float E = 2.0f * (D + 32) * 0x1p-24f * (xx + bmax) + 4.0f * (D + 32) * 0x1p-126f;
   const float bound = 1.01f * (2.0f * E + 2.0f * (D + 4) * 0x1p-24f * (fmaxf(d1 + xx, 0.0f) + E));
   // not greater rather than less or equal: with NaN or infinite inputs the bound is NaN or
   // infinite, and the token takes the literal form over every centroid

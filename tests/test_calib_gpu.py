@@ -1,6 +1,6 @@
 """Calibration on the device at the sizes where its kernels can go wrong: K-means
-with exact distance ties, duplicate tokens, odd token counts and NaN or
-infinite tokens against the oracle's Lloyd rounds (bit for
+with exact distance ties, duplicate tokens, odd token counts, squares below the
+normal range and NaN or infinite tokens against the oracle's Lloyd rounds (bit for
 bit), the token-order statistics at the edges of a
 staged run, and the principal basis of degenerate second moments (low rank, equal
 eigenvalues) against its defining equations."""
@@ -42,6 +42,8 @@ def _tokens(kind, n, d, rng):
         return rng.integers(-1, 2, (1, n, 2, d)).astype(np.float32)
     if kind == "close":     # one point and tokens a few BF16 ulps around it: every centroid inside the bound
         return (1.0 + rng.integers(-2, 3, (1, n, 2, d)) / 128.0).astype(np.float32)
+    if kind == "tiny":      # squares below the normal range
+        return torch.from_numpy((rng.standard_normal((1, n, 2, d)) * 1e-22).astype(np.float32)).bfloat16().float().numpy()
     if kind == "nan":       # NaN and infinite centroids among the first and later ids of both lane halves
         x = (rng.integers(-64, 65, (1, n, 2, d)) / 8.0).astype(np.float32)
         x[0, [4 * n // 48, 12 * n // 48, 33 * n // 48], 0, 3] = np.nan
@@ -55,8 +57,8 @@ def _tokens(kind, n, d, rng):
 # (8192) of the update; centroid counts around a matrix-core block (32)
 @pytest.mark.parametrize("kind,d,n,kc", [("plain", 128, 8200, 33), ("plain", 64, 129, 17), ("ties", 64, 300, 33),
                                          ("ties", 128, 127, 256), ("close", 128, 333, 64), ("close", 64, 31, 1),
-                                         ("plain", 128, 1, 32), ("plain", 64, 8193, 64),
-                                         ("nan", 128, 480, 48), ("nan", 64, 96, 48)])
+                                         ("plain", 128, 1, 32), ("plain", 64, 8193, 64), ("tiny", 128, 200, 20),
+                                         ("tiny", 64, 300, 64), ("nan", 128, 480, 48), ("nan", 64, 96, 48)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_kmeans_bits(kind, d, n, kc, dtype):
     if dtype == "f32" and n > 1000:
