@@ -417,7 +417,6 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   constexpr int KW = CHK * int(sizeof(T)) / 4, VW = CHV * int(sizeof(T)) / 4;
   const T* __restrict__ k_act = reinterpret_cast<const T*>(a.k_act);
   const T* __restrict__ v_act = reinterpret_cast<const T*>(a.v_act);
-  const uint32_t npku = uint32_t(npk);
   // Packed fields are read with buffer loads: one resource per field of this
   // head (base = its first slot), this thread's byte offset inside a tile as the
   // vector offset (fixed for all tiles) and the tile's byte offset as the scalar
@@ -436,13 +435,14 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       w[4 * i] = u.x; w[4 * i + 1] = u.y; w[4 * i + 2] = u.z; w[4 * i + 3] = u.w;
     }
   };
-  auto field = [&](int64_t off, uint32_t bytes) {
+  auto field_to = [&](int64_t off, uint32_t bytes, int64_t end) {  // the first `end` slots
     return __builtin_amdgcn_make_buffer_rsrc((void*)(cache + off + slot0 * bytes), 0,
-                                             int(uint32_t(L.slots) * bytes), 0x00020000);
+                                             int(uint32_t(end) * bytes), 0x00020000);
   };
+  auto field = [&](int64_t off, uint32_t bytes) { return field_to(off, bytes, L.slots); };
   const auto r_kc = field(L.k_codes, D / 4), r_ki = field(L.k_ids, 1), r_kz = field(L.k_zp, zpb),
              r_ks = field(L.k_scale, sstride), r_vc = field(L.v_codes, D / 4), r_vi = field(L.v_ids, 1),
-             r_vz = field(L.v_zp, zpb), r_vs = field(L.v_scale, sstride);
+             r_vz = field(L.v_zp, zpb);
   const auto r_cc = field(L.k_coef, uint32_t(r)), r_cs = field(L.k_cscale, 2);
   // sparse rows (general instance only): this head's row pool and tile directory
   const auto r_pc = __builtin_amdgcn_make_buffer_rsrc((void*)(cache + L.k_coef + bh * L.pool * r), 0,
@@ -450,23 +450,28 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   const auto r_ps = __builtin_amdgcn_make_buffer_rsrc((void*)(cache + L.k_cscale + bh * L.pool * 2), 0,
                                                       int(uint32_t(L.pool) * 2u), 0x00020000);
   const uint32_t* dir = reinterpret_cast<const uint32_t*>(cache + L.k_dir + bh * (L.slots / 64) * 16);
-  const auto r_ksg = field(L.k_sigma, 2), r_vsg = field(L.v_sigma, 2);  // SI8 secondary scales
+  const auto r_ksg = field(L.k_sigma, 2), r_vs = field(L.v_scale, sstride);  // SI8: secondary Key scales, Value scale codes
   const int o_kc = kkey * (D / 4) + kch0 / 4, o_kz = kkey * zpb, o_ks = kkey * sstride;
   const int o_cc = ckey * r + cr0, o_cs = ckey * 2;
   const int o_vc = 2 * vkp * (D / 4) + vch0 / 4, o_vz = 2 * vkp * zpb + vg / 4,
             o_vs = 2 * vkp * sstride + (SI8 ? vg : 2 * vg);
 
-  // FULL: every key of the tile is < n_cache, so no per-thread guards. A key
-  // past n_cache (tail tiles only) gets centroid 0, scale 0 and code 0: a finite
-  // placeholder whose logit the mask turns into -inf, so it never contributes.
+  // Every thread loads its key's fields whatever the key (a tile never passes the
+  // head's slots): like the active chunk's loads, with no condition on the key in
+  // front of the tile barriers. Which ranks a thread reads (crole) and which rows a
+  // sparse tile holds stay conditions: those branches hold loads only and rejoin
+  // before the barrier, which the compiler may not move into them. Keys of a tile outside its segment, past n_cache or of a neighbouring epoch, are masked
+  // to a logit of -inf, whatever they decode to; but their Values meet a probability
+  // of 0, so they have to be finite: the Value scales of keys past the segment read
+  // as 0 (past the end of their buffer resource), and a key before it takes the scale
+  // of the segment's first key.
   // residual group, zero-point byte and 2-bit shift of each K piece and of the V run
   int kgrp[NSUB];
 #pragma unroll
   for (int u = 0; u < NSUB; ++u) kgrp[u] = (kch0 + 16 * u) / G;
   const int vzsh = 2 * (vg % 4);
-  // Placeholder fields (all zero) decode to centroid 0 with scale 0.
-  auto load_raw = [&](TileRegs<NSUB>& p, auto full_tag, uint32_t k0, auto rows_tag) __attribute__((always_inline)) {
-    constexpr bool FULL = decltype(full_tag)::value;
+  // r_v: the scale of the Values of the segment, lo: its first key
+  auto load_raw = [&](TileRegs<NSUB>& p, uint32_t k0, auto rows_tag, auto r_v, int lo) __attribute__((always_inline)) {
     using RT = decltype(rows_tag);
     constexpr bool ANY = std::is_same_v<RT, AnyRows>;
     const bool aligned = std::is_same_v<RT, WholeRows> || (ANY && raligned);
@@ -478,7 +483,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
     _Float16 ksb[NSUB], csb = 0, vsb[2] = {0, 0};
 #pragma unroll
     for (int u = 0; u < NSUB; ++u) { kzb[u] = 0; ksb[u] = 0; kcw[u] = 0; kcb[u] = 0; }
-    if (FULL || k0 + kkey < npku) {
+    {
       kid = __builtin_amdgcn_raw_buffer_load_b8(r_ki, kkey, k0i, 0);
 #pragma unroll
       for (int u = 0; u < NSUB; ++u) {
@@ -501,7 +506,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       }
     }
     if constexpr (RP > 0) {
-      if (sparse && crole && (FULL || k0 + ckey < npku)) {
+      if (sparse && crole) {
         // the key's row through the directory entry of its 64-key tile: present
         // iff its mask bit is set, at pool row base + (set bits below it)
         const uint32_t* e = dir + (k0 / 64) * 4;
@@ -514,7 +519,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
             if (cr0 + k < r)
               cw2[k / 4] |= uint32_t(__builtin_amdgcn_raw_buffer_load_b8(r_pc, row * r + cr0 + k, 0, 0)) << (8 * (k % 4));
         }
-      } else if (crole && (FULL || k0 + ckey < npku)) {
+      } else if (crole) {
         csb = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r_cs, o_cs, k0i * 2, 0));
         if (aligned) {
           if constexpr (RCH == 8) {
@@ -533,19 +538,18 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
     }
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      const uint32_t key = k0 + 2 * vkp + e;
-      if (FULL || key < npku) {
-        vid[e] = __builtin_amdgcn_raw_buffer_load_b8(r_vi, 2 * vkp + e, k0i, 0);
-        vzb[e] = __builtin_amdgcn_raw_buffer_load_b8(r_vz, o_vz + e * int(zpb), k0i * int(zpb), 0);
-        if constexpr (SI8) {
-          vcb[e] = __builtin_amdgcn_raw_buffer_load_b8(r_vs, o_vs + e * int(sstride), k0i * int(sstride), 0);
-          vsb[e] = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r_vsg, 2 * (2 * vkp + e), k0i * 2, 0));
-        } else {
-          vsb[e] = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r_vs, o_vs + e * int(sstride), k0i * int(sstride), 0));
-        }
-        if constexpr (CHV == 16) vcw[e] = __builtin_amdgcn_raw_buffer_load_b32(r_vc, o_vc + e * (D / 4), k0i * (D / 4), 0);
-        else vcw[e] = __builtin_amdgcn_raw_buffer_load_b16(r_vc, o_vc + e * (D / 4), k0i * (D / 4), 0);
+      // keys before the segment: only in its first tile, which the AnyRows form loads
+      const int dv = GEN && ANY ? max(lo - (k0i + 2 * vkp + e), 0) : 0;
+      vid[e] = __builtin_amdgcn_raw_buffer_load_b8(r_vi, 2 * vkp + e, k0i, 0);
+      vzb[e] = __builtin_amdgcn_raw_buffer_load_b8(r_vz, o_vz + e * int(zpb), k0i * int(zpb), 0);
+      if constexpr (SI8) {
+        vcb[e] = __builtin_amdgcn_raw_buffer_load_b8(r_vs, o_vs + e * int(sstride), k0i * int(sstride), 0);
+        vsb[e] = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r_v, 2 * (2 * vkp + e + dv), k0i * 2, 0));
+      } else {
+        vsb[e] = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r_v, o_vs + (e + dv) * int(sstride), k0i * int(sstride), 0));
       }
+      if constexpr (CHV == 16) vcw[e] = __builtin_amdgcn_raw_buffer_load_b32(r_vc, o_vc + e * (D / 4), k0i * (D / 4), 0);
+      else vcw[e] = __builtin_amdgcn_raw_buffer_load_b16(r_vc, o_vc + e * (D / 4), k0i * (D / 4), 0);
     }
     p.k_idb = kid;
 #pragma unroll
@@ -628,9 +632,6 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       for (int c = 0; c < CHV; ++c) store_pair<T>(vt + (vch0 + c) * LY::VS + 2 * vkp, x0[c], x1[c]);
     }
   };
-
-  using Full = std::integral_constant<bool, true>;
-  using Tail = std::integral_constant<bool, false>;
 
   // rows of the active chunk: keys 64 t .. 64 t + 63 of it; past its end the last
   // row again (the mask hides those keys). The row is clamped, not guarded: with
@@ -783,10 +784,10 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         }
         return;
       }
-      const int64_t nfull = (npk - g.base) / KT;  // tiles [0, nfull) of the segment hold packed keys only
+      // Value scales (SI8: secondary scales) of the segment's keys, 0 past them
+      const auto r_v = SI8 ? field_to(L.v_sigma, 2, GEN ? g.hi : npk) : field_to(L.v_scale, sstride, GEN ? g.hi : npk);
       auto prefetch = [&](TileRegs<NSUB>& p, int64_t t) __attribute__((always_inline)) {
-        if (t < nfull) load_raw(p, Full{}, uint32_t(g.base + t * KT), AnyRows{});
-        else load_raw(p, Tail{}, uint32_t(g.base + t * KT), AnyRows{});
+        load_raw(p, uint32_t(g.base + t * KT), AnyRows{}, r_v, int(g.lo));
       };
       int ek, en;
       table_exps(g.epoch, ek, en);
@@ -825,20 +826,19 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       };
       // Steady state, two tiles per trip with the sets in fixed places (so the wait
       // before each dequantisation covers only the older set's loads): the
-      // dequantised tile and the prefetched one (it + 3) are both all packed, so
-      // every load is issued unconditionally and the loads of one set stay in
-      // flight across the other set's dequantisation. The loop is compiled once
-      // per coefficient-load form.
-      const int64_t nsteady = (nfull < te ? nfull : te) - 3;  // it < nsteady: it + 3 < min(nfull, te)
+      // prefetched tile (it + 3) always exists, so every load is issued
+      // unconditionally and the loads of one set stay in flight across the other
+      // set's dequantisation. The loop is compiled once per coefficient-load form.
+      const int64_t nsteady = te - 3;  // it < nsteady: it + 3 < te
       int64_t it = ta;
       auto steady = [&](auto rows_tag) __attribute__((always_inline)) {
         for (; it + 1 < nsteady; it += 2) {
           __syncthreads();
           dequant(P1, it + 1);
-          load_raw(P1, Full{}, uint32_t(g.base + (it + 3) * KT), rows_tag);
+          load_raw(P1, uint32_t(g.base + (it + 3) * KT), rows_tag, r_v, 0);
           __syncthreads();
           dequant(P0, it + 2);
-          load_raw(P0, Full{}, uint32_t(g.base + (it + 4) * KT), rows_tag);
+          load_raw(P0, uint32_t(g.base + (it + 4) * KT), rows_tag, r_v, 0);
         }
       };
       if (GEN && RP > 0 && L.sparse) steady(SparseRows{});

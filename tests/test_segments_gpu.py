@@ -92,3 +92,73 @@ def test_segments(name):
         err = np.abs(out.float().cpu().numpy() - ref).max()
         assert err <= tol, (nb, err, tol)
         assert np.abs(lse.cpu().numpy() - rlse).max() <= 2e-2 if dtype == "bf16" else 1e-4
+
+
+@pytest.mark.parametrize("st", [0, 1], ids=["f16-scales", "i8-scales"])
+@pytest.mark.parametrize("n_act", [0, 20])
+def test_neighbour_epochs_of_other_magnitude(st, n_act):
+    """An epoch boundary inside a tile, Values around 2^-100 on one side and steps near
+    the largest binary16 on the other: neither side's keys may reach the other's
+    Queries as an infinity, whichever tables their tile is decoded with."""
+    H, d, kc, g, r, frame, nq = 2, 128, 16, 32, 4, 100, 200
+    starts, n_pk = [0, 100], 200
+    scale = [2.0 ** -100, 2.0 ** 16]
+    rng = np.random.default_rng(st + n_act)
+    ocfg = oracle.cfg_of(1, H, d, kc, g, r, 4, n_pk, True, st)
+    cfg = qw.make_config(1, H, d, kc, g, r, 4, n_pk, "bf16", st)
+    cache, tables = oracle.new_cache(ocfg), []
+    for e, vs in enumerate(scale):
+        k, v = _bf(rng.standard_normal((1, 100, H, d)), "bf16"), _bf(vs * rng.uniform(-1.5, 1.5, (1, 100, H, d)), "bf16")
+        mu = [_bf(s * rng.standard_normal((1, H, kc, d)), "bf16") for s in (1.0, vs * 2.0 ** -6)]
+        u = _bf(np.stack([np.linalg.qr(rng.standard_normal((d, d)))[0][:r] for _ in range(H)])[None], "bf16")
+        tables.append((mu[0], mu[1], np.ones((1, H, d), np.float32), u, np.ones((1, H, r), np.float32)))
+        oracle.append(ocfg, tables[e], cache, starts[e], k, v)
+    ka, va = (_bf(rng.standard_normal((1, n_act, H, d)), "bf16") for _ in range(2)) if n_act else (None, None)
+    q = _bf(rng.standard_normal((1, nq, H, d)), "bf16")
+    # Query frame 0 sees epoch 0 only, frame 1 epochs 0 and 1, and so on
+    ref, rlse, _ = oracle.attend(ocfg, None, cache, n_pk, q, 0, frame, k_act=ka, v_act=va,
+                                 epochs=list(zip(starts, tables)))
+    ref, rlse = ref.reshape(1, H, nq, d).transpose(0, 2, 1, 3), rlse.reshape(1, H, nq)
+    T = lambda x, t=torch.bfloat16: torch.from_numpy(np.ascontiguousarray(x)).to(DEV, t)  # noqa: E731
+    cb = qw.quantwm_calib_bytes(cfg)
+    calibs = torch.zeros(cb * len(starts), dtype=torch.uint8, device=DEV)
+    for e, t in enumerate(tables):
+        qw.quantwm_calib_pack(cfg, T(t[0]), T(t[1]), T(t[2], torch.float32), T(t[3]), T(t[4], torch.float32),
+                              calibs[e * cb:(e + 1) * cb])
+    out, lse = torch.full((1, nq, H, d), 7.0, dtype=torch.bfloat16, device=DEV), torch.empty((1, H, nq), device=DEV)
+    qd, kd, vd = T(q), T(ka) if n_act else None, T(va) if n_act else None
+    qw.quantwm_attend_epochs(cfg, calibs, starts, torch.from_numpy(cache).to(DEV), n_pk, kd, vd, n_act, qd, nq, 0, frame,
+                             out, lse)
+    got = out.double().cpu().numpy()
+    for f in range(len(starts)):  # BF16 weights and results: 2^-9 each of the Values' magnitude that the frame sees
+        rows = slice(100 * f, 100 * f + 100)
+        assert np.abs(got[:, rows] - ref[:, rows]).max() <= 4 * 2.0 ** -8 * 1.5 * max(scale[:f + 1]), f
+    assert np.abs(lse.cpu().numpy() - rlse).max() <= 2e-2
+
+
+@pytest.mark.parametrize("dtype,st,kc,n_act", [("bf16", 0, 16, 0), ("bf16", 1, 16, 0), ("bf16", 0, 256, 0), ("f32", 0, 16, 0),
+                                               ("f32", 1, 16, 0), ("bf16", 0, 16, 30), ("bf16", 1, 256, 30), ("f32", 0, 16, 30)])
+def test_slots_past_the_cached_tokens_are_not_used(dtype, st, kc, n_act):
+    """Slots past n_cache that hold anything (here bytes 0xff: NaN scales, ids past the
+    tables) leave the result as it is with zeros there."""
+    H, d, g, r, n, nq = 2, 128, 32, 8, 150, 40
+    gen = torch.Generator(device=DEV).manual_seed(kc + st)
+    cfg = qw.make_config(1, H, d, kc, g, r, 4, 256, dtype, st)
+    R = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(cfg.torch_dtype)  # noqa: E731
+    calib = torch.zeros(qw.quantwm_calib_bytes(cfg), dtype=torch.uint8, device=DEV)
+    u = torch.linalg.qr(torch.randn(H, d, r, generator=gen, device=DEV).cpu())[0].transpose(1, 2).contiguous()
+    qw.quantwm_calib_pack(cfg, R(1, H, kc, d), R(1, H, kc, d), torch.ones(1, H, d, device=DEV),
+                          u.to(DEV, cfg.torch_dtype), torch.ones(1, H, r, device=DEV), calib)
+    k, v, q, ka, va = R(1, n, H, d), R(1, n, H, d), R(1, nq, H, d), R(1, 30, H, d), R(1, 30, H, d)
+    got = []
+    for fill in (0, 255):
+        cache = torch.full((qw.quantwm_cache_bytes(cfg),), fill, dtype=torch.uint8, device=DEV)
+        qw.quantwm_append(cfg, calib, cache, 0, k, v, n)
+        out, lse = torch.full_like(q, 7.0), torch.empty((1, H, nq), dtype=torch.float32, device=DEV)
+        if n_act:
+            qw.quantwm_attend_active(cfg, calib, cache, n, ka, va, n_act, q, nq, n, 10, out, lse)
+        else:
+            qw.quantwm_attend(cfg, calib, cache, n, q, nq, n - nq, 10, out, lse)
+        got.append((out, lse))
+    assert torch.isfinite(got[0][0].float()).all()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
