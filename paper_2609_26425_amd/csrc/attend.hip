@@ -712,7 +712,12 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   float m_run = -__builtin_inff(), l_run = 0.0f;
   f32x16 oacc[D / 32];
   int lim = int(nc);
-  int ev = 0;  // O is held times 2^-ev (the binary16 Value table's scale)
+  // O is held times 2^-ev, the binary16 Value table's scale. Between segments O moves
+  // from one scale to the next; in the streaming forms ev stays within +-kMaxShift, so
+  // that this neither overflows nor loses bits, and the rest of a table's exponent
+  // goes to the segment's probabilities (and so to its part of the sum) as 2^psh.
+  constexpr int kMaxShift = 32;
+  int ev = 0, psh = 0;
   // Query fragment (B operand: k = channel, column = Query) and q U_r for epoch e;
   // act: the active chunk, whose keys are unscaled and carry no PSAC term
   auto begin_queries = [&](int e, bool act, bool first) __attribute__((always_inline)) {
@@ -725,6 +730,12 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
     int ek, en;
     table_exps(e, ek, en);
     if (GEN && act) ek = en = 0;
+    if constexpr (GEN && H16) {
+      const int sh = en - min(max(en, -kMaxShift), kMaxShift);
+      en -= sh;
+      l_run = ldexpf(l_run, sh - psh);
+      psh = sh;
+    }
     if constexpr (RP > 0) {
       if (GEN && act) {
 #pragma unroll
@@ -953,7 +964,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         }
       };
       auto probs = [&](f32x16& sv) {
-        const float mc = m_run == -__builtin_inff() ? 0.0f : -m_run * mscale;
+        const float mc = (m_run == -__builtin_inff() ? 0.0f : -m_run * mscale) + (GEN && H16 ? float(psh) : 0.0f);
 #pragma unroll
         for (int i = 0; i < 16; ++i) sv[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[i], mscale, mc));
         if constexpr (KPL == 1) {
@@ -1028,6 +1039,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   });
 
   if constexpr (!LOGITS) {
+    if constexpr (GEN && H16) l_run = ldexpf(l_run, -psh);
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (a.n_split > 1) {
       // partial result of this split: unnormalised O, the running max (raw logit
