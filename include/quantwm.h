@@ -259,8 +259,8 @@ size_t quantwm_attend_workspace_bytes(const quantwm_config* cfg, int64_t n_cache
  * n_q == 0 is a no-op. Keys and Values are dequantised in registers; the cache
  * is only ever read in packed form. workspace: optional device scratch of
  * workspace_bytes, 256-byte aligned, owned by the caller and not read back (NULL
- * means no split, fewer bytes than quantwm_attend_workspace_bytes() as many parts
- * as they hold). Calls
+ * means no split, fewer bytes than quantwm_attend_workspace_bytes() the cheapest
+ * number of parts that they hold, none included). Calls
  * that share a workspace must be ordered on one stream. QWM_ERR_UNSUPPORTED
  * when n_q or the key count (n_cache, plus n_act for the active-chunk forms)
  * exceeds 0x7fff0000 per head. */
@@ -279,8 +279,8 @@ quantwm_status quantwm_attend(const quantwm_config* cfg, const void* calib, cons
  * packed keys, then the exact ones, with one softmax state. The workspace
  * serves the key split as in quantwm_attend:
  * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q) bytes (256-byte
- * aligned) or more let a small launch split, fewer into as many parts as they
- * hold, NULL not at all, with the same result up to fp32 rounding order. */
+ * aligned) or more let a small launch split, fewer into the cheapest number of
+ * parts that they hold, NULL not at all, with the same result up to fp32 rounding order. */
 quantwm_status quantwm_attend_active(const quantwm_config* cfg, const void* calib, const void* cache,
                                      int64_t n_cache, const void* k_act, const void* v_act, int64_t n_act,
                                      const void* q, int64_t n_q, int64_t q_start, int32_t frame_tokens,

@@ -480,13 +480,12 @@ size_t quantwm_attend_active_workspace_bytes(const quantwm_config* cfg, int64_t 
   return two > split ? two : split;
 }
 
-// split_cap > 0 limits the key split of the plain form to that many parts.
 static quantwm_status attend_common(const quantwm_config* cfg, const void* calib, int32_t n_epochs,
                                     const int64_t* epoch_start, const void* cache, int64_t n_cache,
                                     const void* k_act, const void* v_act, int64_t n_act, const void* q, int64_t n_q,
                                     int64_t q_start, int32_t frame_tokens, void* out, float* lse_out,
                                     float* logits_out, void* workspace, size_t workspace_bytes, void* stream,
-                                    int split_cap = 0, int64_t q_first = 0) {
+                                    int64_t q_first = 0) {
   QWM_TRY(check_cfg(cfg));
   if (n_epochs < 1 || n_epochs > qwm::kMaxEpochs) return fail(QWM_ERR_UNSUPPORTED, "n_epochs must be in [1, 64]");
   if (n_epochs > 1) {
@@ -546,14 +545,10 @@ static quantwm_status attend_common(const quantwm_config* cfg, const void* calib
   a.part_ml = nullptr;
   if (!logits_out && workspace) {
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return fail(QWM_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
-    int ns = 1;
-    size_t need = attend_split_bytes(cfg, n_cache + n_act, n_q, &ns);
-    if (split_cap > 0 && ns > split_cap) {
-      ns = split_cap;
-      need = planes_bytes(cfg, ns, n_q);
-    }
-    // a smaller workspace gets as many parts as it holds
-    while (ns > 1 && workspace_bytes < need) need = planes_bytes(cfg, --ns, n_q);
+    // the cheapest number of parts that the workspace holds
+    int most = 1;
+    while (most < qwm::kMaxSplits && planes_bytes(cfg, most + 1, n_q) <= workspace_bytes) ++most;
+    const int ns = qwm::attend_splits(n_q, cfg->heads, cfg->batch, n_cache + n_act, device_cus(), elem, most);
     if (ns > 1) {
       const size_t rows = size_t(ns) * cfg->batch * cfg->heads * size_t(n_q);
       a.n_split = ns;
@@ -603,13 +598,12 @@ quantwm_status quantwm_attend_noalloc(const quantwm_config* cfg, const void* cal
                                       int32_t frame_tokens, void* out, float* lse_out, void* stream) {
   QWM_TRY(check_cfg(cfg));
   if (n_cache < 0 || n_q < 0) return fail(QWM_ERR_INVALID_ARG, "sizes must be >= 0");
-  // the key split quantwm_attend would take, cut to what the static buffer holds
+  // the key split quantwm_attend would take with the static buffer as its workspace
   int ns = 1;
   if (n_q > 0) (void)attend_split_bytes(cfg, n_cache, n_q, &ns);
   void* scratch = nullptr;
   if (ns > 1) {
-    while (ns > 1 && planes_bytes(cfg, ns, n_q) > QWM_ATTEND_NOALLOC_SCRATCH_BYTES) --ns;
-    if (ns < 2)
+    if (planes_bytes(cfg, 2, n_q) > QWM_ATTEND_NOALLOC_SCRATCH_BYTES)
       return fail(QWM_ERR_CAPACITY,
                   "the key split of this call needs %zu bytes of scratch for two parts; the static buffer of "
                   "quantwm_attend_noalloc holds %zu (quantwm_attend with a workspace takes any size)",
@@ -617,8 +611,7 @@ quantwm_status quantwm_attend_noalloc(const quantwm_config* cfg, const void* cal
     QWM_TRY(noalloc_scratch(&scratch));
   }
   return attend_common(cfg, calib, 1, nullptr, cache, n_cache, nullptr, nullptr, 0, q, n_q, q_start, frame_tokens,
-                       out, lse_out, nullptr, scratch, scratch ? size_t(QWM_ATTEND_NOALLOC_SCRATCH_BYTES) : 0, stream,
-                       ns);
+                       out, lse_out, nullptr, scratch, scratch ? size_t(QWM_ATTEND_NOALLOC_SCRATCH_BYTES) : 0, stream);
 }
 
 quantwm_status quantwm_coef_pool_usage(const quantwm_config* cfg, const void* cache, int64_t n_cache,
@@ -667,7 +660,7 @@ quantwm_status quantwm_logits(const quantwm_config* cfg, const void* calib, cons
   if (q_first < 0 || q_first > kMaxPositions - (n_q > 0 ? n_q : 0))
     return fail(QWM_ERR_INVALID_ARG, "need 0 <= q_first and q_first + n_q <= %lld", (long long)kMaxPositions);
   return attend_common(cfg, calib, 1, nullptr, cache, n_cache, nullptr, nullptr, 0, q, n_q, q_start, frame_tokens,
-                       nullptr, nullptr, logits_out, nullptr, 0, stream, 0, q_first);
+                       nullptr, nullptr, logits_out, nullptr, 0, stream, q_first);
 }
 
 }  // extern "C"

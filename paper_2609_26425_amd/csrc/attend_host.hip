@@ -77,12 +77,13 @@ size_t attend_lds_bytes(int d, int elem, int rank, int n_centroids, bool tables)
   return d == 64 ? attend_lds_bytes_t<float, 64>(rank, n_centroids, tables)
                  : attend_lds_bytes_t<float, 128>(rank, n_centroids, tables);
 }
-int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus, int elem) {
+int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus, int elem, int most) {
   // Split the key range only when the launch gives fewer than two workgroups
   // per compute unit (one runs per CU). The split count minimises the rounds of
   // workgroups times each one's work: its share of the key tiles plus a fixed
   // cost of about 32 tiles (table staging, Query fragments, pipeline fill,
-  // partial write), up to 16 splits of at least 8 tiles; 4 while all the
+  // partial write), up to `most` (16, or what a smaller workspace holds: with fewer
+  // parts than wanted no split may be the cheapest) splits of at least 8 tiles; 4 while all the
   // workgroups still run at once, where a split only uses idle CUs (4 heads, 64
   // Queries, 704 keys at d = 128: 29 us in one part, 20.5 us in two; 16 heads, 300
   // Queries, 2,000 keys: 53 us with 3 splits, 35 us with 7, each with the faster
@@ -96,7 +97,7 @@ int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus, i
   const int64_t tiles = (n_cache + KT - 1) / KT;
   int best = 1;
   int64_t best_cost = -1;
-  for (int ns = 1; ns <= 16; ++ns) {
+  for (int ns = 1; ns <= most; ++ns) {
     const int least = elem == 4 ? 1 : (wgs * ns <= cus ? 4 : 8);
     if (ns > 1 && tiles / ns < least) break;
     const int64_t rounds = (wgs * ns + cus - 1) / cus;

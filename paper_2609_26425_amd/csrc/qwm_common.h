@@ -167,7 +167,8 @@ hipError_t launch_append_bf16(const AppendArgs& a, int batch, hipStream_t s);
 hipError_t launch_attend_f32(const AttendArgs& a, int d, int batch, bool logits, hipStream_t s);
 hipError_t launch_attend_bf16(const AttendArgs& a, int d, int batch, bool logits, hipStream_t s);
 size_t attend_lds_bytes(int d, int elem, int rank, int n_centroids, bool tables_in_lds);
-int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus, int elem);
+constexpr int kMaxSplits = 16;
+int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus, int elem, int most = kMaxSplits);
 bool attend_tables_fit(int d, int elem, int rank, int n_centroids);
 
 hipError_t launch_derive_constants(const quantwm_config& c, uint8_t* calib, hipStream_t s);

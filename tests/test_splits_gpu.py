@@ -11,10 +11,9 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("dtype,d,n,nq", [("bf16", 128, 1400, 64), ("bf16", 64, 515, 33), ("f32", 64, 1000, 70),
-                                          ("f32", 128, 130, 300)])
-def test_splits_match_the_unsplit_call(dtype, d, n, nq):
-    H, kc, r, frame = 2, 24, 8, 16
+def _call(dtype, d, n, nq, H):
+    """A seeded call: attend(workspace bytes) -> (out, lse), planes(parts) -> bytes, config."""
+    kc, r, frame = 24, 8, 16
     g = torch.Generator(device=DEV).manual_seed(n)
     cfg = qw.make_config(1, H, d, kc, 32, r, 4, n, dtype)
     dt = cfg.torch_dtype
@@ -35,7 +34,13 @@ def test_splits_match_the_unsplit_call(dtype, d, n, nq):
 
     def planes(ns):
         return (ns * H * nq * d * 4 + 255) // 256 * 256 + ns * H * nq * 8
+    return attend, planes, cfg
 
+
+@pytest.mark.parametrize("dtype,d,n,nq", [("bf16", 128, 1400, 64), ("bf16", 64, 515, 33), ("f32", 64, 1000, 70),
+                                          ("f32", 128, 130, 300)])
+def test_splits_match_the_unsplit_call(dtype, d, n, nq):
+    attend, planes, cfg = _call(dtype, d, n, nq, 2)
     full = qw.quantwm_attend_workspace_bytes(cfg, n, nq)
     parts = next(ns for ns in range(2, 17) if planes(ns) == full)
     tiles = (n + 63) // 64
@@ -48,5 +53,17 @@ def test_splits_match_the_unsplit_call(dtype, d, n, nq):
         out, lse = attend(nb)
         assert np.abs(out - ref).max() <= tol * np.abs(ref).max(), nb
         assert np.abs(lse - rlse).max() <= (2e-3 if dtype == "bf16" else 1e-5) * (1 + np.abs(rlse).max()), nb
-    if planes(2) - 1 < planes(2):  # one byte short of two parts: the unsplit launch, bit for bit
-        assert np.array_equal(attend(planes(2) - 1)[0], ref)
+    # one byte short of two parts: the unsplit launch, bit for bit
+    assert np.array_equal(attend(planes(2) - 1)[0], ref)
+
+
+def test_a_workspace_for_fewer_parts_takes_the_cheapest_count_that_fits():
+    """33 heads x 5 Query blocks over 128 key tiles want three parts (2 rounds of
+    workgroups over 43 + 32 tiles against one over 128 + 32); two parts (2 rounds over
+    64 + 32) would take longer than none, so a workspace for two runs unsplit."""
+    attend, planes, cfg = _call("bf16", 64, 8192, 1280, 33)
+    assert qw.quantwm_attend_workspace_bytes(cfg, 8192, 1280) == planes(3)
+    ref, rlse = attend(0)
+    out, lse = attend(planes(3) - 1)
+    assert np.array_equal(out, ref) and np.array_equal(lse, rlse)
+    assert not np.array_equal(attend(planes(3))[1], rlse)
