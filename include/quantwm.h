@@ -287,11 +287,9 @@ quantwm_status quantwm_attend_active(const quantwm_config* cfg, const void* cali
                                      void* out, float* lse_out, void* workspace, size_t workspace_bytes,
                                      void* stream);
 
-/* A workspace size that covers quantwm_attend_active: the larger of fp32 partial
- * planes for the packed keys and the active chunk apart (none without an active
- * chunk or with fewer than 64 packed keys) and the split workspace of
- * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q). The call itself
- * uses the latter only. */
+/* Workspace bytes of quantwm_attend_active's key split:
+ * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q). 0 where the launch
+ * does not split. */
 size_t quantwm_attend_active_workspace_bytes(const quantwm_config* cfg, int64_t n_cache, int64_t n_act,
                                              int64_t n_q);
 
@@ -310,12 +308,9 @@ quantwm_status quantwm_attend_epochs(const quantwm_config* cfg, const void* cali
                                      int64_t n_q, int64_t q_start, int32_t frame_tokens, void* out,
                                      float* lse_out, void* workspace, size_t workspace_bytes, void* stream);
 
-/* A workspace size that covers quantwm_attend_epochs (n_epochs >= 2; 0
- * otherwise): the larger of an fp32 partial plane (or its key splits) per
- * epoch, one more for an active chunk, and the split workspace of
- * quantwm_attend_workspace_bytes(cfg, n_cache + n_act, n_q). epoch_start is the
- * host array of the call. The call runs every epoch in one launch and uses the
- * split workspace only, as quantwm_attend_active does. */
+/* Workspace bytes of quantwm_attend_epochs' key split, as for
+ * quantwm_attend_active (0 for n_epochs outside [2, 64] or a null epoch_start, the
+ * host array of the call). */
 size_t quantwm_attend_epochs_workspace_bytes(const quantwm_config* cfg, int32_t n_epochs,
                                              const int64_t* epoch_start, int64_t n_cache, int64_t n_act,
                                              int64_t n_q);

@@ -449,35 +449,18 @@ static size_t planes_bytes(const quantwm_config* cfg, int planes, int64_t n_q) {
   return (rows * cfg->head_dim * 4 + 255) / 256 * 256 + rows * 2 * 4;
 }
 
-// The streaming calls split their key range like quantwm_attend and need no
-// more than its workspace. Their size queries answer with what a plane per
-// calibration epoch (or for the packed keys and the active chunk) takes, the
-// size that callers have always been told.
+// The streaming calls split their key range as quantwm_attend does over all their keys.
 size_t quantwm_attend_epochs_workspace_bytes(const quantwm_config* cfg, int32_t n_epochs, const int64_t* epoch_start,
                                              int64_t n_cache, int64_t n_act, int64_t n_q) {
   if (check_cfg(cfg) != QWM_OK || n_cache < 0 || n_act < 0 || n_q <= 0) return 0;
   if (n_epochs < 2 || n_epochs > qwm::kMaxEpochs || !epoch_start) return 0;
-  const int64_t kt = qwm::kAttendTileKeys, end = n_act > 0 ? n_cache / kt * kt : n_cache;
-  int planes = n_act > 0 ? 1 : 0;
-  for (int e = 0; e < n_epochs; ++e) {
-    const int64_t hi0 = e + 1 < n_epochs ? epoch_start[e + 1] : n_cache, hi = hi0 < end ? hi0 : end;
-    if (hi > epoch_start[e])
-      planes += qwm::attend_splits(n_q, cfg->heads, cfg->batch, hi - epoch_start[e], device_cus(), qwm::elem_bytes(*cfg));
-  }
-  const size_t per = planes_bytes(cfg, planes, n_q);
-  const size_t split = attend_split_bytes(cfg, n_cache + n_act, n_q, nullptr);
-  return per > split ? per : split;
+  return attend_split_bytes(cfg, n_cache + n_act, n_q, nullptr);
 }
 
 size_t quantwm_attend_active_workspace_bytes(const quantwm_config* cfg, int64_t n_cache, int64_t n_act,
                                              int64_t n_q) {
   if (check_cfg(cfg) != QWM_OK || n_cache < 0 || n_act < 0 || n_q <= 0) return 0;
-  const int64_t whole = n_cache / qwm::kAttendTileKeys * qwm::kAttendTileKeys;
-  const size_t two = whole == 0 || n_act == 0
-                         ? 0
-                         : planes_bytes(cfg, qwm::attend_splits(n_q, cfg->heads, cfg->batch, whole, device_cus(), qwm::elem_bytes(*cfg)) + 1, n_q);
-  const size_t split = attend_split_bytes(cfg, n_cache + n_act, n_q, nullptr);
-  return two > split ? two : split;
+  return attend_split_bytes(cfg, n_cache + n_act, n_q, nullptr);
 }
 
 static quantwm_status attend_common(const quantwm_config* cfg, const void* calib, int32_t n_epochs,

@@ -106,9 +106,8 @@ def _run_epochs(wl, starts, n_act, rows, seed_hist=300):
                                     v_act=np.ascontiguousarray(v[:, n_pk:]) if n_act else None,
                                     epochs=list(zip(starts, tables)))
     tol = 2e-2 if wl.dtype == "bf16" else 1e-4
-    for mode in ("none", "split", "per-epoch"):
-        nb = {"none": 0, "split": qw.quantwm_attend_workspace_bytes(cfg, wl.n_cache, wl.n_q),
-              "per-epoch": qw.quantwm_attend_epochs_workspace_bytes(cfg, list(starts), n_pk, n_act, wl.n_q)}[mode]
+    for mode in ("none", "split"):
+        nb = {"none": 0, "split": qw.quantwm_attend_epochs_workspace_bytes(cfg, list(starts), n_pk, n_act, wl.n_q)}[mode]
         if mode != "none" and nb == 0:
             continue
         ws = torch.empty(nb, dtype=torch.uint8, device=DEV) if nb else None
