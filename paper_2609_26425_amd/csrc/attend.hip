@@ -964,7 +964,7 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         }
       };
       auto probs = [&](f32x16& sv) {
-        const float mc = (m_run == -__builtin_inff() ? 0.0f : -m_run * mscale) + (GEN && H16 ? float(psh) : 0.0f);
+        const float mc = m_run == -__builtin_inff() ? 0.0f : __builtin_fmaf(-m_run, mscale, GEN && H16 ? float(psh) : 0.0f);
 #pragma unroll
         for (int i = 0; i < 16; ++i) sv[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[i], mscale, mc));
         if constexpr (KPL == 1) {
