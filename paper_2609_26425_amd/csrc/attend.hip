@@ -277,7 +277,8 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   // the wave index is uniform across a wave: taken through readfirstlane, the
   // producer/consumer split is a scalar branch, so neither role keeps the
   // other's registers live
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64, l32 = lane % 32,
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64),
+            lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), tid = wave * 64 + lane, l32 = lane % 32,
             hf = lane / 32;
   // XCD-aware task order: workgroup L runs on XCD L % 8, so each XCD takes a
   // contiguous run of (Query block, head, batch) tasks, and the Query blocks
@@ -317,7 +318,6 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   const int64_t qoff = LOGITS ? a.q_row0 : 0;
   int64_t kfull = qs + ((qa + qoff) / F + 1) * F;  // keys below are visible to every Query of the workgroup
   if (kfull > nc) kfull = nc;
-  const int n_seg = GEN ? a.n_epochs + (a.n_act > 0 ? 1 : 0) : 1;
   auto segment = [&](int i) {
     Segment g{0, kend, 0, (kend + KT - 1) / KT, 0, false};
     if constexpr (GEN) {
@@ -331,21 +331,50 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
     }
     return g;
   };
+  // tiles of all segments; with several epochs a lane of the wave counts for each
+  // (kMaxEpochs is the wave's size): one load, where a loop over them, here and up to
+  // the workgroup's first segment, waits for one after the other (2 heads x 60
+  // Queries, 12,000 keys in 40 epochs, sparse rows, d = 64: 66 us so, 40 us now)
+  static_assert(kMaxEpochs == 64, "a lane per epoch");
   int64_t v_all = 0;
-  for (int i = 0; i < n_seg; ++i) v_all += segment(i).tiles;
+  int past = 0;  // lane's epoch: tiles up to its end
+  if (!GEN || a.n_epochs == 1) {
+    v_all = segment(0).tiles;
+  } else {
+    // counted anew rather than kept in a register from the kernel's start
+    const int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    past = l < a.n_epochs ? int(segment(l).tiles) : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(past, o);
+      past += l >= o ? y : 0;
+    }
+    v_all = __builtin_amdgcn_readlane(past, 63);
+  }
+  const int64_t v_packed = v_all;
+  if (GEN && a.n_act > 0) v_all += segment(a.n_epochs).tiles;
   const int64_t per_split = (v_all + a.n_split - 1) / a.n_split;
   const int64_t v0 = split * per_split < v_all ? split * per_split : v_all;
   const int64_t v1 = v0 + per_split < v_all ? v0 + per_split : v_all;  // this split: tiles [v0, v1)
+  // the segment of tile v0, and the tiles before it
+  int seg0 = 0;
+  int64_t before = 0;
+  if constexpr (GEN) {
+    const uint64_t at = a.n_epochs == 1 ? uint64_t(v0 < v_packed) : __ballot(past > v0);
+    seg0 = at ? __builtin_ctzll(at) : a.n_epochs;
+    before = !at ? v_packed : (seg0 > 0 ? __builtin_amdgcn_readlane(past, seg0 - 1) : 0);
+  }
   // calls f(segment, first tile, end tile, buffer parity of tile 0, first of the
   // workgroup) for every segment with tiles of this split; tile t sits in
-  // buffer (t + parity) & 1, alternating across segments
+  // buffer (t + parity) & 1, alternating across segments. (Epochs past kend, which
+  // have no tiles, come last.)
   auto each_segment = [&](auto&& f) __attribute__((always_inline)) {
     if constexpr (!GEN) {
       f(segment(0), v0, v1, 0, true);
     } else {
-      int64_t vb = 0;
+      int64_t vb = before;
       int done = 0;
-      for (int i = 0; i < n_seg; ++i) {
+      for (int i = seg0; vb < v1; ++i) {
         const Segment g = segment(i);
         const int64_t ta = v0 > vb ? v0 - vb : 0, te = v1 - vb < g.tiles ? v1 - vb : g.tiles;
         vb += g.tiles;
@@ -506,18 +535,30 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
       }
     }
     if constexpr (RP > 0) {
-      if (sparse && crole) {
+      if (sparse) {
         // the key's row through the directory entry of its 64-key tile: present
-        // iff its mask bit is set, at pool row base + (set bits below it)
+        // iff its mask bit is set, at pool row base + (set bits below it). An absent
+        // row reads as 0, past the end of the pool's resource (at most 2^31 bytes), so
+        // that no branch waits for the entry and other loads stay in flight.
+        constexpr uint32_t kAbsent = 0xC0000000u;
         const uint32_t* e = dir + (k0 / 64) * 4;
         const uint64_t m = uint64_t(e[2]) | (uint64_t(e[3]) << 32);
-        if ((m >> ckey) & 1) {
-          const int row = int(e[0]) + __popcll(m & ((uint64_t(1) << ckey) - 1));
-          csb = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r_ps, row * 2, 0, 0));
+        const bool has = crole && ((m >> ckey) & 1);
+        const uint32_t row = e[0] + uint32_t(__popcll(m & ((uint64_t(1) << ckey) - 1)));
+        const uint32_t at = has ? row * uint32_t(r) + uint32_t(cr0) : kAbsent;
+        csb = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r_ps, int(has ? row * 2 : kAbsent), 0, 0));
+        if (raligned) {
+          if constexpr (RCH == 8) {
+            const auto u = __builtin_amdgcn_raw_buffer_load_b64(r_pc, int(at), 0, 0);
+            cw2[0] = u[0];
+            cw2[1] = u[1];
+          } else {
+            cw2[0] = __builtin_amdgcn_raw_buffer_load_b32(r_pc, int(at), 0, 0);
+          }
+        } else {
 #pragma unroll
           for (int k = 0; k < RCH; ++k)
-            if (cr0 + k < r)
-              cw2[k / 4] |= uint32_t(__builtin_amdgcn_raw_buffer_load_b8(r_pc, row * r + cr0 + k, 0, 0)) << (8 * (k % 4));
+            cw2[k / 4] |= uint32_t(__builtin_amdgcn_raw_buffer_load_b8(r_pc, int(cr0 + k < r ? at + k : kAbsent), 0, 0)) << (8 * (k % 4));
         }
       } else if (crole) {
         csb = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r_cs, o_cs, k0i * 2, 0));
@@ -731,6 +772,8 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
     table_exps(e, ek, en);
     if (GEN && act) ek = en = 0;
     if constexpr (GEN && H16) {
+      ek = __builtin_amdgcn_readfirstlane(ek);  // of the head: kept scalar
+      en = __builtin_amdgcn_readfirstlane(en);
       const int sh = en - min(max(en, -kMaxShift), kMaxShift);
       en -= sh;
       l_run = ldexpf(l_run, sh - psh);
@@ -795,8 +838,11 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
         }
         return;
       }
-      // Value scales (SI8: secondary scales) of the segment's keys, 0 past them
-      const auto r_v = SI8 ? field_to(L.v_sigma, 2, GEN ? g.hi : npk) : field_to(L.v_scale, sstride, GEN ? g.hi : npk);
+      // Value scales (SI8: secondary scales) of a segment's keys, 0 past them
+      auto scales = [&](const Segment& s) {
+        return SI8 ? field_to(L.v_sigma, 2, GEN ? s.hi : npk) : field_to(L.v_scale, sstride, GEN ? s.hi : npk);
+      };
+      const auto r_v = scales(g);
       auto prefetch = [&](TileRegs<NSUB>& p, int64_t t) __attribute__((always_inline)) {
         load_raw(p, uint32_t(g.base + t * KT), AnyRows{}, r_v, int(g.lo));
       };

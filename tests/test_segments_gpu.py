@@ -35,6 +35,8 @@ CASES = {
     "rank-0": ([0, 70], 200, 90, 0, 128, 16, 0, 32, 50, "bf16"),
     "f32": ([0, 100, 500], 1090, 129, 0, 64, 16, 4, 32, 50, "f32"),
     "f32-128": ([0, 77], 200, 65, 1, 128, 16, 32, 32, 50, "f32"),
+    "64-epochs": ([70 * i for i in range(64)], 4500, 65, 0, 64, 8, 4, 16, 50, "bf16"),
+    "64-epochs-f32": ([64 * i for i in range(64)], 4160, 0, 1, 64, 8, 4, 16, 50, "f32"),
 }
 
 
@@ -162,3 +164,41 @@ def test_slots_past_the_cached_tokens_are_not_used(dtype, st, kc, n_act):
         got.append((out, lse))
     assert torch.isfinite(got[0][0].float()).all()
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("d,r,dtype", [(64, 4, "bf16"), (128, 6, "bf16"), (128, 16, "bf16"), (128, 32, "bf16"), (64, 13, "f32")])
+def test_epochs_over_sparse_rows(d, r, dtype):
+    """The same tokens appended with sparse and with slot-addressed PSAC rows give the
+    same bits: rows of whole words and of single bytes, present and absent, over
+    epochs and an exact chunk, split and not."""
+    H, kc, g, n, nq, starts = 3, 16, 32, 1200, 70, [0, 90, 500, 800]
+    gen = torch.Generator(device=DEV).manual_seed(d + r)
+    cfgs = [qw.make_config(1, H, d, kc, g, r, 4, n, dtype, st, coef_stage=n) for st in (0, 4)]
+    R = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(cfgs[0].torch_dtype)  # noqa: E731
+    cb = qw.quantwm_calib_bytes(cfgs[0])
+    calibs = torch.zeros(cb * len(starts), dtype=torch.uint8, device=DEV)
+    for e in range(len(starts)):
+        u = torch.linalg.qr(torch.randn(H, d, r, generator=gen, device=DEV).cpu())[0].transpose(1, 2).contiguous()
+        mu = R(1, H, kc, d)
+        qw.quantwm_calib_pack(cfgs[0], mu, R(1, H, kc, d), torch.ones(1, H, d, device=DEV), u.to(DEV, mu.dtype),
+                              torch.ones(1, H, r, device=DEV), calibs[e * cb:(e + 1) * cb])
+        if e == 0:
+            mu0 = mu
+    k, v, q, ka, va = R(1, n, H, d), R(1, n, H, d), R(1, nq, H, d), R(1, 50, H, d), R(1, 50, H, d)
+    k[:, 5:85:2] = mu0[:, :, 3][:, None]  # no residual: these rows have scale 0 and are absent
+    got = []
+    for cfg in cfgs:
+        cache = torch.zeros(qw.quantwm_cache_bytes(cfg), dtype=torch.uint8, device=DEV)
+        for e, s0 in enumerate(starts):
+            m = (starts + [n])[e + 1] - s0
+            qw.quantwm_append(cfg, calibs[e * cb:(e + 1) * cb], cache, s0, k[:, s0:s0 + m].contiguous(),
+                              v[:, s0:s0 + m].contiguous(), m)
+        for nb in (0, qw.quantwm_attend_epochs_workspace_bytes(cfg, starts, n, 50, nq)):
+            ws = torch.empty(nb, dtype=torch.uint8, device=DEV) if nb else None
+            out, lse = torch.full_like(q, 7.0), torch.empty((1, H, nq), dtype=torch.float32, device=DEV)
+            qw.quantwm_attend_epochs(cfg, calibs, starts, cache, n, ka, va, 50, q, nq, n - 20, 10, out, lse, ws)
+            got.append((out, lse))
+    used, dropped = qw.quantwm_coef_pool_usage(cfgs[1], cache, n)
+    assert dropped == 0 and 0 < used < H * n
+    for i in range(2):
+        assert torch.equal(got[i][0], got[2 + i][0]) and torch.equal(got[i][1], got[2 + i][1]), i
