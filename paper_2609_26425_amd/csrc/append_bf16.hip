@@ -68,9 +68,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kWaveTokens = 32;
 
 // Waves per workgroup for up to NB blocks of 32 centroids. Every Key distance stays
-// in registers through the selection (16 per block and lane): four blocks leave
-// three waves per SIMD, and two workgroups of six waves share a CU's LDS at 128
-// centroids and d = 128; eight blocks leave two waves per SIMD and one workgroup.
+// in registers through the selection (16 per block and lane), which leaves two waves
+// per SIMD. Up to four blocks two workgroups of four waves share a CU (80 KB of LDS
+// each at 128 centroids and d = 128); with eight blocks the tables leave room for one
+// workgroup, of eight waves.
 template <int NB>
 constexpr int kMaxWaves = NB <= 4 ? 4 : 8;
 
@@ -873,7 +874,10 @@ hipError_t launch_one(const AppendArgs& a, int batch, hipStream_t s) {
 
 template <int D, int G, int RP, bool SI8>
 hipError_t launch_rank(const AppendArgs& a, int batch, hipStream_t s) {
-  if (a.top_m > 4) return launch_one<D, G, RP, 8, 8, SI8>(a, batch, s);
+  // four blocks of 32 centroids for up to 128 whatever the candidate count: smaller
+  // workgroups (120 heads x 600 tokens, 16 centroids, M = 8, d = 64: 32.5 us with the
+  // eight-block instance, 21.7 us so)
+  if (a.top_m > 4) return a.n_centroids > 128 ? launch_one<D, G, RP, 8, 8, SI8>(a, batch, s) : launch_one<D, G, RP, 8, 4, SI8>(a, batch, s);
   return a.n_centroids > 128 ? launch_one<D, G, RP, 4, 8, SI8>(a, batch, s) : launch_one<D, G, RP, 4, 4, SI8>(a, batch, s);
 }
 
