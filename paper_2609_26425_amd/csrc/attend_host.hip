@@ -82,15 +82,19 @@ int attend_splits(int64_t n_q, int heads, int batch, int64_t n_cache, int cus, i
   // per compute unit (one runs per CU). The split count minimises the rounds of
   // workgroups times each one's work: its share of the key tiles plus a fixed
   // cost of about 32 tiles (table staging, Query fragments, pipeline fill,
-  // partial write), up to `most` (16, or what a smaller workspace holds: with fewer
-  // parts than wanted no split may be the cheapest) splits of at least 8 tiles; 4 while all the
-  // workgroups still run at once, where a split only uses idle CUs (4 heads, 64
-  // Queries, 704 keys at d = 128: 29 us in one part, 20.5 us in two; 16 heads, 300
-  // Queries, 2,000 keys: 53 us with 3 splits, 35 us with 7, each with the faster
-  // start of the kernel). fp32 tiles take about eight times as long (matrix cores
-  // at 1/16 of the BF16 rate), so the fixed cost is 2 of them and a split may be a
-  // single tile (2 heads, 256 Queries, 1,024 keys at d = 64: 92 us with 2 splits,
-  // 33 us with 16).
+  // partial write). It goes up to `most`: 16, or what a smaller workspace holds
+  // (with fewer parts than wanted no split may be the cheapest). A split has at
+  // least 8 tiles; 4 while all the workgroups still run at once, where a split
+  // only uses idle CUs (4 heads, 64 Queries, 704 keys at d = 128: 29 us in one
+  // part, 20.5 us in two; 16 heads, 300 Queries, 2,000 keys: 53 us with 3 splits,
+  // 35 us with 7, each with the faster start of the kernel). An fp32 tile (matrix
+  // cores at 1/16 of the BF16 rate, scalar operand reads) takes 8.5 us for 256
+  // Queries at d = 64 and 17 us at d = 128, and a workgroup 25 and 38 us besides:
+  // the fixed cost is 2 tiles, and a split may be a single one (2 heads, 256
+  // Queries, 1,024 keys, with 2, 8 and 16 splits: 92, 40 and 34 us at d = 64, 173,
+  // 69 and 55 us at d = 128). Of the counts tried on each of 64 shapes from 2 x 64
+  // Queries x 256 keys to 40 x 600 x 1,024 and 8 x 600 x 4,096 at both head
+  // dimensions, the one picked here was the fastest every time.
   const int fixed = elem == 4 ? 2 : 32;
   const int64_t wgs = (n_q + BQ - 1) / BQ * heads * batch;
   if (wgs <= 0 || wgs >= 2 * int64_t(cus)) return 1;
