@@ -277,8 +277,12 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   // the wave index is uniform across a wave: taken through readfirstlane, the
   // producer/consumer split is a scalar branch, so neither role keeps the
   // other's registers live
+  // BF16: the lane from the lane mask, not from a thread id kept (or spilled) from
+  // the start; in the fp32 instances that spilled more (120 to 270 B a lane at d = 128)
+  constexpr bool MASK_ID = sizeof(T) == 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64),
-            lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), tid = wave * 64 + lane, l32 = lane % 32,
+            lane = MASK_ID ? __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : threadIdx.x % 64,
+            tid = MASK_ID ? wave * 64 + lane : threadIdx.x, l32 = lane % 32,
             hf = lane / 32;
   // XCD-aware task order: workgroup L runs on XCD L % 8, so each XCD takes a
   // contiguous run of (Query block, head, batch) tasks, and the Query blocks
