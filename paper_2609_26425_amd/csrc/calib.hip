@@ -29,8 +29,10 @@ __device__ inline void store_rn(bf16* p, double x) { *p = to_bf16_rn(x); }
 // b_j = sum_c p_jc mu_jc; the k^T Mn k term is the same for every centroid.
 //
 // A block takes kDeriveRows centroids of one head (the first block of a head
-// also its small fields). Latency bounds it (a serial b_j sum per centroid):
-// one block per head took 96 us at 10 heads, 128 centroids and d = 128, these take 31 us.
+// also its small fields). Latency bounds it (a serial b_j sum per centroid).
+// Packing the tables and deriving these, 10 heads, 128 centroids, d = 128: 93 us
+// with one block per head, 47 us with these blocks, 29 us without a branch per
+// channel in the b_j sums (10 heads, 16 centroids, d = 64, fp32: 15, 18 and 9 us).
 constexpr int kDeriveRows = 16;
 template <typename T>
 __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_calib_layout C, int d, int G,
@@ -50,10 +52,10 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
   const float* __restrict__ mm = reinterpret_cast<const float*>(slab + C.m);
 #pragma unroll 8
   for (int i = j0 * d + threadIdx.x; i < j1 * d; i += 256) {
-    const int c = i % d;
+    const int c = i & (d - 1);  // d is 64 or 128
     const float mkv = ldf(mk + i), mvv = ldf(mv + i);
     if (full) {
-      const T* mj = mk + (i / d) * d;
+      const T* mj = mk + (i - c);
       float p = 0.0f;
       for (int c2 = 0; c2 < d; ++c2) p = __builtin_fmaf(mm[c * d + c2], ldf(mj + c2), p);
       ak[i] = -2.0f * p;
@@ -87,12 +89,20 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
     const bool val = threadIdx.x & 1;
     if (j < j1) {
       float acc = 0.0f;
+      const T* __restrict__ mu = (val ? mv : mk) + j * d;
+      if (full) {
+#pragma unroll 8
+        for (int c = 0; c < d; ++c) {
+          const float m = ldf(mu + c), p = -0.5f * ak[j * d + c];  // p_jc exactly
+          acc = __builtin_fmaf(val ? m : p, m, acc);
+        }
+      } else {
+        // every load on both sides: no branch per channel
 #pragma unroll 16
-      for (int c = 0; c < d; ++c) {
-        const float mu = ldf((val ? mv : mk) + j * d + c);
-        // full metric: -0.5 a_jc is p_jc exactly
-        const float p = val ? mu : (full ? -0.5f * ak[j * d + c] : w[c] * mu);
-        acc = __builtin_fmaf(p, mu, acc);
+        for (int c = 0; c < d; ++c) {
+          const float m = ldf(mu + c), wc = w[c];
+          acc = __builtin_fmaf(val ? m : wc * m, m, acc);
+        }
       }
       (val ? bv : bk)[j] = acc;
     }
@@ -107,7 +117,7 @@ __global__ __launch_bounds__(256) void derive_kernel(uint8_t* calib, quantwm_cal
     float* udr = reinterpret_cast<float*>(slab + C.u_dr);
     const int rs = r == 0 ? 0 : (r <= 16 ? 16 : 32);
     for (int i = threadIdx.x; i < rs * d; i += 256) {
-      const int c = i / rs, k = i % rs;
+      const int c = rs == 16 ? i >> 4 : i >> 5, k = i & (rs - 1);
       udr[i] = k < r ? ldf(ut + k * d + c) : 0.0f;
     }
   }
