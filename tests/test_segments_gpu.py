@@ -1,9 +1,10 @@
 """Attention over several segments (calibration epochs, an exact active chunk) in
 one launch, at the sizes where the walk over segments can go wrong: epochs of
 one tile, boundaries inside tiles, active chunks around a tile, no packed key at
-all, key splits that start inside any segment, tables in LDS or not, and epochs
-whose tables differ in magnitude by powers of two (the binary16 copies carry one
-exponent each)."""
+all, key splits that start inside any segment, tables in LDS or not, 64 epochs, and
+epochs whose tables differ in magnitude by powers of two (the binary16 copies carry
+one exponent each). Half the Queries weigh one part only, and every output is
+bounded by the magnitude of the Values that it weighs."""
 import numpy as np
 import pytest
 import torch
@@ -50,24 +51,44 @@ def test_segments(name):
     ocfg = oracle.cfg_of(1, H, d, kc, g, r, 4, max(n_pk, 64), dtype == "bf16", st)
     cfg = qw.make_config(1, H, d, kc, g, r, 4, max(n_pk, 64), dtype, st)
     cache = oracle.new_cache(ocfg)
-    bounds, tables = list(starts) + [n_pk], []
-    vmax = 1.0
+    bounds, tables, khat, vhat = list(starts) + [n_pk], [], [], []
+    mark = 8.0 * np.eye(16, d)  # the Keys of part e (an epoch, the exact chunk) carry row e % 16
     for e in range(len(starts)):
         n = bounds[e + 1] - bounds[e]
         # Keys and Values of this epoch at their own magnitude
         ks, vs = 2.0 ** (-3 * (e % 2)), 2.0 ** (9 * (e % 3) - 9)
-        k, v = _bf(ks * rng.standard_normal((1, max(n, 1), H, d)), dtype), _bf(vs * rng.standard_normal((1, max(n, 1), H, d)), dtype)
-        mu = [_bf(s * rng.standard_normal((1, H, kc, d)), dtype) for s in (ks, vs)]
+        k = _bf(mark[e % 16] + ks * rng.standard_normal((1, max(n, 1), H, d)), dtype)
+        v = _bf(vs * rng.standard_normal((1, max(n, 1), H, d)), dtype)
+        mu = [_bf(m + s * rng.standard_normal((1, H, kc, d)), dtype) for m, s in ((mark[e % 16], ks), (0.0, vs))]
+        if e == 0:  # a component below the resolution of the binary16 copies
+            mu[0][..., 3, 5], mu[1][..., 3, 7] = 2.0 ** -38, -2.0 ** -48
         u = _bf(np.stack([np.linalg.qr(rng.standard_normal((d, d)))[0][:r] for _ in range(H)])[None], dtype)
         t = (mu[0], mu[1], np.ones((1, H, d), np.float32), u, np.ones((1, H, r), np.float32))
         if n:
             oracle.append(ocfg, t, cache, bounds[e], k, v)
-            vmax = max(vmax, 5.0 * vs)
+            dec = [oracle.decode(ocfg, t, cache, 0, h, bounds[e + 1]) for h in range(H)]
+            khat.append(np.stack([x[0][bounds[e]:] for x in dec]))
+            vhat.append(np.stack([x[2][bounds[e]:] for x in dec]))
         tables.append(t)
-    ka, va = (_bf(rng.standard_normal((1, n_act, H, d)), dtype) for _ in range(2)) if n_act else (None, None)
-    q = _bf(rng.standard_normal((1, nq, H, d)), dtype)
-    ref, rlse, _ = oracle.attend(ocfg, tables[0], cache, n_pk, q, q_start, frame, k_act=ka, v_act=va,
-                                 epochs=list(zip(starts, tables)))
+    ka, va = None, None
+    if n_act:
+        ka = _bf(mark[len(starts) % 16] + rng.standard_normal((1, n_act, H, d)), dtype)
+        va = _bf(rng.standard_normal((1, n_act, H, d)), dtype)
+        khat.append(ka[0].transpose(1, 0, 2).astype(np.float64))
+        vhat.append(va[0].transpose(1, 0, 2).astype(np.float64))
+    q = rng.standard_normal((1, nq, H, d))
+    # every other Query puts its weight on the Keys of one part (logits 28 and more
+    # above the others'), whatever the magnitude of that part's Values
+    for i in range(0, nq, 2):
+        q[0, i, :, (i // 2) % min(16, len(starts) + 1)] += 40.0
+    q = _bf(q, dtype)
+    ref, rlse, logits = oracle.attend(ocfg, tables[0], cache, n_pk, q, q_start, frame, want_logits=True, k_act=ka,
+                                      v_act=va, epochs=list(zip(starts, tables)))
+    # sum_j p_j |v_j| of every output, and the largest sum of |q_c k_c| / sqrt(d)
+    khat, vhat = np.concatenate(khat, 1), np.concatenate(vhat, 1)
+    p = np.exp(logits.reshape(H, nq, total) - rlse.reshape(H, nq, 1))
+    mag = np.matmul(p, np.abs(vhat)).transpose(1, 0, 2)[None]
+    qk = max(np.matmul(np.abs(q[0, :, h].astype(np.float64)), np.abs(khat[h]).T).max() for h in range(H)) / np.sqrt(d)
     ref, rlse = ref.reshape(1, H, nq, d).transpose(0, 2, 1, 3), rlse.reshape(1, H, nq)
     dt = cfg.torch_dtype
     T = lambda x, t=dt: torch.from_numpy(np.ascontiguousarray(x)).to(DEV, t)  # noqa: E731
@@ -79,10 +100,13 @@ def test_segments(name):
     dcache, qd = torch.from_numpy(cache).to(DEV), T(q)
     kd, vd = (T(ka), T(va)) if n_act else (None, None)
     split = qw.quantwm_attend_workspace_bytes(cfg, total, nq)
-    # outputs are weighted means of Values up to vmax: BF16 rounds the weights and
-    # the result to 2^-9 each, fp32 sums err by 1e-5 (operand rounding of the
-    # correction adds to the logits: four times the sum of both)
-    tol = vmax * (4 * 2.0 ** -8 if dtype == "bf16" else 1e-4)
+    # A logit errs by its fp32 sum, (d + r + 8) 2^-24 of its terms' magnitudes; in BF16
+    # also by q U_r rounded the other way at a tie (allowed 2^-9). A weight errs by that
+    # and its rounding (2^-9 in BF16), once in O and once in the sum; the fp32 sums over
+    # the keys by n 2^-24, and the result rounds once more.
+    dl = (d + r + 8) * 2.0 ** -24 * qk + (2.0 ** -9 if dtype == "bf16" else 0.0)
+    rel = 2 * (dl + total * 2.0 ** -24) + (3 * 2.0 ** -9 if dtype == "bf16" else 2.0 ** -23)
+    ltol = dl + total * 2.0 ** -24 + (2.0 ** -9 if dtype == "bf16" else 2.0 ** -23 * np.abs(rlse).max())
     for nb in {0, split}:
         ws = torch.empty(nb, dtype=torch.uint8, device=DEV) if nb else None
         out, lse = torch.full_like(qd, 7.0), torch.empty((1, H, nq), dtype=torch.float32, device=DEV)
@@ -91,9 +115,10 @@ def test_segments(name):
         else:
             qw.quantwm_attend_active(cfg, calibs, dcache, n_pk, kd, vd, n_act, qd, nq, q_start, frame, out, lse, ws)
         torch.cuda.synchronize()
-        err = np.abs(out.float().cpu().numpy() - ref).max()
-        assert err <= tol, (nb, err, tol)
-        assert np.abs(lse.cpu().numpy() - rlse).max() <= 2e-2 if dtype == "bf16" else 1e-4
+        err = (np.abs(out.double().cpu().numpy() - ref) / mag).max()
+        assert err <= rel, (nb, err, rel)
+        lerr = np.abs(lse.cpu().numpy() - rlse).max()
+        assert lerr <= ltol, (nb, lerr, ltol)
 
 
 @pytest.mark.parametrize("st", [0, 1], ids=["f16-scales", "i8-scales"])
