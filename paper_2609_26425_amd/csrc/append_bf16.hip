@@ -47,8 +47,9 @@
 // operation order in fp32 with IEEE division and round-to-nearest-even, as in
 // the fp32 kernel.
 //
-// What bounds it: vector issue (about 5,800 instructions per wave at 128
-// centroids, d = 128) and the latency of its chains at two waves per SIMD. With
+// What bounds it: vector issue (about 6,100 instructions per wave at 128
+// centroids, d = 128: 60% of the SIMDs' cycles) and the latency of its chains at two
+// waves per SIMD. With
 // every lane reading centroid rows from global memory the cache's tag lookups
 // did: 64 lines per load instruction. 40 heads x 4,680 tokens, 128 centroids,
 // r = 16: 162 us so, 94 us from LDS; 120 heads x 3,120, 256 centroids, r = 32,

@@ -254,10 +254,10 @@ __device__ inline V pack_operand(const float* x) {
 // plain launch; the softmax state stays in registers. Between two segments the
 // producers stage the next tables while the consumers finish the last tile, so a
 // segment costs a pipeline fill (about three tiles) and nothing else. 40 heads x
-// 4,680 Queries, d = 128, 32,760 keys in 7 epochs: 3.41 ms, against 4.10 ms with a
+// 4,680 Queries, d = 128, 32,760 keys in 7 epochs: 3.53 ms, against 4.18 ms with a
 // plain launch per epoch and a merge of their partial planes. 28,080 packed keys
-// with 8-bit scales + 4,680 exact ones: 3.39 ms, against 5.00 ms in two merged
-// parts. (A plain launch over as many packed keys takes 3.24 ms.)
+// with 8-bit scales + 4,680 exact ones: 3.44 ms, against 5.02 ms in two merged
+// parts. (A plain launch over as many packed keys takes 3.28 ms.)
 template <typename T, int D, int RP, bool LOGITS, bool TAB, bool GEN, bool SI8>
 __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
   typedef Mfma<T> MF;
@@ -680,8 +680,8 @@ __global__ __launch_bounds__(NT) void attend_kernel(const AttendArgs a) {
 
   // rows of the active chunk: keys 64 t .. 64 t + 63 of it; past its end the last
   // row again (the mask hides those keys). The row is clamped, not guarded: with
-  // a guard the compiler folded the per-lane condition into the tile loop, and
-  // the lanes of a wave reached its barrier apart.
+  // a guard the compiler folded the per-lane condition into the tile loop (in its
+  // assembly the loop then ends on the execution mask), and results were wrong.
   auto load_act = [&](ActRegs<KW, VW>& p, int64_t t) __attribute__((always_inline)) {
     const int64_t r0 = t * KT, last = a.n_act - 1;
     load_words(act_row(k_act, r0 + kkey < last ? r0 + kkey : last, kch0), p.k, KW);
