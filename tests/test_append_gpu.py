@@ -25,6 +25,9 @@ CASES = {
     "129-rows": (2, 70, 128, 129, 16, 5, 2, 1, 1),
     "m8": (3, 90, 128, 100, 32, 16, 8, 1, 0),
     "m5-few": (3, 90, 64, 6, 32, 0, 5, 1, 0),
+    "m8-128": (3, 70, 128, 128, 32, 16, 8, 1, 1),
+    "m6-129": (2, 70, 64, 129, 16, 4, 6, 1, 0),
+    "m5-129-waves": (130, 200, 64, 129, 64, 12, 5, 1, 1),
     "m-all": (2, 64, 128, 3, 32, 4, 4, 1, 0),
     "dup-m4": (2, 150, 128, 60, 32, 8, 4, 5, 0),
     "dup-m1": (2, 150, 64, 40, 32, 8, 1, 2, 0),
